@@ -53,6 +53,29 @@ def test_stamp_mask_bit_exact(svc, orc, case):
             assert np.array_equal(mask, want)
 
 
+@pytest.mark.parametrize("shape,offset", [((1, 1), 0), ((700, 3), 0), ((9, 1030), 0), ((70, 128), 0),
+                                          ((70, 128), 3), ((65, 2050), 0)])
+@pytest.mark.parametrize("r_iso,margin,s", [(1, 0, 0), (3, 2, 31), (64, 1, 33), (2, 0, 64)])
+def test_stamp_mask_tile_edges(svc, orc, shape, offset, r_iso, margin, s):
+    """Words, tiles and window clipping at the frame's edges, boxes wider than a
+    word, and masks that do not start on 16 bytes; bit-exact."""
+    import torch
+    H, W = shape
+    r = np.random.default_rng(H * W + s)
+    R = (SKY + r.normal(size=shape) * 30).astype(np.float32)
+    for _ in range(max(2, H * W // 4000)):
+        R[r.integers(H), r.integers(W)] += 4000 * r.random()
+    with svc.Plan(H, W, 1, (1.5,), (0,), 1) as plan:
+        buf = torch.full((H * W + offset,), 7, dtype=torch.uint8).cuda()
+        say("stamp edges", shape, offset, r_iso, margin, s)
+        mask, n = plan.stamp_mask(to_dev(R), SKY, 80.0, 0.5, r_iso=r_iso, margin=margin, stamp_half=s,
+                                  mask=buf[offset:].view(H, W))
+        c = orc.stamp_centres(R, SKY, 80.0, 0.5, r_iso, margin)
+        assert n == len(c)
+        assert np.array_equal(to_host(mask), orc.stamp_mask(H, W, c, s))
+        assert int((buf[:offset] != 7).sum()) == 0
+
+
 def test_add_background(svc, orc):
     H, W, d_s = 50, 70, 3
     b = np.array([3.0, -1.0, 2.0, 0.5, 0.25, -0.75, 0.1, 0.2, -0.3, 0.4], np.float32)
