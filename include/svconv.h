@@ -64,7 +64,9 @@ enum svconv_status {
 /* Arithmetic of the basis contraction (the dominant step); for the
  * SEPARABLE form see below. */
 enum svconv_precision {
-    SVCONV_FP32 = 0,    /* float32 matrix cores (v_mfma_f32_16x16x4_f32)      */
+    SVCONV_FP32 = 0,    /* float32 matrix cores (v_mfma_f32_16x16x4_f32); the
+                           regrouped form and delta bases in float64 on the
+                           vector units                                        */
     SVCONV_BF16 = 1,    /* bf16 inputs, fp32 accumulation, 1 product          */
     SVCONV_FP16 = 2,    /* fp16 inputs, fp32 accumulation, 1 product          */
     SVCONV_BF16X3 = 3,  /* R and B split hi+lo in bf16: hh + lh + hl          */

@@ -1,4 +1,4 @@
-// Regrouped contraction for small kernels on the vector units.
+// Regrouped contraction in float64 on the vector units.
 //
 // D = sum_m P_m (Kt_m (x) R) - I (Eq. 1 with Eq. 2 regrouped: P_m depends
 // only on the output pixel, so the M kernels Kt_m = sum_n a[n][m] B_n carry
@@ -6,172 +6,272 @@
 // coefficient array itself, Kt_m[u,v] = a[n(u,v)][m], so the taps are read
 // straight from a and no per-call table is built.
 //
-// With k <= 9 taps per axis the contraction is 2 M k^2 FLOP per pixel (588 at
-// the paper's 7 x 7, second-order case), too little work per byte for the
-// matrix cores' padded 16-filter blocks to pay: plain float32 FMAs with the
-// taps in scalar registers (uniform over the wave) and the staged tile in
-// LDS.  Each thread owns 8 consecutive output rows of one column; per kernel
-// row it sums the k taps of each spatial term in float32 and adds that row
-// sum into a float64 total, which keeps the float32 rounding to one kernel
-// row's worth.  The pedestal restore s sum_m gamma_m P_m and the subtraction
-// of I are in float64.
+// A thread keeps its column x, and P_m = xh^i yh^j, so the M taps of a kernel
+// pixel fold into d_s + 1 taps b_j(x) = sum_i xh^i Kt_(i,j), one per power of
+// yh, once for all the rows the thread owns: d_s + 1 products per tap and
+// pixel instead of M (3 instead of 6 at second order), plus M - 1 per tap and
+// column.  Everything is float64: on this chip a float64 FMA issues at the rate
+// of an unpacked float32 one (4 cycles a wave), so what float32 products with
+// float64 row sums spent on conversions and additions is saved as well, and D
+// is rounded once.  The taps arrive by scalar loads (uniform over the wave).
 //
-// Workgroup: 256 threads, output tile 64 x 32 (4 row groups of 8 rows).
+// Bound: the float64 FMA rate (161 FMAs and 74 other vector instructions per
+// pixel at 7 x 7, second order; the vector units issue on about three quarters
+// of the cycles).  7 x 7 delta basis, second order, 4846 x 4868: 315 us
+// (float32 FMAs over six terms, float64 row sums) -> 194 us, error against
+// float64 4.0e-8 -> 2.5e-8 of D; 21 x 21, 49 bases, second order, 2048 x 4096:
+// 741 us (float32 matrix cores) -> 432 us; 31 x 31, third order, 2048 x 2048:
+// 1323 -> 715 us.
+//
+// Per kernel column du and DR_CH kernel rows (an item), the samples the
+// thread's rows need are read from LDS once and widened.  ROWS = 16 rows per
+// thread amortise the folding and the windows; where the frame is too small to
+// fill the chip with such waves, S waves share the same pixels and take every
+// S-th item, and their sums are added through LDS.
 #include "internal.hpp"
 #include "sep_fold.hpp"
 
 namespace svc {
 
-constexpr int DR_TW = 64, DR_TH = 32, DR_NT = 256, DR_RPT = 8;
+constexpr int DR_TW = 64;
+constexpr int DR_CH = 7;        // kernel rows per window: 7 and 21 rows are whole windows
+constexpr int DR_STAGE = 8;     // staging loads in flight per thread
 
-// DFB: tap (m, dv, du) = a[(k^2 - 1 - (dv k + du)) M + m] (the delta basis in
-// correlation orientation); otherwise taps[m][dv][du] (the regrouped filters).
-template <int H, int DS, bool DFB>
-__global__ __launch_bounds__(DR_NT) void contract_direct_kernel(DirectArgs a) {
-    constexpr int K = 2 * H + 1;
-    constexpr int M = (DS + 1) * (DS + 2) / 2;
-    constexpr int SR = DR_TH + 2 * H, SC = DR_TW + 2 * H;
-    __shared__ float tile[SR][SC];
-    __shared__ double gam_s[M];
+// DFB: taps is a itself (float32), tap (m, dv, du) = a[(k^2 - 1 - (dv k + du)) M + m]
+// (the delta basis in correlation orientation); otherwise taps64[du][dv][m].
+template <int J, int ROWS, int WAVES, int S, bool DFB>
+__global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs a) {
+    constexpr int DS = J - 1, M = J * (J + 1) / 2;
+    constexpr int NT = 64 * WAVES, TH = ROWS * WAVES / S;
+    extern __shared__ float tile[];
+    const int h = a.h, K = 2 * h + 1;
+    const int SC = DR_TW + 2 * h, SR = TH + 2 * h;
 
-    const int tid = threadIdx.x, c = tid & 63, rg = tid >> 6;
-    const int tx = blockIdx.x % a.tiles_x, ty = blockIdx.x / a.tiles_x;
-    const int X0 = tx * DR_TW, Y0 = ty * DR_TH;
-    const cptr<float> tp = as_const(a.taps);
-    auto tap = [&](int m, int t) -> float { return DFB ? tp[(K * K - 1 - t) * M + m] : tp[m * K * K + t]; };
+    const int tid = threadIdx.x, c = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ty = blockIdx.x / a.tiles_x, tx = blockIdx.x - ty * a.tiles_x;
+    const int X0 = tx * DR_TW, Y0 = ty * TH;
 
-    // stage R - s; R = 0 outside the image.  Every sample is loaded from a
-    // clamped, in-image address and none conditionally, so that all loads are
-    // in flight together; the image mask applies when storing.
-    constexpr int SITER = (SR * SC + DR_NT - 1) / DR_NT;
-    float sv[SITER];
+    // stage R, 0 outside the image: loads from clamped addresses, several rows
+    // in flight, masks at the store.  First 64 columns of whole rows (scalar
+    // row addresses), then the 2 h columns right of them.
+    {
+        const int gx = X0 - h + c;
+        const unsigned gxc = min(max(gx, 0), a.W - 1);
+        const bool inx = gx >= 0 && gx < a.W;
+        for (int r0 = wave; r0 < SR; r0 += WAVES * DR_STAGE) {
+            float v[DR_STAGE];
 #pragma unroll
-    for (int i = 0; i < SITER; ++i) {
-        const int q = min(tid + i * DR_NT, SR * SC - 1);
-        const int r = q / SC, cc = q - r * SC;
-        const int gy = min(max(Y0 - H + r, 0), a.H - 1), gx = min(max(X0 - H + cc, 0), a.W - 1);
-        sv[i] = a.X[(size_t)gy * a.W + gx];
-    }
+            for (int b = 0; b < DR_STAGE; ++b) {
+                const int gy = min(max(Y0 - h + r0 + WAVES * b, 0), a.H - 1);
+                v[b] = (a.X + (size_t)gy * a.W)[gxc];
+            }
 #pragma unroll
-    for (int i = 0; i < SITER; ++i) {
-        const int q = tid + i * DR_NT;
-        if (q < SR * SC) {
-            const int r = q / SC, cc = q - r * SC;
-            const int gy = Y0 - H + r, gx = X0 - H + cc;
-            const float x = (gy >= 0 && gy < a.H && gx >= 0 && gx < a.W) ? sv[i] : 0.f;
-            tile[r][cc] = x - a.ped;
+            for (int b = 0; b < DR_STAGE; ++b) {
+                const int r = r0 + WAVES * b, gy = Y0 - h + r;
+                if (r < SR) tile[r * SC + c] = (inx && gy >= 0 && gy < a.H) ? v[b] : 0.f;
+            }
         }
-    }
-    // pedestal sums gamma_m = sum of Kt_m's taps (float64)
-    if (tid < M) {
-        double s = 0.0;
-        for (int t = 0; t < K * K; ++t) s += (double)tap(tid, t);
-        gam_s[tid] = s;
+        const int n = SR * 2 * h;
+        const float inv = 1.f / (float)(2 * h);
+        for (int q0 = tid; q0 < n; q0 += NT * DR_STAGE) {
+            float v[DR_STAGE];
+            int at[DR_STAGE];
+#pragma unroll
+            for (int b = 0; b < DR_STAGE; ++b) {
+                // q / 2 h: exact, as q < 2^14 and (q + 1/2) / 2 h is 1/124 from an integer at least
+                const int q = min(q0 + NT * b, n - 1), r = (int)(((float)q + 0.5f) * inv);
+                const int cc = DR_TW + q - r * 2 * h;
+                const int gy = Y0 - h + r, gx2 = X0 - h + cc;
+                at[b] = r * SC + cc;
+                const float s = a.X[(size_t)min(max(gy, 0), a.H - 1) * a.W + min(max(gx2, 0), a.W - 1)];
+                v[b] = (gy >= 0 && gy < a.H && gx2 >= 0 && gx2 < a.W) ? s : 0.f;
+            }
+#pragma unroll
+            for (int b = 0; b < DR_STAGE; ++b) tile[at[b]] = v[b];   // past the end: the last sample again
+        }
     }
     __syncthreads();
 
-    double tot[DR_RPT][M];
+    const int x = X0 + c;
+    const double xh = a.sx * x + a.ox;
+    double acc[J][ROWS];
 #pragma unroll
-    for (int o = 0; o < DR_RPT; ++o)
+    for (int j = 0; j < J; ++j)
 #pragma unroll
-        for (int m = 0; m < M; ++m) tot[o][m] = 0.0;
+        for (int r = 0; r < ROWS; ++r) acc[j][r] = 0.0;
 
+    // taps of a kernel pixel at a byte offset: uniform, so they arrive by scalar loads
+    typedef typename std::conditional<DFB, float, double>::type tap_t;
+    struct Taps { tap_t v[M]; };
+    const cptr<char> taps = (cptr<char>)(DFB ? (const void*)a.taps : (const void*)a.taps64);
+    auto load_taps = [&](unsigned off) {
+        Taps t;
+        const cptr<tap_t> p = (cptr<tap_t>)(taps + off);
+#pragma unroll
+        for (int m = 0; m < M; ++m) t.v[m] = p[m];
+        return t;
+    };
+    // byte offset of (dv, du), and from there to (dv + 1, du)
+    constexpr unsigned TB = M * sizeof(tap_t);
+    auto offset = [&](int dv, int du) {
+        return (unsigned)(DFB ? K * K - 1 - (dv * K + du) : du * K + dv) * TB;
+    };
+    const unsigned down = DFB ? 0u - (unsigned)K * TB : TB;
+    const int group = S == 1 ? wave : wave / S, member = S == 1 ? 0 : wave % S;
+    // items in order of du, then dv0; this wave takes items member, member + S, ...
+    const unsigned n_ch = (K + DR_CH - 1) / DR_CH, inv_ch = 65536u / n_ch + 1u;
+    unsigned item = member;
+    int du, dv0;
+    auto place = [&]() {
+        du = (int)((item * inv_ch) >> 16);   // item / n_ch: exact, as item <= 63 x 9 + 8
+        dv0 = (int)(item - du * n_ch) * DR_CH;
+    };
+    place();
+    unsigned off = offset(dv0, min(du, K - 1));
+    Taps next = load_taps(off);
 #pragma unroll 1
-    for (int dv0 = 0; dv0 < K; ++dv0) {
-        // the kernel row's taps: uniform addresses with constant offsets, so they
-        // arrive by scalar loads
-        const int dv = __builtin_amdgcn_readfirstlane(dv0);
-        float tv[K][M];
-        if constexpr (DFB) {
-            const cptr<float> row = tp + (K * K - K - dv * K) * M;   // du = K - 1 at the lowest address
+    while (du < K) {
+        double s[ROWS + DR_CH - 1];
+        const float* col = tile + (group * ROWS + dv0) * SC + c + du;
 #pragma unroll
-            for (int du = 0; du < K; ++du)
+        for (int i = 0; i < ROWS + DR_CH - 1; ++i) s[i] = (double)col[i * SC];
+        const int n = K - dv0;   // taps of this item, if fewer than DR_CH
+        item += S;
+        place();
+        const unsigned off_item = offset(dv0, min(du, K - 1));
 #pragma unroll
-                for (int m = 0; m < M; ++m) tv[du][m] = row[(K - 1 - du) * M + m];
-        } else {
-            const cptr<float> row = tp + dv * K;
+        for (int i = 0; i < DR_CH; ++i) {
+            if (i < n) {   // uniform
+                // the taps of the next kernel pixel are requested before the
+                // products of this one
+                const Taps t = next;
+                off = (i + 1 < DR_CH && i + 1 < n) ? off + down : off_item;
+                next = load_taps(off);
+                __builtin_amdgcn_sched_barrier(0);
+                // spatial term m = q (q + 1) / 2 + j is xh^(q - j) yh^j
+                double b[J];
 #pragma unroll
-            for (int du = 0; du < K; ++du)
+                for (int j = 0; j < J; ++j) {
+                    b[j] = (double)t.v[DS * (DS + 1) / 2 + j];
 #pragma unroll
-                for (int m = 0; m < M; ++m) tv[du][m] = row[m * K * K + du];
-        }
+                    for (int q = DS - 1; q >= j; --q) b[j] = fma(b[j], xh, (double)t.v[q * (q + 1) / 2 + j]);
+                }
 #pragma unroll
-        for (int o = 0; o < DR_RPT; ++o) {
-            const float* row = &tile[DR_RPT * rg + o + dv][c];
-            float racc[M];
+                for (int r = 0; r < ROWS; ++r)
 #pragma unroll
-            for (int m = 0; m < M; ++m) racc[m] = 0.f;
-#pragma unroll
-            for (int du = 0; du < K; ++du) {
-                const float smp = row[du];
-#pragma unroll
-                for (int m = 0; m < M; ++m) racc[m] = fmaf(tv[du][m], smp, racc[m]);
+                    for (int j = 0; j < J; ++j) acc[j][r] = fma(b[j], s[r + i], acc[j][r]);
             }
-#pragma unroll
-            for (int m = 0; m < M; ++m) tot[o][m] += (double)racc[m];
         }
     }
 
-    const int x = X0 + c;
+    // this wave's part of D at its rows
+    const int y0 = Y0 + group * ROWS;
+    double v[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const double yh = a.sy * (y0 + r) + a.oy;
+        v[r] = acc[DS][r];
+#pragma unroll
+        for (int j = DS - 1; j >= 0; --j) v[r] = fma(v[r], yh, acc[j][r]);
+    }
+    // with S waves on the same pixels each finishes 1 / S of the rows
+    constexpr int RW = ROWS / S;
+    if constexpr (S > 1) {
+        double* red = reinterpret_cast<double*>(tile);   // [WAVES][ROWS][64], over the samples
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) red[(wave * ROWS + r) * 64 + c] = v[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            double t = 0.0;
+#pragma unroll
+            for (int q = 0; q < S; ++q) t += red[((group * S + q) * ROWS + member * RW + r) * 64 + c];
+            v[r] = t;
+        }
+    }
     if (x >= a.W) return;
     // I at this thread's pixels, all requested at once from clamped addresses
     // (without I, R stands in for the loads)
-    float iv[DR_RPT];
+    const int yo = y0 + member * RW;
+    float iv[RW];
     {
         const float* ip = a.I ? a.I : a.X;
 #pragma unroll
-        for (int o = 0; o < DR_RPT; ++o) iv[o] = ip[(size_t)min(Y0 + DR_RPT * rg + o, a.H - 1) * a.W + x];
+        for (int r = 0; r < RW; ++r) iv[r] = ip[(size_t)min(yo + r, a.H - 1) * a.W + x];
     }
-    const double xh = a.sx * x + a.ox;
-    double xp[DS + 1];
-    xp[0] = 1.0;
 #pragma unroll
-    for (int q = 1; q <= DS; ++q) xp[q] = xp[q - 1] * xh;
-#pragma unroll
-    for (int o = 0; o < DR_RPT; ++o) {
-        const int y = Y0 + DR_RPT * rg + o;
+    for (int r = 0; r < RW; ++r) {
+        const int y = yo + r;
         if (y >= a.H) break;
-        const double yh = a.sy * y + a.oy;
-        double yp[DS + 1];
-        yp[0] = 1.0;
-#pragma unroll
-        for (int q = 1; q <= DS; ++q) yp[q] = yp[q - 1] * yh;
-        // spatial term m = t (t + 1) / 2 + j is xh^(t - j) yh^j
-        double v = 0.0;
-        int m = 0;
-#pragma unroll
-        for (int t = 0; t <= DS; ++t)
-#pragma unroll
-            for (int j = 0; j <= t; ++j, ++m)
-                v = fma(xp[t - j] * yp[j], fma((double)a.ped, gam_s[m], tot[o][m]), v);
-        const size_t idx = (size_t)y * a.W + x;
-        a.out[idx] = (float)(a.I ? v - (double)iv[o] : v);
+        a.out[(size_t)y * a.W + x] = (float)(a.I ? v[r] - (double)iv[r] : v[r]);
     }
 }
 
-template <int H, bool DFB>
-static void launch_direct_h(const DirectArgs& a, dim3 grid, hipStream_t s) {
-    switch (a.d_s) {
-        case 0: hipLaunchKernelGGL((contract_direct_kernel<H, 0, DFB>), grid, dim3(DR_NT), 0, s, a); break;
-        case 1: hipLaunchKernelGGL((contract_direct_kernel<H, 1, DFB>), grid, dim3(DR_NT), 0, s, a); break;
-        default: hipLaunchKernelGGL((contract_direct_kernel<H, 2, DFB>), grid, dim3(DR_NT), 0, s, a); break;
-    }
+// taps64[du][dv][m] = sum_n a[n][m] F_n[dv][du] (the regrouped filters)
+__global__ void regroup64_kernel(const double* __restrict__ F64, const float* __restrict__ a, int N, int M, int k,
+                                 double* __restrict__ taps) {
+    const int kk = k * k;
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= M * kk) return;
+    const int m = idx / kk, q = idx - m * kk;
+    double s = 0.0;
+#pragma unroll 8
+    for (int n = 0; n < N; ++n) s += (double)a[n * M + m] * F64[(size_t)n * kk + q];
+    const int dv = q / k, du = q - dv * k;
+    taps[(du * k + dv) * M + m] = s;
 }
 
-bool direct_supported(int h, int d_s) { return h >= 1 && h <= kDirectMaxHalfWidth && d_s <= 2; }
+int regroup_filters64(const double* F64, const float* a, int N, int M, int k, double* taps, hipStream_t s) {
+    hipLaunchKernelGGL(regroup64_kernel, dim3((M * k * k + 127) / 128), dim3(128), 0, s, F64, a, N, M, k, taps);
+    return hip_status(hipGetLastError(), "regroup64_kernel");
+}
 
-int launch_contract_direct(DirectArgs a, bool dfb, hipStream_t s) {
-    if (!direct_supported(a.h, a.d_s) || a.M != (a.d_s + 1) * (a.d_s + 2) / 2)
-        return fail(SVCONV_EUNSUPPORTED, "direct regrouped kernel needs 1 <= half-width <= 4 and spatial degree <= 2");
+static int direct_tiles(const DirectArgs& a, int th) { return a.tiles_x * ((a.H + th - 1) / th); }
+
+template <int J, int ROWS, int WAVES, int S>
+static void launch_direct(const DirectArgs& a, hipStream_t s) {
+    constexpr int TH = ROWS * WAVES / S;
+    // the rows of the last window are read past the tile's 2 h halo rows, unused
+    const int k = 2 * a.h + 1, rows = TH + (k + DR_CH - 1) / DR_CH * DR_CH - 1;
+    size_t lds = (size_t)rows * (DR_TW + 2 * a.h) * sizeof(float);
+    if (S > 1 && lds < (size_t)WAVES * ROWS * 64 * sizeof(double)) lds = (size_t)WAVES * ROWS * 64 * sizeof(double);
+    const dim3 grid(direct_tiles(a, TH)), block(64 * WAVES);
+    if (a.taps64)
+        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, false>), grid, block, lds, s, a);
+    else
+        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, true>), grid, block, lds, s, a);
+}
+
+template <int J>
+static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
+    // above third order the totals of 16 rows no longer fit the registers.
+    // (8 rows at second order: more waves, but 13 % more instructions per pixel,
+    // 435 -> 471 us at 21 x 21, 2048 x 4096)
+    constexpr int ROWS = J <= 4 ? 16 : 8, CUS = 256;
+    // whole tiles per wave while they give every CU three workgroups (what the
+    // registers hold); then four waves on the same pixels, and eight where
+    // even those tiles leave CUs with less than two (21 x 21 at 512 x 512: 127
+    // us with one wave per 4 rows, 26 us with eight on 16 rows).  A 3 x 3 or 5
+    // x 5 kernel has no eight items to share.
+    if (direct_tiles(a, 4 * ROWS) >= 3 * CUS) return launch_direct<J, ROWS, 4, 1>(a, s);
+    if (direct_tiles(a, ROWS) >= 2 * CUS || a.h < 3) return launch_direct<J, ROWS, 4, 4>(a, s);
+    launch_direct<J, ROWS, 8, 8>(a, s);
+}
+
+int launch_contract_direct(DirectArgs a, hipStream_t s) {
     a.tiles_x = (a.W + DR_TW - 1) / DR_TW;
-    const int tiles = a.tiles_x * ((a.H + DR_TH - 1) / DR_TH);
-    if (tiles == 0) return SVCONV_OK;
-    const dim3 grid(tiles);
-    switch (a.h) {
-        case 1: dfb ? launch_direct_h<1, true>(a, grid, s) : launch_direct_h<1, false>(a, grid, s); break;
-        case 2: dfb ? launch_direct_h<2, true>(a, grid, s) : launch_direct_h<2, false>(a, grid, s); break;
-        case 3: dfb ? launch_direct_h<3, true>(a, grid, s) : launch_direct_h<3, false>(a, grid, s); break;
-        default: dfb ? launch_direct_h<4, true>(a, grid, s) : launch_direct_h<4, false>(a, grid, s); break;
+    if (a.h < 0 || a.h > kMaxHalfWidth || a.H <= 0 || a.W <= 0 || !a.taps == !a.taps64)
+        return fail(SVCONV_EUNSUPPORTED, "direct regrouped kernel: bad arguments");
+    switch (a.d_s) {
+        case 0: launch_direct_rows<1>(a, s); break;
+        case 1: launch_direct_rows<2>(a, s); break;
+        case 2: launch_direct_rows<3>(a, s); break;
+        case 3: launch_direct_rows<4>(a, s); break;
+        case 4: launch_direct_rows<5>(a, s); break;
+        case 5: launch_direct_rows<6>(a, s); break;
+        case 6: launch_direct_rows<7>(a, s); break;
+        default: return fail(SVCONV_EUNSUPPORTED, "direct regrouped kernel needs spatial degree <= 6");
     }
     return hip_status(hipGetLastError(), "contract_direct_kernel");
 }

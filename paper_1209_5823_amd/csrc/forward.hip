@@ -466,17 +466,27 @@ int regroup_filters(const double* F64, const double* beta, const float* a, int N
 // F'_m'[dv][du] = H_m'[u = du - h][v = dv - h].  The float64 basis table holds
 // F_n[dv][du] = B_n[2h - dv][2h - du], so B_n[u][v] (row v+h, column u+h)
 // = F_n[h - v][h - u].
-__global__ void adjoint_filter_kernel(const double* __restrict__ F64, const float* __restrict__ a,
-                                      int N, int M, int k, double sx, double sy,
-                                      float* __restrict__ Ft) {
-    const int kk = k * k;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= M * kk) return;
-    const int mp = idx / kk, q = idx - mp * kk;
+// One workgroup per kernel pixel: lane m forms Kt_m there (float64), then
+// every H_m' from those M values, each in its place [du][dv][M] for the
+// float64 direct contraction (one thread per (m', pixel) would form Kt anew
+// for each m').
+__global__ __launch_bounds__(64) void adjoint_filter_kernel(const double* __restrict__ F64,
+                                                            const float* __restrict__ a, int N, int M, int k,
+                                                            double sx, double sy, double* __restrict__ taps) {
+    __shared__ double kt[kMaxSpatialTerms];
+    const int kk = k * k, q = blockIdx.x, mp = threadIdx.x;
     const int dv = q / k, du = q - dv * k;
     const int h = k / 2;
     const int u = du - h, v = dv - h;
     const int fq = (h - v) * k + (h - u);  // F_n index holding B_n[u][v]
+    if (mp < M) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int n = 0; n < N; ++n) s += (double)a[n * M + mp] * F64[(size_t)n * kk + fq];
+        kt[mp] = s;
+    }
+    __syncthreads();
+    if (mp >= M) return;
     int ip, jp;
     term_exponents(mp, ip, jp);
     double acc = 0.0;
@@ -484,8 +494,6 @@ __global__ void adjoint_filter_kernel(const double* __restrict__ F64, const floa
         int i, jj;
         term_exponents(m, i, jj);
         if (i < ip || jj < jp) continue;
-        double kt = 0.0;
-        for (int n = 0; n < N; ++n) kt += (double)a[n * M + m] * F64[(size_t)n * kk + fq];
         // binomials C(i, ip) C(jj, jp)
         double ci = 1.0, cj = 1.0;
         for (int t = 1; t <= ip; ++t) ci = ci * (i - ip + t) / t;
@@ -493,17 +501,14 @@ __global__ void adjoint_filter_kernel(const double* __restrict__ F64, const floa
         double px = 1.0, py = 1.0;
         for (int t = 0; t < i - ip; ++t) px *= u * sx;
         for (int t = 0; t < jj - jp; ++t) py *= v * sy;
-        acc += ci * cj * px * py * kt;
+        acc += ci * cj * px * py * kt[m];
     }
-    Ft[idx] = (float)acc;
+    taps[(du * k + dv) * M + mp] = acc;
 }
 
-int adjoint_filters(const double* F64, const float* a, int N, int M, int d_s, int k, double sx,
-                    double sy, float* Ft, hipStream_t s) {
-    (void)d_s;
-    const int total = M * k * k;
-    hipLaunchKernelGGL(adjoint_filter_kernel, dim3((total + 255) / 256), dim3(256), 0, s, F64, a,
-                       N, M, k, sx, sy, Ft);
+int adjoint_filters(const double* F64, const float* a, int N, int M, int k, double sx, double sy, double* taps,
+                    hipStream_t s) {
+    hipLaunchKernelGGL(adjoint_filter_kernel, dim3(k * k), dim3(64), 0, s, F64, a, N, M, k, sx, sy, taps);
     return hip_status(hipGetLastError(), "adjoint_filter_kernel");
 }
 

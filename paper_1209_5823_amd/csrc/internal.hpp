@@ -116,15 +116,15 @@ struct SepZArgs {
     const double* gam;          // [kSepCoefPad] sum_n a[n][m] beta_n, zero-padded
 };
 
-// Regrouped contraction of small kernels on the vector units (direct.hip).
-constexpr int kDirectMaxHalfWidth = 4;
+// Regrouped contraction in float64 on the vector units (direct.hip).
 struct DirectArgs {
     const float* X;             // [H][W]
     const float* I;             // nullable
     float* out;                 // [H][W]
-    int H, W, h, d_s, M;
-    float ped;
-    const float* taps;          // Dirac delta basis: a [k^2][M]; otherwise Kt [M][k][k] (correlation order)
+    int H, W, h, d_s;
+    // exactly one of the two is set:
+    const float* taps;          // Dirac delta basis: a [k^2][M]
+    const double* taps64;       // otherwise: regrouped filters [du][dv][M] (regroup_filters64)
     double sx, ox, sy, oy;
     int tiles_x;
 };
@@ -170,9 +170,9 @@ struct svconv_plan {
     float* dScaleH = nullptr;           // [2][kMaxFilters] scales / inverse scales, fp16 fragments
 
     // per-call scratch (allocated once)
-    float* dFt32 = nullptr;             // [kMaxFilters][k][k] per-call filters (regrouped / adjoint)
+    float* dFt32 = nullptr;             // [kMaxFilters][k][k] per-call filters (regrouped / adjoint; 8-byte
+                                        // taps of the direct kernel: 2 M <= kMaxFilters)
     double* dBetaT = nullptr;           // [kMaxFilters]
-    float* dFragT32 = nullptr;          // fragments of per-call filters (FP32)
     uint16_t* dFragTB = nullptr;        // per-call bf16 fragments
     uint16_t* dFragTH = nullptr;        // per-call fp16 fragments
     float* dScaleT = nullptr;           // [2][kMaxFilters] per-call scales / inverse scales
@@ -208,8 +208,9 @@ int build_lowp_fragments(const float* F, int NF, int k, int fp16, float* scale,
 bool lowp_packed(const ContractArgs& a, int nb);
 int regroup_filters(const double* F64, const double* beta, const float* a, int N, int M, int k,
                     float* Ft, double* betaT, hipStream_t s);
-int adjoint_filters(const double* F64, const float* a, int N, int M, int d_s, int k,
-                    double sx, double sy, float* Ft, hipStream_t s);
+// filters of the adjoint in R, laid out as taps64 of the direct contraction
+int adjoint_filters(const double* F64, const float* a, int N, int M, int k, double sx, double sy, double* taps,
+                    hipStream_t s);
 int launch_contract_f32(const ContractArgs& a, const float* frag, int nb, hipStream_t s);
 int launch_contract_lowp(const ContractArgs& a, const uint16_t* frag, int nb, int precision,
                          hipStream_t s);
@@ -243,8 +244,8 @@ int launch_sepz_prep(const SepZArgs& z, const float* a, const double* f1d, const
 int launch_contract_sepz(SepZArgs a, int precision, hipStream_t s);
 
 // direct.hip
-bool direct_supported(int h, int d_s);
-int launch_contract_direct(DirectArgs a, bool dfb, hipStream_t s);
+int regroup_filters64(const double* F64, const float* a, int N, int M, int k, double* taps, hipStream_t s);
+int launch_contract_direct(DirectArgs a, hipStream_t s);
 
 // Both separable forms go through the one-dimensional factors in the adjoints
 // and the fit.

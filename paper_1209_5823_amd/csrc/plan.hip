@@ -74,7 +74,7 @@ static void free_plan(svconv_plan* p) {
     void* ptrs[] = {p->dSep1d, p->dSepFam, p->dSepCoef, p->dSepFrag, p->dSepMom, p->dSepRinfo,
                     p->dSepZRow, p->dSepZTab, p->dSepZInv, p->dSepZGam,
                     p->dF32,   p->dF64,   p->dBeta,   p->dFragF32, p->dFragLoB, p->dFragLoH,
-                    p->dScaleB, p->dScaleH, p->dFt32, p->dBetaT, p->dFragT32, p->dFragTB,  p->dFragTH,
+                    p->dScaleB, p->dScaleH, p->dFt32, p->dBetaT, p->dFragTB,  p->dFragTH,
                     p->dScaleT, p->dQpart, p->dQ,    p->dGrad,    p->dVec,     p->dStatus,
                     p->dNMpart, p->dTband, p->dRed};
     for (void* q : ptrs)
@@ -138,7 +138,6 @@ static int finish_plan(svconv_plan* p, svconv_plan** out) {
     // more kernel pixels is contracted in the regrouped form only)
     const int nbN = p->N <= kMaxFilters ? (p->N + 15) / 16 : 1;
     const size_t frag32 = f32_fragment_floats(k, nbN);
-    const size_t fragT32 = f32_fragment_floats(k, (kMaxSpatialTerms + 15) / 16);
     const size_t fraglN = lowp_fragment_elems(k, nbN);
     const size_t fraglT = lowp_fragment_elems(k, (kMaxSpatialTerms + 15) / 16);
     if ((st = dalloc(&p->dF32, F32.size(), "basis table")) ||
@@ -151,7 +150,6 @@ static int finish_plan(svconv_plan* p, svconv_plan** out) {
         (st = dalloc(&p->dScaleH, (size_t)2 * kMaxFilters, "fp16 scales")) ||
         (st = dalloc(&p->dFt32, (size_t)kMaxFilters * kk, "per-call filters")) ||
         (st = dalloc(&p->dBetaT, (size_t)kMaxFilters, "per-call sums")) ||
-        (st = dalloc(&p->dFragT32, fragT32, "per-call fp32 fragments")) ||
         (st = dalloc(&p->dFragTB, fraglT, "per-call bf16 fragments")) ||
         (st = dalloc(&p->dFragTH, fraglT, "per-call fp16 fragments")) ||
         (st = dalloc(&p->dScaleT, (size_t)2 * kMaxFilters, "per-call scales")) ||
@@ -321,6 +319,28 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
         }
         return launch_contract_sep(sa, p->stream);
     }
+    if (!lowp && (p->form == SVCONV_FORM_REGROUPED || (p->dfb && p->N <= kMaxFilters))) {
+        // regrouped in float64 on the vector units.  The responses of a delta
+        // basis are shifted pixels, so its basis form is the same sum.
+        DirectArgs d{};
+        d.X = R;
+        d.I = I;
+        d.out = out;
+        d.H = p->H;
+        d.W = p->W;
+        d.h = p->h;
+        d.d_s = p->d_s;
+        d.sx = c.sx; d.ox = c.ox; d.sy = c.sy; d.oy = c.oy;
+        if (p->dfb) {
+            d.taps = a;
+        } else {
+            double* taps = reinterpret_cast<double*>(p->dFt32);
+            int st = regroup_filters64(p->dF64, a, p->N, p->M, p->k, taps, p->stream);
+            if (st) return st;
+            d.taps64 = taps;
+        }
+        return launch_contract_direct(d, p->stream);
+    }
     if (p->form == SVCONV_FORM_BASIS) {
         if (p->N > kMaxFilters) return fail(SVCONV_EUNSUPPORTED, "basis form needs N <= 64");
         c.NF = p->N;
@@ -332,29 +352,7 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
         return launch_contract_lowp(c, is_fp16(p->precision) ? p->dFragLoH : p->dFragLoB, nb,
                                     p->precision, p->stream);
     }
-    // regrouped: Kt_m built on the device for this call (the delta basis' Kt_m
-    // is a itself); small kernels in float32 on the vector units
-    if (!lowp && direct_supported(p->h, p->d_s)) {
-        DirectArgs d{};
-        d.X = R;
-        d.I = I;
-        d.out = out;
-        d.H = p->H;
-        d.W = p->W;
-        d.h = p->h;
-        d.d_s = p->d_s;
-        d.M = p->M;
-        d.ped = p->pedestal;
-        d.sx = c.sx; d.ox = c.ox; d.sy = c.sy; d.oy = c.oy;
-        if (p->dfb) {
-            d.taps = a;
-            return launch_contract_direct(d, true, p->stream);
-        }
-        int st = regroup_filters(p->dF64, p->dBeta, a, p->N, p->M, p->k, p->dFt32, p->dBetaT, p->stream);
-        if (st) return st;
-        d.taps = p->dFt32;
-        return launch_contract_direct(d, false, p->stream);
-    }
+    // regrouped on the 16-bit matrix cores: Kt_m built on the device for this call
     if (p->M > 32) return fail(SVCONV_EUNSUPPORTED, "regrouped form needs M <= 32");
     int st = regroup_filters(p->dF64, p->dBeta, a, p->N, p->M, p->k, p->dFt32, p->dBetaT, p->stream);
     if (st) return st;
@@ -362,11 +360,6 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
     c.coef = nullptr;
     c.beta = p->dBetaT;
     const int nb = (p->M + 15) / 16;
-    if (!lowp) {
-        st = build_f32_fragments(p->dFt32, p->M, p->k, p->dFragT32, p->stream);
-        if (st) return st;
-        return launch_contract_f32(c, p->dFragT32, nb, p->stream);
-    }
     const bool h16 = is_fp16(p->precision);
     uint16_t* frag = h16 ? p->dFragTH : p->dFragTB;
     c.fscale = p->dScaleT + kMaxFilters;
@@ -621,26 +614,20 @@ int svconv_backward(svconv_plan* p, const float* R, const float* a, const float*
         if (st) return st;
     } else if (gR) {
         ContractArgs c{};
-        c.X = gD;
-        c.H = p->H;
-        c.W = p->W;
-        c.h = p->h;
-        c.M = p->M;
-        c.d_s = p->d_s;
-        c.ped = 0.f;
-        c.I = nullptr;
-        c.out = gR;
-        c.y_begin = 0;
-        c.n_rows = p->H;
         coords(p, c);
-        st = adjoint_filters(p->dF64, a, p->N, p->M, p->d_s, p->k, c.sx, c.sy, p->dFt32, p->stream);
+        double* taps = reinterpret_cast<double*>(p->dFt32);
+        st = adjoint_filters(p->dF64, a, p->N, p->M, p->k, c.sx, c.sy, taps, p->stream);
         if (st) return st;
-        st = build_f32_fragments(p->dFt32, p->M, p->k, p->dFragT32, p->stream);
-        if (st) return st;
-        c.NF = p->M;
-        c.coef = nullptr;
-        c.beta = nullptr;
-        st = launch_contract_f32(c, p->dFragT32, (p->M + 15) / 16, p->stream);
+        DirectArgs d{};
+        d.X = gD;
+        d.out = gR;
+        d.H = p->H;
+        d.W = p->W;
+        d.h = p->h;
+        d.d_s = p->d_s;
+        d.taps64 = taps;
+        d.sx = c.sx; d.ox = c.ox; d.sy = c.sy; d.oy = c.oy;
+        st = launch_contract_direct(d, p->stream);
         if (st) return st;
     }
     if (ga) st = run_adjoint_a(p, R, gD, ga);
