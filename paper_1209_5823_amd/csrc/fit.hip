@@ -84,181 +84,251 @@ int launch_loss_grad(svconv_plan* p, const float* D, const unsigned char* mask, 
 
 // --------------------------------------------------- normal matrix ----
 
-constexpr int NM_PIX_CHUNK = 4096;    // pixels per workgroup and band
-constexpr size_t NM_BAND_BYTES = (size_t)512 << 20;
+constexpr int NM_PIX_CHUNK = 4096;    // most pixels of one segment
+constexpr size_t NM_BAND_BYTES = (size_t)512 << 20;   // basis responses of a band
+constexpr size_t NM_PART_BYTES = (size_t)256 << 20;   // its partial sums
+constexpr int NM_CHUNKS = 32;         // partial sums of the reduction over segments
 
-__device__ __forceinline__ double ipow_f(double x, int e) {
-    double r = 1.0;
-    for (int t = 0; t < e; ++t) r *= x;
-    return r;
+// The planes X_0 .. X_(P-1) whose products are summed: the basis responses,
+// then (with a background) the constant 1, then (with a right-hand side) I.
+struct GramPlanes {
+    const float* T;             // responses [N][rows][W] of the band; or R itself for a delta basis
+    size_t stride;              // rows * W
+    int dfb_k;                  // > 0: plane n is R shifted by the kernel pixel n of this width
+    int N, P;
+    const float* ones;          // [W + 16] of 1
+    const float* I;             // [H][W], nullable
+};
+
+struct GramArgs {
+    GramPlanes q;
+    int W, y_begin, segs, cpr, seg_len, x_lo, x_hi, n_a;
+    const unsigned char* mask;  // nullable
+    const double* xw;           // [n_a][W] xh^a, 0 outside the interior when mask is null
+    double* part;               // [segs][n_a][E]
+};
+
+// X_p at row y, band row `row`: pointer to its column 0
+__device__ __forceinline__ const float* plane_row(const GramPlanes& q, int p, int row, int y, int W) {
+    if (p >= q.N) return (q.I && p == q.P - 1) ? q.I + (size_t)y * W : q.ones;
+    if (q.dfb_k) {
+        const int h = q.dfb_k / 2, v = p / q.dfb_k - h, u = p % q.dfb_k - h;
+        return q.T + (long)(y - v) * W - u;
+    }
+    return q.T + p * q.stride + (size_t)row * W;
 }
 
-// G_part[seg][a][n][n'] for 64 x 64 (n, n') and one power a of xh per
-// workgroup; a segment is up to NM_PIX_CHUNK pixels of one row of the band.
-// The 16 x 16 blocks with row block <= column block are formed (the waves
-// share them out); blocks whose rows or columns are all padding are skipped.
-// A operand: T_n(p_k); B operand: T_n'(p_k) xh^a mask.
-constexpr int GRAM_WAVES = 5;   // two of the 10 block pairs per wave
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 
-__global__ __launch_bounds__(64 * GRAM_WAVES) void gram_kernel(const float* __restrict__ T, int N, int band_px,
-                                                   int y_begin, int W, int H, int h, int cpr,
-                                                   const unsigned char* __restrict__ mask,
-                                                   double sx, double ox, int n_a,
-                                                   double* __restrict__ part) {
-    const int ea = blockIdx.x;
-    const int seg = blockIdx.y;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int kq = lane >> 4, j = lane & 15;
-    const int row = seg / cpr, x_begin = (seg - row * cpr) * NM_PIX_CHUNK;
-    const int x_end = min(W, x_begin + NM_PIX_CHUNK);
-    const int y = y_begin + row;
+// G_a[p][p'] = sum over a segment (up to NM_PIX_CHUNK pixels of one row) of
+// mask xh^a X_p X_p', by one wave per segment and power a on the float64
+// matrix cores.  The planes are taken as NBF blocks of 16 and R planes over.
+// One register serves as both operands (lane (kq, j) of the 16x16x4
+// instruction holds row j, k = kq of A and column j, k = kq of B: plane j at
+// pixel kq), so a wave that forms all NBF (NBF + 1) / 2 blocks of the upper
+// triangle loads and widens each plane once.  The R planes over (2 of 50 in
+// the 49-basis fits) would cost a block column padded to 16; their products
+// are float64 FMAs on the same registers instead, each lane for its plane and
+// pixel, summed over kq at the end.
+//
+// Bound: float64 matrix cores and vector FMAs, which share an issue rate (66
+// and 4.2 cycles measured per instruction, not overlapped): per 4 pixels and
+// power 10 blocks -> 6 blocks + 19 vector instructions at 50 planes.  2048 x
+// 2048, 50 planes, second order: 2700 -> 1345 us, the reduction below 490 -> 60
+// us; 1024 x 1024, delta basis: 780 -> 324 us.
+//
+// The segments of the powers of one row run on one XCD, whose L2 then serves
+// the n_a passes over its planes.
+template <int NBF, int R>
+__global__ __launch_bounds__(64) void gram_kernel(GramArgs g) {
+    constexpr int NBLK = NBF * (NBF + 1) / 2, NR = R ? NBF + 1 : NBF;   // row blocks read
+    constexpr int E = NBLK * 256 + R * NR * 16;
+    const int xcd = blockIdx.x & 7, i8 = blockIdx.x >> 3;
+    const int ea = i8 % g.n_a, seg = (i8 / g.n_a) * 8 + xcd;
+    if (seg >= g.segs) return;
+    const int lane = threadIdx.x, kq = lane >> 4, j = lane & 15;
+    const int row = seg / g.cpr, x_begin = g.x_lo + (seg - row * g.cpr) * g.seg_len;
+    const int x_end = min(g.x_hi, x_begin + g.seg_len), y = g.y_begin + row;
 
-    // G is symmetric: only the 10 blocks (rb, cb) with rb <= cb of the 4 x 4
-    // block grid are formed, two of them by each of the 5 waves (equal work
-    // on every SIMD)
-    constexpr int PAIRS[10][2] = {{0, 0}, {0, 1}, {0, 2}, {0, 3}, {1, 1},
-                                  {1, 2}, {1, 3}, {2, 2}, {2, 3}, {3, 3}};
-    constexpr int PQ = 2;
-    const int p_begin = PQ * w;
-    d4 acc[PQ];
+    const float* rp[NR];                 // this lane's plane of each row block
+    const float* cp[R ? R : 1];          // the planes over (uniform)
 #pragma unroll
-    for (int q = 0; q < PQ; ++q) acc[q] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int b = 0; b < NR; ++b) rp[b] = plane_row(g.q, min(16 * b + j, g.q.P - 1), row, y, g.W);
+#pragma unroll
+    for (int c = 0; c < R; ++c) cp[c] = plane_row(g.q, min(16 * NBF + c, g.q.P - 1), row, y, g.W);
+    const double* wrow = g.xw + (size_t)ea * g.W;
+    const unsigned char* mrow = g.mask ? g.mask + (size_t)y * g.W : nullptr;
+
+    d4 acc[NBLK];
+    double rem[R ? R : 1][NR];
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b) acc[b] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < R; ++c)
+#pragma unroll
+        for (int b = 0; b < NR; ++b) rem[c][b] = 0.0;
+
     // 16 pixels per step: lane group kq takes pixels x0 + 4 kq .. x0 + 4 kq + 3
-    // (the k slot of instruction s is pixel x0 + 4 kq + s in both operands),
-    // so each lane reads 4 consecutive floats of a filter row
-    const bool vec = (W & 3) == 0;
-    // pixel weights xh^ea (0 outside the mask) of the segment, formed once
-    // per workgroup (x^ea from the binary digits of ea <= 12)
-    __shared__ double wsh[NM_PIX_CHUNK];
-    for (int i = threadIdx.x; i < x_end - x_begin; i += 64 * GRAM_WAVES) {
-        const int x = x_begin + i;
-        const double xh = sx * x + ox, x2 = xh * xh, x4 = x2 * x2, x8 = x4 * x4;
-        wsh[i] = in_mask(mask, H, W, h, x, y) ? ((ea & 1) ? xh : 1.0) * ((ea & 2) ? x2 : 1.0) *
-                                                     ((ea & 4) ? x4 : 1.0) * ((ea & 8) ? x8 : 1.0)
-                                               : 0.0;
-    }
-    __syncthreads();
-    // the lane's block rows of its two block pairs; every operand load
-    // below is unconditional, from a clamped row
-    const float* tb = T + (size_t)row * W + 4 * kq;
-    size_t offa[PQ], offb[PQ];
-    bool use[PQ], ina[PQ], inb[PQ];
+    // (the k slot of instruction s is pixel x0 + 4 kq + s in both operands)
+    struct Step {
+        f4u r[NR], c[R ? R : 1];
+        d2u w[2];
+        unsigned m;
+    };
+    auto load = [&](int x0) {
+        Step o;
+        const int x = x0 + 4 * kq;
 #pragma unroll
-    for (int q = 0; q < PQ; ++q) {
-        const int pi = p_begin + q;
-        const int rb = PAIRS[pi][0], cb = PAIRS[pi][1];
-        use[q] = 16 * rb < N && 16 * cb < N;   // uniform
-        ina[q] = 16 * rb + j < N;
-        inb[q] = 16 * cb + j < N;
-        offa[q] = (size_t)min(16 * rb + j, N - 1) * band_px;
-        offb[q] = (size_t)min(16 * cb + j, N - 1) * band_px;
-    }
-    int x0 = x_begin;
-    if (vec) {
-        // the steps whose 16 pixels are all inside the segment, two per turn:
-        // the operands of one step are requested (into a register set of
-        // their own) before the products of the step before it
-        const int x_full = x_begin + (x_end - x_begin) / 16 * 16;
-        auto load_step = [&](int xs, float4 (&o)[PQ][2]) {
+        for (int b = 0; b < NR; ++b) o.r[b] = *reinterpret_cast<const f4u*>(rp[b] + x);
 #pragma unroll
-            for (int q = 0; q < PQ; ++q) {
-                o[q][0] = *reinterpret_cast<const float4*>(tb + offa[q] + xs);
-                o[q][1] = *reinterpret_cast<const float4*>(tb + offb[q] + xs);
-            }
-        };
-        auto run_step = [&](int xs, const float4 (&o)[PQ][2]) {
-            const double* wp = wsh + (xs - x_begin + 4 * kq);
-            double wq[4];
+        for (int c = 0; c < R; ++c) o.c[c] = *reinterpret_cast<const f4u*>(cp[c] + x);
+        o.w[0] = *reinterpret_cast<const d2u*>(wrow + x);
+        o.w[1] = *reinterpret_cast<const d2u*>(wrow + x + 2);
+        if (mrow) {
+            o.m = 0;
 #pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4) wq[s4] = wp[s4];
-#pragma unroll
-            for (int q = 0; q < PQ; ++q) {
-                if (use[q]) {
-                    const float av[4] = {o[q][0].x, o[q][0].y, o[q][0].z, o[q][0].w};
-                    const float bv[4] = {o[q][1].x, o[q][1].y, o[q][1].z, o[q][1].w};
-#pragma unroll
-                    for (int s4 = 0; s4 < 4; ++s4)
-                        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                            ina[q] ? (double)av[s4] : 0.0, inb[q] ? (double)bv[s4] * wq[s4] : 0.0,
-                            acc[q], 0, 0, 0);
-                }
-            }
-        };
-        float4 oA[PQ][2], oB[PQ][2];
-        if (x0 < x_full) load_step(x0, oA);
-        for (; x0 + 32 <= x_full; x0 += 32) {
-            load_step(x0 + 16, oB);
-            run_step(x0, oA);
-            load_step(x0 + 32 < x_full ? x0 + 32 : x0 + 16, oA);   // past the end: unused
-            run_step(x0 + 16, oB);
+            for (int s = 0; s < 4; ++s) o.m |= mrow[x + s] ? 1u << s : 0u;
         }
-        if (x0 < x_full) {
-            run_step(x0, oA);
+        return o;
+    };
+    // the last pixels: loads from clamped columns, weight 0 past the end
+    auto load_tail = [&](int x0) {
+        Step o;
+        o.m = 0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int x = x0 + 4 * kq + s, xc = min(x, x_end - 1);
+#pragma unroll
+            for (int b = 0; b < NR; ++b) o.r[b][s] = rp[b][xc];
+#pragma unroll
+            for (int c = 0; c < R; ++c) o.c[c][s] = cp[c][xc];
+            o.w[s >> 1][s & 1] = x < x_end ? wrow[xc] : 0.0;
+            if (mrow) o.m |= mrow[xc] ? 1u << s : 0u;
+        }
+        return o;
+    };
+    auto products = [&](const Step& o) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            double w = o.w[s >> 1][s & 1];
+            if (mrow && !((o.m >> s) & 1)) w = 0.0;
+            double a[NR];
+#pragma unroll
+            for (int b = 0; b < NR; ++b) a[b] = (double)o.r[b][s];
+            int blk = 0;
+#pragma unroll
+            for (int cb = 0; cb < NBF; ++cb) {
+                const double bw = a[cb] * w;
+#pragma unroll
+                for (int rb = 0; rb <= cb; ++rb, ++blk)
+                    acc[blk] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rb], bw, acc[blk], 0, 0, 0);
+            }
+#pragma unroll
+            for (int c = 0; c < R; ++c) {
+                const double d = (double)o.c[c][s] * w;
+#pragma unroll
+                for (int b = 0; b < NR; ++b) rem[c][b] = fma(a[b], d, rem[c][b]);
+            }
+        }
+    };
+    // the operands of one step are requested (into a register set of their
+    // own) before the products of the step before it
+    const int n_full = max(0, (x_end - x_begin) / 16);
+    int x0 = x_begin;
+    if (n_full > 0) {
+        Step oa = load(x0);
+        int t = 0;
+        for (; t + 2 <= n_full; t += 2, x0 += 32) {
+            const Step ob = load(x0 + 16);
+            products(oa);
+            oa = load(t + 2 < n_full ? x0 + 32 : x0 + 16);   // past the end: unused
+            products(ob);
+        }
+        if (t < n_full) {
+            products(oa);
             x0 += 16;
         }
     }
-    // the remaining pixels (all of them when W is not a multiple of 4)
-    for (; x0 < x_end; x0 += 16) {
-        const int xb = x0 + 4 * kq;
-        const size_t pb = (size_t)row * W + xb;
-        double wq[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) wq[s] = (xb + s < x_end) ? wsh[xb + s - x_begin] : 0.0;
-        auto load4 = [&](int nrow, float* v) {
-            v[0] = v[1] = v[2] = v[3] = 0.f;
-            if (nrow < N) {
-                const float* src = T + (size_t)nrow * band_px + pb;
-#pragma unroll
-                for (int s = 0; s < 4; ++s) v[s] = (xb + s < x_end) ? src[s] : 0.f;
-            }
-        };
-#pragma unroll
-        for (int q = 0; q < PQ; ++q) {
-            {
-                const int rb = PAIRS[p_begin + q][0], cb = PAIRS[p_begin + q][1];
-                if (16 * rb < N && 16 * cb < N) {   // uniform
-                    float av[4], bv[4];
-                    load4(16 * rb + j, av);
-                    load4(16 * cb + j, bv);
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[s], (double)bv[s] * wq[s],
-                                                                       acc[q], 0, 0, 0);
-                }
-            }
-        }
-    }
+    if (x0 < x_end) products(load_tail(x0));
+
     // the float64 16x16x4 instruction stores row 4 e + kq of the 16 x 16
-    // block in register e of lane (kq, j) (groups of one row, unlike the
-    // float32 form's groups of four): lane (kq, j) holds
-    // G[n = 16 rb + 4 e + kq][n' = 16 cb + j]
-    double* dst = part + ((size_t)seg * n_a + ea) * 64 * 64;
+    // block in register e of lane (kq, j): lane (kq, j) holds
+    // G[16 rb + 4 e + kq][16 cb + j], block cb (cb + 1) / 2 + rb
+    double* dst = g.part + ((size_t)seg * g.n_a + ea) * E;
 #pragma unroll
-    for (int q = 0; q < PQ; ++q) {
-        const int rb = PAIRS[p_begin + q][0], cb = PAIRS[p_begin + q][1];
+    for (int b = 0; b < NBLK; ++b)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dst[(16 * rb + 4 * e + kq) * 64 + 16 * cb + j] = acc[q][e];
-    }
+        for (int e = 0; e < 4; ++e) dst[b * 256 + (4 * e + kq) * 16 + j] = acc[b][e];
+#pragma unroll
+    for (int c = 0; c < R; ++c)
+#pragma unroll
+        for (int b = 0; b < NR; ++b) {
+            double v = rem[c][b];
+            v += __shfl_xor(v, 16);
+            v += __shfl_xor(v, 32);
+            if (kq == 0) dst[NBLK * 256 + (c * NR + b) * 16 + j] = v;
+        }
 }
 
-// S[(a, b)][.][.] += sum over segments (fixed order) of yh(segment row)^b G_a
-__global__ void gram_reduce(const double* __restrict__ part, int n_seg, int cpr, int n_a,
-                            int y_begin, double sy, double oy, double* __restrict__ S) {
-    // thread (a, e): entry e of the partial sums of x power a, read once and
-    // added into S[mu(a, b)] for every y power b <= 2 d - a (n_a = 2 d + 1);
-    // yh^b by repeated products, the same sums as one power at a time
+// Blocks of 16 planes and planes over: a block column padded to 16 costs
+// (nbf + 1) matrix products of 66 cycles per 4 pixels, a plane over 2 + nbf + 1
+// vector instructions of 4.2 (times the next instance's R), so up to 8 planes
+// over two or more blocks and up to 4 over one are cheaper than the block.
+struct GramShape {
+    int nbf, r;
+    int blocks() const { return nbf * (nbf + 1) / 2; }
+    int entries() const { return blocks() * 256 + r * (nbf + 1) * 16; }
+};
+
+static GramShape gram_shape(int planes) {
+    const int full = planes / 16, over = planes % 16;
+    const int most = full >= 2 ? 8 : full == 1 ? 4 : 0;
+    if (over == 0) return {full, 0};
+    if (over > most) return {full + 1, 0};
+    return {full, over <= 2 ? 2 : over <= 4 ? 4 : 8};
+}
+
+// Entry of the pair (p, p') of planes
+__device__ __forceinline__ int gram_entry(int nbf, int r, int p, int p2) {
+    const int lo = min(p, p2), hi = max(p, p2), cb = hi >> 4, rb = lo >> 4;
+    if (cb < nbf || r == 0) return (cb * (cb + 1) / 2 + rb) * 256 + (lo & 15) * 16 + (hi & 15);
+    return nbf * (nbf + 1) / 2 * 256 + ((hi - 16 * nbf) * (nbf + 1) + rb) * 16 + (lo & 15);
+}
+
+static int launch_gram(const GramArgs& g, GramShape sh, hipStream_t s) {
+    const dim3 grid((unsigned)((g.segs + 7) / 8 * 8 * g.n_a)), block(64);
+#define GRAM(NBF, R)                                                                     \
+    if (sh.nbf == NBF && sh.r == R) {                                                    \
+        hipLaunchKernelGGL((gram_kernel<NBF, R>), grid, block, 0, s, g);                 \
+        return hip_status(hipGetLastError(), "gram_kernel");                             \
+    }
+    GRAM(1, 0) GRAM(1, 2) GRAM(1, 4) GRAM(2, 0) GRAM(2, 2) GRAM(2, 4) GRAM(2, 8)
+    GRAM(3, 0) GRAM(3, 2) GRAM(3, 4) GRAM(3, 8) GRAM(4, 0)
+#undef GRAM
+    return fail(SVCONV_EUNSUPPORTED, "normal matrix: more than 64 planes");
+}
+
+// part2[chunk][(a, b)][.] = sum over the chunk's segments (in order) of
+// yh(segment row)^b G_a.  Thread (a, e) reads entry e once for every y power
+// b <= 2 d - a.  Bound: one read of the partial sums; NM_CHUNKS ranges of
+// segments keep the chip busy (in one range, 490 us of the 2048 x 2048 case).
+__global__ __launch_bounds__(256) void gram_reduce(const double* __restrict__ part, int E, int n_seg, int cpr,
+                                                   int n_a, int y_begin, double sy, double oy,
+                                                   double* __restrict__ part2) {
     constexpr int NB_MAX = 2 * kMaxSpatialDegree + 1;
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int ea = blockIdx.y;
-    if (e >= 4096) return;
-    if (((e >> 6) >> 4) > ((e & 63) >> 4)) return;   // lower blocks are not formed (S symmetric)
+    const int ea = blockIdx.y, n_mu = n_a * (n_a + 1) / 2;
+    if (e >= E) return;
+    const int per = (n_seg + NM_CHUNKS - 1) / NM_CHUNKS;
+    const int c_begin = blockIdx.z * per, c_end = min(n_seg, c_begin + per);
     const int n_eb = n_a - ea;                        // uniform
     double acc[NB_MAX];
 #pragma unroll
     for (int eb = 0; eb < NB_MAX; ++eb) acc[eb] = 0.0;
-#pragma unroll 4
-    for (int c = 0; c < n_seg; ++c) {
-        const double v = part[((size_t)c * n_a + ea) * 4096 + e];
+#pragma unroll 8
+    for (int c = c_begin; c < c_end; ++c) {
+        const double v = part[((size_t)c * n_a + ea) * E + e];
         const double yh = sy * (y_begin + c / cpr) + oy;
         double pw = 1.0;
 #pragma unroll
@@ -267,70 +337,114 @@ __global__ void gram_reduce(const double* __restrict__ part, int n_seg, int cpr,
             pw *= yh;
         }
     }
+    double* dst = part2 + (size_t)blockIdx.z * n_mu * E + e;
 #pragma unroll
     for (int eb = 0; eb < NB_MAX; ++eb) {
         if (eb < n_eb) {
             const int tt = ea + eb;
-            S[(size_t)(tt * (tt + 1) / 2 + eb) * 4096 + e] += acc[eb];
+            dst[(size_t)(tt * (tt + 1) / 2 + eb) * E] = acc[eb];
         }
     }
 }
 
-__global__ void zero_kernel(double* __restrict__ v, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (size_t)gridDim.x * blockDim.x)
-        v[i] = 0.0;
+// S (+)= the chunks' sums, in order
+__global__ __launch_bounds__(256) void gram_total(const double* __restrict__ part2, int n, int first,
+                                                  double* __restrict__ S) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    double s = first ? 0.0 : S[i];
+#pragma unroll 8
+    for (int c = 0; c < NM_CHUNKS; ++c) s += part2[(size_t)c * n + i];
+    S[i] = s;
 }
 
-// JtJ[(n,m)][(n',m')] = S[mu(i_m + i_m', j_m + j_m')][n][n']
-__global__ void assemble_jtj(const double* __restrict__ S, int N, int M, double* __restrict__ JtJ) {
+// xw[a][x] = xh^a (0 outside [x_lo, x_hi)), the row of ones, and S = 0
+__global__ void gram_tables_kernel(int W, int x_lo, int x_hi, double sx, double ox, int n_a, double* __restrict__ xw,
+                                   float* __restrict__ ones, double* __restrict__ S, int n_s) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n_s) S[i] = 0.0;
+    if (i < W + 16) ones[i] = 1.f;
+    if (i >= n_a * W) return;
+    const int a = i / W, x = i - a * W;
+    const double xh = sx * x + ox;
+    double p = 1.0;
+    for (int t = 0; t < a; ++t) p *= xh;
+    xw[i] = (x >= x_lo && x < x_hi) ? p : 0.0;
+}
+
+// JtJ[(n,m)][(n',m')] = S[mu(i_m + i_m', j_m + j_m')][n][n'] and, with q >= 0,
+// rhs[(n,m)] = S[mu(i_m, j_m)][n][q] = sum_{p in mask} P_m T_n I (plane q holds I)
+__global__ void assemble_jtj(const double* __restrict__ S, int E, int nbf, int r, int N, int M, int q,
+                             double* __restrict__ JtJ, double* __restrict__ rhs) {
     const int NM = N * M;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= NM * NM) return;
-    const int r = idx / NM, c = idx % NM;
-    const int n = r / M, m = r % M, n2 = c / M, m2 = c % M;
-    auto expo = [](int q, int& i, int& jj) {
+    const int row = idx / NM, c = idx - row * NM;
+    const int n = row / M, m = row - n * M, n2 = c / M, m2 = c - n2 * M;
+    auto expo = [](int k, int& i, int& jj) {
         int t = 0;
-        while ((t + 1) * (t + 2) / 2 <= q) ++t;
-        jj = q - t * (t + 1) / 2;
+        while ((t + 1) * (t + 2) / 2 <= k) ++t;
+        jj = k - t * (t + 1) / 2;
         i = t - jj;
     };
     int i1, j1, i2, j2;
     expo(m, i1, j1);
     expo(m2, i2, j2);
-    const int a = i1 + i2, b = j1 + j2, t = a + b;
-    const int mu = t * (t + 1) / 2 + b;
-    // only blocks with row block <= column block are formed (S is symmetric)
-    const int lo = ((n >> 4) <= (n2 >> 4)) ? n : n2, hi = ((n >> 4) <= (n2 >> 4)) ? n2 : n;
-    JtJ[idx] = S[(size_t)mu * 4096 + lo * 64 + hi];
+    const int t = i1 + i2 + j1 + j2, mu = t * (t + 1) / 2 + j1 + j2;
+    JtJ[idx] = S[(size_t)mu * E + gram_entry(nbf, r, n, n2)];
+    if (q >= 0 && c == 0) rhs[row] = S[(size_t)m * E + gram_entry(nbf, r, n, q)];   // mu(i_m, j_m) = m
 }
 
-__global__ void fill_ones_kernel(float* __restrict__ v, int n) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) v[i] = 1.f;
-}
-
-__global__ void copy_plane_kernel(const float* __restrict__ src, float* __restrict__ dst, int n) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) dst[i] = src[i];
-}
-
-// rhs[(n,m)] = S[mu(i_m, j_m)][n][q] = sum_{p in mask} P_m T_n I, where plane q
-// of the band held I (column q of the Gram sums, q >= n, so the entry is formed)
-__global__ void assemble_rhs(const double* __restrict__ S, int N, int M, int q, double* __restrict__ rhs) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= N * M) return;
-    const int n = idx / M, m = idx % M;
-    int t = 0;
-    while ((t + 1) * (t + 2) / 2 <= m) ++t;
-    const int j = m - t * (t + 1) / 2;
-    rhs[idx] = S[(size_t)(t * (t + 1) / 2 + j) * 4096 + n * 64 + q];
+// The basis responses T_n + s beta_n of rows [y0, y0 + rows) into the plan's band
+static int band_responses(svconv_plan* p, const float* R, int y0, int rows) {
+    double sx = 0, ox = 0, sy = 0, oy = 0;
+    if (p->Wf > 1) { sx = 2.0 / (p->Wf - 1); ox = sx * p->x0 - 1.0; }
+    if (p->Hf > 1) { sy = 2.0 / (p->Hf - 1); oy = sy * p->y0 - 1.0; }
+    if (sep_form(p)) {
+        // through the separable factors
+        SepArgs sa{};
+        sa.X = R;
+        sa.H = p->H;
+        sa.W = p->W;
+        sa.h = p->h;
+        sa.ped = p->pedestal;
+        sa.G = (int)p->sigmas.size();
+        sa.fam = p->dSepFam;
+        sa.f1d = p->dSep1d;
+        sa.beta = p->dBeta;
+        sa.coef = p->dF32;   // not read in this mode
+        sa.M = p->M;
+        sa.d_s = p->d_s;
+        sa.sx = sx; sa.ox = ox; sa.sy = sy; sa.oy = oy;
+        sa.y_begin = y0;
+        sa.n_rows = rows;
+        sa.tout = p->dTband;
+        return launch_contract_sep(sa, p->stream);
+    }
+    ContractArgs c{};
+    c.X = R;
+    c.H = p->H;
+    c.W = p->W;
+    c.h = p->h;
+    c.NF = p->N;
+    c.M = p->M;
+    c.d_s = p->d_s;
+    c.beta = p->dBeta;
+    c.ped = p->pedestal;
+    c.sx = sx; c.ox = ox; c.sy = sy; c.oy = oy;
+    c.tout = p->dTband;
+    // basis-form kernel with out == nullptr: coefficients are neither read nor used
+    c.coef = p->dF32;
+    c.y_begin = y0;
+    c.n_rows = rows;
+    return launch_contract_f32(c, p->dFragF32, (p->N + 15) / 16, p->stream);
 }
 
 // With a background polynomial the fit has one more "basis" whose response
 // is the constant 1 (bg = sum_m b_m P_m * 1), so the same Gram sums give the
-// background rows and columns of the normal matrix: plane N of the band is
-// filled with ones.  With I and rhs given, one more plane holds I, and the
-// Gram sums of the basis planes with it are the right-hand side
-// rhs[(n,m)] = sum_p P_m T_n I of the normal equations.
+// background rows and columns of the normal matrix.  With I and rhs given, one
+// more plane is I, and the Gram sums of the basis planes with it are the
+// right-hand side rhs[(n,m)] = sum_p P_m T_n I of the normal equations.
 int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const unsigned char* mask,
                          double* JtJ, double* rhs) {
     const int NF = p->N + p->bg;
@@ -339,17 +453,36 @@ int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const u
     if (planes > 64)
         return fail(SVCONV_EUNSUPPORTED,
                     "normal equations need N (+1 with a background, +1 with the right-hand side) <= 64");
+    const GramShape sh = gram_shape(planes);
+    const int E = sh.entries();
     const int n_mu = (2 * p->d_s + 1) * (2 * p->d_s + 2) / 2;
     const int n_a = 2 * p->d_s + 1;                       // powers of xh
-    const int cpr = (p->W + NM_PIX_CHUNK - 1) / NM_PIX_CHUNK;   // segments per row
-    const size_t row_bytes = (size_t)planes * p->W * sizeof(float);
-    int band = (int)(NM_BAND_BYTES / row_bytes);
+    // The responses of a delta basis at interior pixels are pixels of R: no
+    // response planes are written for it (with a mask, stamps may reach the
+    // border, where R is 0 outside the image, so the planes are formed)
+    const bool shifts = p->dfb && !mask;
+    // rows and columns that can have weight; columns start on 4 where the
+    // weights cover the columns below (a shifted R has none left of x = h)
+    const int y_lo = mask ? 0 : p->h, y_hi = mask ? p->H : p->H - p->h;
+    const int x_in = mask ? 0 : p->h, x_hi = mask ? p->W : p->W - p->h;
+    const int x_lo = shifts ? x_in : x_in & ~3;
+    const int rows_all = y_hi > y_lo && x_hi > x_in ? y_hi - y_lo : 0;
+    // segments: whole rows up to NM_PIX_CHUNK pixels, shorter where there would
+    // be less than four waves per SIMD
+    int seg_len = NM_PIX_CHUNK, cpr = 1;
+    for (;; seg_len /= 2) {
+        cpr = x_hi > x_lo ? (x_hi - x_lo + seg_len - 1) / seg_len : 1;
+        if ((long)cpr * rows_all * n_a >= 4096 || seg_len <= 128) break;
+    }
+    const size_t row_bytes = (size_t)p->N * p->W * sizeof(float), part_row = (size_t)cpr * n_a * E;
+    size_t band = shifts ? (size_t)rows_all : NM_BAND_BYTES / row_bytes;
+    if (band > NM_PART_BYTES / (part_row * sizeof(double))) band = NM_PART_BYTES / (part_row * sizeof(double));
     if (band < 8) band = 8;
-    if (band > p->H) band = p->H;
-    const size_t part_elems = (size_t)band * cpr * n_a * 4096;
-    const size_t s_elems = (size_t)n_mu * 4096;
-    const size_t tband_bytes = (size_t)band * row_bytes;
-    const size_t nmpart_bytes = (part_elems + s_elems) * sizeof(double);
+    if (band > (size_t)rows_all) band = rows_all;
+    const size_t part_elems = band * part_row, part2_elems = (size_t)NM_CHUNKS * n_mu * E;
+    const size_t s_elems = (size_t)n_mu * E, xw_elems = (size_t)n_a * p->W, ones_elems = ((size_t)p->W + 16 + 1) / 2;
+    const size_t tband_bytes = shifts ? 0 : band * row_bytes;
+    const size_t nmpart_bytes = (part_elems + part2_elems + s_elems + xw_elems + ones_elems) * sizeof(double);
     // scratch of the normal matrix: allocated on its first call (grown when
     // a later call needs more), kept by the plan
     if (p->tband_bytes < tband_bytes || p->nmpart_bytes < nmpart_bytes) {
@@ -358,7 +491,7 @@ int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const u
         p->dTband = nullptr;
         p->dNMpart = nullptr;
         p->tband_bytes = p->nmpart_bytes = 0;
-        if (hipMalloc((void**)&p->dTband, tband_bytes) != hipSuccess ||
+        if ((tband_bytes && hipMalloc((void**)&p->dTband, tband_bytes) != hipSuccess) ||
             hipMalloc((void**)&p->dNMpart, nmpart_bytes) != hipSuccess) {
             (void)hipGetLastError();
             if (p->dTband) (void)hipFree(p->dTband);
@@ -369,92 +502,62 @@ int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const u
         p->tband_bytes = tband_bytes;
         p->nmpart_bytes = nmpart_bytes;
     }
-    double* S = p->dNMpart + part_elems;
-    hipLaunchKernelGGL(zero_kernel, dim3(256), dim3(256), 0, p->stream, S, s_elems);
-    int st = hip_status(hipGetLastError(), "zero_kernel");
-    if (st) return st;
-
-    ContractArgs c{};
-    c.X = R;
-    c.H = p->H;
-    c.W = p->W;
-    c.h = p->h;
-    c.NF = p->N;
-    c.M = p->M;
-    c.d_s = p->d_s;
-    c.coef = nullptr;
-    c.beta = p->dBeta;
-    c.ped = p->pedestal;
-    c.I = nullptr;
-    c.out = nullptr;
+    double* part2 = p->dNMpart + part_elems;
+    double* S = part2 + part2_elems;
+    double* xw = S + s_elems;
+    float* ones = reinterpret_cast<float*>(xw + xw_elems);
     double sx = 0, ox = 0, sy = 0, oy = 0;
     if (p->Wf > 1) { sx = 2.0 / (p->Wf - 1); ox = sx * p->x0 - 1.0; }
     if (p->Hf > 1) { sy = 2.0 / (p->Hf - 1); oy = sy * p->y0 - 1.0; }
-    c.sx = sx; c.ox = ox; c.sy = sy; c.oy = oy;
-    c.tout = p->dTband;
-    // basis-form kernel with out == nullptr: coefficients are neither read nor used
-    c.coef = reinterpret_cast<const float*>(p->dF32);
-    const int nb = (p->N + 15) / 16;
-    for (int y0 = 0; y0 < p->H; y0 += band) {
-        const int rows = (y0 + band <= p->H) ? band : p->H - y0;
-        c.y_begin = y0;
-        c.n_rows = rows;
-        if (sep_form(p)) {
-            // basis responses through the separable factors
-            SepArgs sa{};
-            sa.X = R;
-            sa.I = nullptr;
-            sa.out = nullptr;
-            sa.H = p->H;
-            sa.W = p->W;
-            sa.h = p->h;
-            sa.ped = p->pedestal;
-            sa.G = (int)p->sigmas.size();
-            sa.fam = p->dSepFam;
-            sa.f1d = p->dSep1d;
-            sa.beta = p->dBeta;
-            sa.coef = reinterpret_cast<const float*>(p->dF32);   // not read in this mode
-            sa.M = p->M;
-            sa.d_s = p->d_s;
-            sa.sx = sx; sa.ox = ox; sa.sy = sy; sa.oy = oy;
-            sa.y_begin = y0;
-            sa.n_rows = rows;
-            sa.tout = p->dTband;
-            st = launch_contract_sep(sa, p->stream);
-        } else {
-            st = launch_contract_f32(c, p->dFragF32, nb, p->stream);
-        }
-        if (st) return st;
-        const int band_px = rows * p->W;
-        if (p->bg) {
-            hipLaunchKernelGGL(fill_ones_kernel, dim3(1024), dim3(256), 0, p->stream,
-                               p->dTband + (size_t)p->N * band_px, band_px);
-            st = hip_status(hipGetLastError(), "fill_ones_kernel");
+    {
+        size_t n = s_elems > xw_elems ? s_elems : xw_elems;
+        if (n < (size_t)p->W + 16) n = (size_t)p->W + 16;
+        hipLaunchKernelGGL(gram_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, p->stream, p->W, x_in,
+                           x_hi, sx, ox, n_a, xw, ones, S, (int)s_elems);
+    }
+    int st = hip_status(hipGetLastError(), "gram_tables_kernel");
+    if (st) return st;
+
+    GramArgs g{};
+    g.q.dfb_k = shifts ? p->k : 0;
+    g.q.T = shifts ? R : p->dTband;
+    g.q.N = p->N;
+    g.q.P = planes;
+    g.q.ones = ones;
+    g.q.I = want_rhs ? I : nullptr;
+    g.W = p->W;
+    g.cpr = cpr;
+    g.seg_len = seg_len;
+    g.x_lo = x_lo;
+    g.x_hi = x_hi;
+    g.n_a = n_a;
+    g.mask = mask;
+    g.xw = xw;
+    g.part = p->dNMpart;
+    for (int y0 = y_lo; y0 < y_lo + rows_all; y0 += (int)band) {
+        const int rows = min((int)band, y_lo + rows_all - y0);
+        if (!shifts) {
+            st = band_responses(p, R, y0, rows);
             if (st) return st;
         }
-        if (want_rhs) {
-            hipLaunchKernelGGL(copy_plane_kernel, dim3(1024), dim3(256), 0, p->stream,
-                               I + (size_t)y0 * p->W, p->dTband + (size_t)NF * band_px, band_px);
-            st = hip_status(hipGetLastError(), "copy_plane_kernel");
-            if (st) return st;
-        }
-        const int segs = rows * cpr;
-        hipLaunchKernelGGL(gram_kernel, dim3(n_a, segs), dim3(64 * GRAM_WAVES), 0, p->stream, p->dTband, planes,
-                           band_px, y0, p->W, p->H, p->h, cpr, mask, sx, ox, n_a, p->dNMpart);
-        st = hip_status(hipGetLastError(), "gram_kernel");
+        g.q.stride = (size_t)rows * p->W;
+        g.y_begin = y0;
+        g.segs = rows * cpr;
+        st = launch_gram(g, sh, p->stream);
         if (st) return st;
-        hipLaunchKernelGGL(gram_reduce, dim3(4096 / 256, n_a), dim3(256), 0, p->stream,
-                           p->dNMpart, segs, cpr, n_a, y0, sy, oy, S);
+        hipLaunchKernelGGL(gram_reduce, dim3((E + 255) / 256, n_a, NM_CHUNKS), dim3(256), 0, p->stream, p->dNMpart, E,
+                           g.segs, cpr, n_a, y0, sy, oy, part2);
         st = hip_status(hipGetLastError(), "gram_reduce");
+        if (st) return st;
+        hipLaunchKernelGGL(gram_total, dim3((unsigned)((s_elems + 255) / 256)), dim3(256), 0, p->stream, part2,
+                           (int)s_elems, y0 == y_lo ? 1 : 0, S);
+        st = hip_status(hipGetLastError(), "gram_total");
         if (st) return st;
     }
     const int NM = NF * p->M;
-    hipLaunchKernelGGL(assemble_jtj, dim3((NM * NM + 255) / 256), dim3(256), 0, p->stream, S, NF,
-                       p->M, JtJ);
-    st = hip_status(hipGetLastError(), "assemble_jtj");
-    if (st || !want_rhs) return st;
-    hipLaunchKernelGGL(assemble_rhs, dim3((NM + 255) / 256), dim3(256), 0, p->stream, S, NF, p->M, NF, rhs);
-    return hip_status(hipGetLastError(), "assemble_rhs");
+    hipLaunchKernelGGL(assemble_jtj, dim3((NM * NM + 255) / 256), dim3(256), 0, p->stream, S, E, sh.nbf, sh.r, NF,
+                       p->M, want_rhs ? NF : -1, JtJ, rhs);
+    return hip_status(hipGetLastError(), "assemble_jtj");
 }
 
 // -------------------------------------------------------- Cholesky ----
