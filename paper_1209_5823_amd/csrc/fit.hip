@@ -562,186 +562,201 @@ int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const u
 
 // -------------------------------------------------------- Cholesky ----
 
-// Right-looking in-place factorisation by one workgroup; A stays in global
-// memory (at most 1024 x 1024 doubles, resident in L2).  status[0] becomes
-// the first non-positive pivot index + 1 (0 = SPD).
-__global__ __launch_bounds__(1024) void cholesky_kernel(double* __restrict__ A, int n,
-                                                        int* __restrict__ status) {
-    __shared__ int bad;
-    __shared__ double piv;
-    const int tid = threadIdx.x;
-    if (tid == 0) bad = 0;
-    __syncthreads();
-    for (int jc = 0; jc < n; ++jc) {
-        if (tid == 0) {
-            const double d = A[(size_t)jc * n + jc];
-            if (!(d > 0.0) || !isfinite(d)) {
-                bad = jc + 1;
-                piv = 1.0;
-            } else {
-                piv = sqrt(d);
-                A[(size_t)jc * n + jc] = piv;
-            }
-        }
-        __syncthreads();
-        if (bad) break;
-        const double inv = 1.0 / piv;
-        for (int i = jc + 1 + tid; i < n; i += 1024) A[(size_t)i * n + jc] *= inv;
-        __syncthreads();
-        // trailing update of the lower triangle: A[i][c] -= L[i][jc] L[c][jc], jc < c <= i
-        const int m = n - jc - 1;
-        const long cnt = (long)m * (m + 1) / 2;
-        for (long q = tid; q < cnt; q += 1024) {
-            // row-major enumeration of the lower triangle of an m x m block
-            long i = (long)((sqrt(8.0 * q + 1.0) - 1.0) * 0.5);
-            while (i * (i + 1) / 2 > q) --i;
-            while ((i + 1) * (i + 2) / 2 <= q) ++i;
-            const long c = q - i * (i + 1) / 2;
-            const int ii = jc + 1 + (int)i, cc = jc + 1 + (int)c;
-            A[(size_t)ii * n + cc] -= A[(size_t)ii * n + jc] * A[(size_t)cc * n + jc];
-        }
-        __syncthreads();
-    }
-    __syncthreads();
-    if (!bad) {
-        for (long q = tid; q < (long)n * n; q += 1024) {
-            const int i = (int)(q / n), c = (int)(q % n);
-            if (c > i) A[q] = 0.0;
-        }
-    }
-    if (tid == 0) status[0] = bad;
-}
-
-// Blocked right-looking factorisation for larger matrices: for each block
-// column k0 of width CH_NB, one workgroup factors the diagonal block in LDS
-// and solves the panel below it (L21 = A21 L11^-T), then one workgroup per
-// 32 x 32 tile of the trailing lower triangle applies A22 -= L21 L21^T.
+// Blocked right-looking factorisation, one launch per block column k0 of
+// CH_NB = 32: every workgroup factors the 32 x 32 diagonal block for itself,
+// solves the two 32-row panels its tile of the trailing lower triangle needs
+// (L21 = A21 L11^-T) and applies A22 -= L21 L21^T to that tile.  Factoring the
+// block in every workgroup costs nothing (they run side by side) and saves the
+// launch between panel and update; it is done by one wave with a row per lane
+// in registers, entries of other rows broadcast by v_readlane.
+// Bound: the serial chain of the 32 pivots (a square root, a reciprocal and a
+// rank-1 update each).  n = 294: 430 us (panel kernel with 4 barriers per
+// column 34 us a block, then an update kernel) -> 200 us with the host's launches
+// and status copy; n = 735: 1420 -> 420 us.
+//
+// Workgroups still read the lower triangle of the block column while others
+// finish it, so the results go where nobody reads: L21^T and the strict lower
+// part of L11, transposed, into the upper triangle, the diagonal into `diag`.
+// chol_finish_kernel moves them to their places and clears the upper triangle.
 constexpr int CH_NB = 32;
 
-__global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A, int n, int k0,
-                                                         int* __restrict__ status) {
-    __shared__ double L[CH_NB][CH_NB + 1];
-    __shared__ int bad;
-    const int tid = threadIdx.x;
-    const int nb = min(CH_NB, n - k0);
-    for (int q = tid; q < nb * nb; q += 256) {
-        const int r = q / nb, c = q - r * nb;
-        L[r][c] = A[(size_t)(k0 + r) * n + k0 + c];
+// v of lane `l` (uniform), through scalar registers
+__device__ __forceinline__ double lane_value(double v, int l) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+    return __hiloint2double(hi, lo);
+}
+
+// root = sqrt(d) and inv = 1 / sqrt(d) for finite d > 0, by Goldschmidt's
+// iteration from the hardware's estimate (both within an ulp or two); the
+// library's square root and division after one another are 40 dependent
+// instructions, the larger part of a pivot's latency.
+__device__ __forceinline__ void sqrt_both(double d, double& root, double& inv) {
+    const double y = __builtin_amdgcn_rsq(d);
+    double g = d * y, h = 0.5 * y;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const double r = fma(-h, g, 0.5);
+        g = fma(g, r, g);
+        h = fma(h, r, h);
     }
-    if (tid == 0) bad = status[0];
+    root = fma(fma(-g, g, d), h, g);
+    inv = h + h;
+}
+
+__global__ __launch_bounds__(256) void chol_step_kernel(double* __restrict__ A, int n, int k0,
+                                                        double* __restrict__ diag, int* __restrict__ status) {
+    __shared__ double L11[CH_NB][CH_NB + 1];                    // A11, then L11
+    __shared__ __attribute__((aligned(16))) double Lt[CH_NB][CH_NB + 2];   // its transpose
+    __shared__ double inv[CH_NB], P[2][CH_NB][CH_NB + 1];       // 1 / pivots; the two panels
+    const int tid = threadIdx.x;
+    const int nb = min(CH_NB, n - k0), k1 = k0 + nb;
+    int ti = (int)((sqrt(8.0 * blockIdx.x + 1.0) - 1.0) * 0.5);
+    while (ti * (ti + 1) / 2 > (int)blockIdx.x) --ti;
+    while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.x) ++ti;
+    const int tj = (int)blockIdx.x - ti * (ti + 1) / 2;
+    const int r0 = k1 + 32 * ti, c0 = k1 + 32 * tj;
+
+    // all of the workgroup's operands are requested together
+    const int cc = tid & 31, rq = tid >> 5;
+    double d11[4], pi[4], pj[4], a22[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = rq + 8 * i;
+        d11[i] = A[(size_t)min(k0 + r, n - 1) * n + min(k0 + cc, n - 1)];
+        pi[i] = A[(size_t)min(r0 + r, n - 1) * n + min(k0 + cc, n - 1)];
+        pj[i] = A[(size_t)min(c0 + r, n - 1) * n + min(k0 + cc, n - 1)];
+        a22[i] = A[(size_t)min(r0 + r, n - 1) * n + min(c0 + cc, n - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = rq + 8 * i;
+        // a short block is completed with the identity
+        L11[r][cc] = (r < nb && cc <= r) ? d11[i] : (r == cc ? 1.0 : 0.0);
+        P[0][r][cc] = (r0 + r < n && cc < nb) ? pi[i] : 0.0;
+        P[1][r][cc] = (c0 + r < n && cc < nb) ? pj[i] : 0.0;
+    }
     __syncthreads();
-    for (int j = 0; j < nb; ++j) {
-        if (tid == 0) {
-            double d = L[j][j];
-            if (!(d > 0.0) || !isfinite(d)) {
+    if (tid < 64) {
+        const int r = tid & 31;
+        double row[CH_NB];
+#pragma unroll
+        for (int c = 0; c < CH_NB; ++c) row[c] = L11[r][c];
+        int bad = 0;
+        double my_inv = 1.0;
+#pragma unroll
+        for (int j = 0; j < CH_NB; ++j) {
+            double d = lane_value(row[j], j);
+            if (!(d > 0.0) || !isfinite(d)) {   // uniform
                 if (!bad) bad = k0 + j + 1;
                 d = 1.0;
             }
-            L[j][j] = sqrt(d);
-        }
-        __syncthreads();
-        const double inv = 1.0 / L[j][j];
-        for (int i = j + 1 + tid; i < nb; i += 256) L[i][j] *= inv;
-        __syncthreads();
-        const int m = nb - j - 1;
-        for (int q = tid; q < m * m; q += 256) {
-            const int i = j + 1 + q / m, c = j + 1 + q % m;
-            if (c <= i) L[i][c] -= L[i][j] * L[c][j];
-        }
-        __syncthreads();
-    }
-    for (int q = tid; q < nb * nb; q += 256) {
-        const int r = q / nb, c = q - r * nb;
-        A[(size_t)(k0 + r) * n + k0 + c] = (c <= r) ? L[r][c] : 0.0;
-    }
-    // panel rows below: x L11^T = a, forward substitution over the block's
-    // columns on the row held in registers; the empty asm with a memory clobber
-    // keeps the compiler from hoisting all of L11 into registers across rows
-    for (int i = k0 + nb + tid; i < n; i += 256) {
-        asm volatile("" ::: "memory");
-        double x[CH_NB];
-        double* row = A + (size_t)i * n + k0;
+            double piv, q;
+            sqrt_both(d, piv, q);
+            if (r == j) my_inv = q;
+            row[j] = r == j ? piv : row[j] * q;
+            // entries above the diagonal become meaningless and are never read
 #pragma unroll
-        for (int c = 0; c < CH_NB; ++c) {
-            if (c < nb) {
-                double s = row[c];
+            for (int c = j + 1; c < CH_NB; ++c) row[c] = fma(-row[j], lane_value(row[j], c), row[c]);
+        }
+        if (tid < 32) {
+            inv[r] = my_inv;
 #pragma unroll
-                for (int t = 0; t < c; ++t) s -= x[t] * L[c][t];
-                x[c] = s / L[c][c];
-                row[c] = x[c];
+            for (int c = 0; c < CH_NB; ++c) {
+                const double v = c <= r ? row[c] : 0.0;
+                L11[r][c] = v;
+                Lt[c][r] = v;
+            }
+            if (tid == 0 && blockIdx.x == 0) {
+                // the first block column starts the status word
+                if (k0 == 0) status[0] = bad;
+                else if (bad && status[0] == 0) status[0] = bad;
             }
         }
     }
-    if (tid == 0) status[0] = bad;
-}
-
-// A22 -= L21 L21^T on the lower triangle; block b is tile (ti, tj), tj <= ti
-__global__ __launch_bounds__(256) void chol_update_kernel(double* __restrict__ A, int n, int k0,
-                                                          int nb) {
-    __shared__ double Li[CH_NB][CH_NB + 1], Lj[CH_NB][CH_NB + 1];
-    const int b = blockIdx.x;
-    int ti = (int)((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
-    while (ti * (ti + 1) / 2 > b) --ti;
-    while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
-    const int tj = b - ti * (ti + 1) / 2;
-    const int k1 = k0 + nb;
-    const int r0 = k1 + 32 * ti, c0 = k1 + 32 * tj;
-    const int tid = threadIdx.x;
-    for (int q = tid; q < 32 * nb; q += 256) {
-        const int r = q / nb, c = q - r * nb;
-        Li[r][c] = (r0 + r < n) ? A[(size_t)(r0 + r) * n + k0 + c] : 0.0;
-        Lj[r][c] = (c0 + r < n) ? A[(size_t)(c0 + r) * n + k0 + c] : 0.0;
-    }
     __syncthreads();
-    const int cc = tid & 31, rb = tid >> 5;     // column, first of 4 rows (stride 8)
-    for (int rr = rb; rr < 32; rr += 8) {
-        const int gi = r0 + rr, gj = c0 + cc;
-        if (gi < n && gj < n && gj <= gi) {
-            double s = 0.0;
-            for (int t = 0; t < nb; ++t) s = fma(Li[rr][t], Lj[cc][t], s);
-            A[(size_t)gi * n + gj] -= s;
+    if (blockIdx.x == 0) {
+        if (tid < nb) diag[k0 + tid] = L11[tid][tid];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int c = rq + 8 * i;   // L11[cc][c], c < cc, to row c of the upper triangle
+            if (cc < nb && c < cc) A[(size_t)(k0 + c) * n + k0 + cc] = L11[cc][c];
         }
     }
-}
-
-__global__ void chol_zero_upper(double* __restrict__ A, int n) {
-    const size_t total = (size_t)n * n;
-    for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < total;
-         q += (size_t)gridDim.x * blockDim.x) {
-        const int i = (int)(q / n), c = (int)(q % n);
-        if (c > i) A[q] = 0.0;
+    if (k1 >= n) return;   // uniform
+    // the panels: x L11^T = a, a row per lane, one wave per panel
+    if (tid < 128 && (tid & 63) < 32) {
+        const int w = tid >> 6, r = tid & 31;
+        if (w == 0 || ti != tj) {
+            double x[CH_NB];
+#pragma unroll
+            for (int c = 0; c < CH_NB; ++c) x[c] = P[w][r][c];
+#pragma unroll
+            for (int c = 0; c < CH_NB; ++c) {
+                x[c] *= inv[c];
+#pragma unroll
+                for (int t = c + 1; t < CH_NB; ++t) x[t] = fma(-x[c], Lt[c][t], x[t]);
+            }
+#pragma unroll
+            for (int c = 0; c < CH_NB; ++c) P[w][r][c] = x[c];
+            // the tiles of the first column write the panel, transposed
+            if (w == 0 && tj == 0 && r0 + r < n) {
+#pragma unroll
+                for (int c = 0; c < CH_NB; ++c)
+                    if (c < nb) A[(size_t)(k0 + c) * n + r0 + r] = x[c];
+            }
+        }
+    }
+    __syncthreads();
+    const double (*Pj)[CH_NB + 1] = ti == tj ? P[0] : P[1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = rq + 8 * i, gi = r0 + r, gj = c0 + cc;
+        double s = 0.0;
+#pragma unroll
+        for (int t = 0; t < CH_NB; ++t) s = fma(P[0][r][t], Pj[cc][t], s);
+        if (gi < n && gj <= gi) A[(size_t)gi * n + gj] = a22[i] - s;
     }
 }
 
-__global__ void chol_status_clear(int* status) {
-    if (threadIdx.x == 0) status[0] = 0;
+// Tile (ti, tj) of the lower triangle from its transpose in the upper one
+// (which becomes zero), the diagonal from `diag`.
+__global__ __launch_bounds__(256) void chol_finish_kernel(double* __restrict__ A, int n,
+                                                          const double* __restrict__ diag) {
+    __shared__ double t[32][33];
+    int ti = (int)((sqrt(8.0 * blockIdx.x + 1.0) - 1.0) * 0.5);
+    while (ti * (ti + 1) / 2 > (int)blockIdx.x) --ti;
+    while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.x) ++ti;
+    const int tj = (int)blockIdx.x - ti * (ti + 1) / 2;
+    const int cc = threadIdx.x & 31, rq = threadIdx.x >> 5;
+    const int r0 = 32 * ti, c0 = 32 * tj;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = rq + 8 * i;   // upper tile: rows c0 + r, columns r0 + cc
+        if (c0 + r < n && r0 + cc < n) t[r][cc] = A[(size_t)(c0 + r) * n + r0 + cc];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = rq + 8 * i, gi = r0 + r, gj = c0 + cc;
+        if (ti != tj && c0 + r < n && r0 + cc < n) A[(size_t)(c0 + r) * n + r0 + cc] = 0.0;
+        if (gi < n && gj < n) A[(size_t)gi * n + gj] = gj < gi ? t[cc][r] : gj == gi ? diag[gi] : 0.0;
+    }
 }
 
 int launch_cholesky(svconv_plan* p, double* A, int n) {
     int st = SVCONV_OK;
-    if (n <= 64) {
-        hipLaunchKernelGGL(cholesky_kernel, dim3(1), dim3(1024), 0, p->stream, A, n, p->dStatus);
-        st = hip_status(hipGetLastError(), "cholesky_kernel");
-    } else {
-        hipLaunchKernelGGL(chol_status_clear, dim3(1), dim3(64), 0, p->stream, p->dStatus);
-        st = hip_status(hipGetLastError(), "chol_status_clear");
-        for (int k0 = 0; k0 < n && !st; k0 += CH_NB) {
-            const int nb = (n - k0) < CH_NB ? (n - k0) : CH_NB;
-            hipLaunchKernelGGL(chol_panel_kernel, dim3(1), dim3(256), 0, p->stream, A, n, k0, p->dStatus);
-            st = hip_status(hipGetLastError(), "chol_panel_kernel");
-            const int rest = n - k0 - nb;
-            if (!st && rest > 0) {
-                const int nt = (rest + 31) / 32;
-                hipLaunchKernelGGL(chol_update_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, p->stream,
-                                   A, n, k0, nb);
-                st = hip_status(hipGetLastError(), "chol_update_kernel");
-            }
-        }
-        if (!st) {
-            hipLaunchKernelGGL(chol_zero_upper, dim3(256), dim3(256), 0, p->stream, A, n);
-            st = hip_status(hipGetLastError(), "chol_zero_upper");
-        }
+    double* diag = p->dVec;   // [n]
+    for (int k0 = 0; k0 < n && !st; k0 += CH_NB) {
+        const int nt = n - k0 > CH_NB ? (n - k0 - 1) / CH_NB : 0;   // tiles of the rows below the block
+        hipLaunchKernelGGL(chol_step_kernel, dim3(nt ? nt * (nt + 1) / 2 : 1), dim3(256), 0, p->stream, A, n, k0, diag,
+                           p->dStatus);
+        st = hip_status(hipGetLastError(), "chol_step_kernel");
     }
+    if (st) return st;
+    const int nt = (n + 31) / 32;
+    hipLaunchKernelGGL(chol_finish_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, p->stream, A, n, diag);
+    st = hip_status(hipGetLastError(), "chol_finish_kernel");
     if (st) return st;
     int bad = 0;
     st = hip_status(hipMemcpyAsync(&bad, p->dStatus, sizeof(int), hipMemcpyDeviceToHost, p->stream),
@@ -752,113 +767,140 @@ int launch_cholesky(svconv_plan* p, double* A, int n) {
     return SVCONV_OK;
 }
 
-// x = L^-T L^-1 rhs by blocked substitutions in one workgroup of 1024
-// threads.  Per block of 32 unknowns, one wave solves the 32 x 32 triangle
-// (each unknown broadcast across the lanes, the diagonal's reciprocals formed
-// first); then every thread folds the block's unknowns into the right-hand
-// side entries still to be solved (right-looking): one row of the panel per
-// thread in the forward pass (32 independent loads of contiguous doubles),
-// one column per thread in the backward pass (loads coalesced across the
-// wave).  So each block waits on memory once.  v holds the right-hand side,
-// then the solution.
-constexpr int CS_B = 32;
+// x = L^-T L^-1 rhs by blocked substitutions in one workgroup, n <= 1024.
+// Wave 0 solves one 32 x 32 triangle after the other, each unknown broadcast
+// by v_readlane, while eight helper waves form what the next block takes from
+// the unknowns found so far (coalesced loads, thread (hr, hc) for the rows hr and
+// hr + 16) and stage its triangle and the 32 x 32 piece that meets the block
+// being solved, which wave 0 applies itself: one barrier per block.
+// Bound: the serial chain of the triangles, about 100 cycles per unknown.  n =
+// 294: 80 us (panels after triangles, every thread a row of its own with 64
+// cache lines per load) -> 34 us; n = 735: 228 -> 124 us.  With a64, the Newton update is applied
+// at the end: a64 -= x, a32 = float(a64), norm = ||x||_2.
+constexpr int CS_B = 32, CS_HELPERS = 512, CS_NT = 64 + CS_HELPERS;
 
-__global__ __launch_bounds__(1024) void chol_solve_kernel(const double* __restrict__ L,
-                                                          const double* __restrict__ rhs,
-                                                          double* __restrict__ x, int n) {
-    extern __shared__ double v[];   // n doubles
-    const int tid = threadIdx.x;
-    for (int i = tid; i < n; i += 1024) v[i] = rhs[i];
+__global__ __launch_bounds__(CS_NT) void chol_solve_kernel(const double* __restrict__ L,
+                                                           const double* __restrict__ rhs,
+                                                           double* __restrict__ x, int n,
+                                                           double* __restrict__ a64, float* __restrict__ a32,
+                                                           double* __restrict__ norm) {
+    // per buffer: the triangle below its diagonal, the reciprocals, the piece
+    // and the sums of the block to solve next
+    __shared__ double v[kMaxCoefficients], T[2][CS_B][CS_B + 1], piece[2][CS_B][CS_B + 1], part[2][CS_B][CS_B + 1];
+    __shared__ double dinv[2][CS_B];
+    const int tid = threadIdx.x, nblk = (n + CS_B - 1) / CS_B;
+    const int ht = tid - 64, hr = ht >> 5, hc = ht & 31;   // helpers
+    // entry (r, c) of L, zero outside
+    auto at = [&](int r, int c) {
+        const double t = L[(size_t)min(max(r, 0), n - 1) * n + min(max(c, 0), n - 1)];
+        return r >= 0 && r < n && c >= 0 && c < n ? t : 0.0;
+    };
+    // helpers: block kb into `buf`, `known` blocks of unknowns before (after) it
+    // summed, the one next to it staged as the piece
+    auto prepare = [&](int buf, int kb, bool forward) {
+        const int j0 = kb * CS_B;
+        double t[2], p[2], s[2] = {0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int r = hr + 16 * q;
+            // T[t][j] is what unknown j takes from row t: L[t][j], j < t, or L[j][t], j > t
+            t[q] = at(j0 + r, j0 + hc);
+            p[q] = forward ? at(j0 + r, j0 - CS_B + hc) : at(j0 + CS_B + r, j0 + hc);
+        }
+        if (forward) {
+#pragma unroll 8
+            for (int i = 0; i < kb - 1; ++i) {
+                const double y = v[CS_B * i + hc];
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    s[q] = fma(L[(size_t)min(j0 + hr + 16 * q, n - 1) * n + CS_B * i + hc], y, s[q]);
+            }
+        } else {
+#pragma unroll 8
+            for (int i = kb + 2; i < nblk; ++i)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int r = CS_B * i + hr + 16 * q;   // v is 0 past n
+                    s[q] = fma(L[(size_t)min(r, n - 1) * n + j0 + hc], v[r], s[q]);
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int r = hr + 16 * q;
+            if (forward) {
+                T[buf][r][hc] = hc < r ? t[q] : 0.0;
+                piece[buf][r][hc] = p[q];
+                part[buf][r][hc] = s[q];
+            } else {
+                T[buf][hc][r] = hc < r ? t[q] : 0.0;
+                piece[buf][hc][r] = p[q];
+                part[buf][hc][r] = s[q];
+            }
+            if (r == hc) dinv[buf][r] = j0 + r < n ? 1.0 / t[q] : 1.0;
+        }
+    };
+    // wave 0: the unknowns of block kb, given those of block `from` next to it
+    auto solve = [&](int buf, int kb, int from, bool forward) {
+        const int t = tid & 31, half = (tid >> 5) * 16;
+        const double inv = dinv[buf][t];
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s0 += part[buf][t][half + i];
+        if (from >= 0 && from < nblk) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s1 = fma(piece[buf][t][half + i], v[CS_B * from + half + i], s1);
+        }
+        s0 += s1;
+        double acc = v[CS_B * kb + t] - (s0 + __shfl_xor(s0, 32));
+#pragma unroll
+        for (int i = 0; i < CS_B; ++i) {
+            const int j = forward ? i : CS_B - 1 - i;
+            acc = fma(-T[buf][t][j], lane_value(acc * inv, j), acc);   // 0 for the unknowns already found
+        }
+        if (tid < 32) v[CS_B * kb + t] = CS_B * kb + t < n ? acc * inv : 0.0;
+    };
+    for (int i = tid; i < nblk * CS_B; i += CS_NT) v[i] = i < n ? rhs[i] : 0.0;
     __syncthreads();
-    const int nblk = (n + CS_B - 1) / CS_B;
-    // forward: L y = b
+    if (tid >= 64) prepare(0, 0, true);
+    __syncthreads();
     for (int kb = 0; kb < nblk; ++kb) {
-        const int j0 = kb * CS_B, nb = min(CS_B, n - j0);
-        if (tid < 64) {
-            // lane t < nb: row j0 + t of the triangle, loaded into registers first
-            const int t = tid;
-            const bool live = t < nb;
-            const double* Lt = L + (size_t)(j0 + (live ? t : 0)) * n + j0;
-            double l[CS_B];
-#pragma unroll
-            for (int j = 0; j < CS_B; ++j) l[j] = (live && j < nb) ? Lt[j] : 0.0;
-            const double inv = live ? 1.0 / Lt[t] : 0.0;
-            double acc = live ? v[j0 + t] : 0.0;
-#pragma unroll
-            for (int j = 0; j < CS_B; ++j) {
-                if (j < nb) {
-                    const double yj = __shfl(acc, j) * __shfl(inv, j);
-                    if (t > j) acc = fma(-l[j], yj, acc);
-                    if (t == j) acc = yj;
-                }
-            }
-            if (live) v[j0 + t] = acc;
-        }
-        __syncthreads();
-        // rows below the block: v[i] -= L[i][j0 .. j0 + nb) y
-        for (int i = j0 + nb + tid; i < n; i += 1024) {
-            const double* Li = L + (size_t)i * n + j0;
-            double s = 0.0;
-            if (nb == CS_B) {
-                // a full block: the row's loads issued together
-                double l[CS_B];
-#pragma unroll
-                for (int c = 0; c < CS_B; ++c) l[c] = Li[c];
-#pragma unroll
-                for (int c = 0; c < CS_B; ++c) s = fma(l[c], v[j0 + c], s);
-            } else {
-                for (int c = 0; c < nb; ++c) s = fma(Li[c], v[j0 + c], s);
-            }
-            v[i] -= s;
-        }
+        if (tid < 64) solve(kb & 1, kb, kb - 1, true);
+        else if (kb + 1 < nblk) prepare((kb + 1) & 1, kb + 1, true);
+        else prepare((kb + 1) & 1, kb, false);   // the backward pass starts where this one ends
         __syncthreads();
     }
-    // backward: L^T x = y
-    for (int kb = nblk - 1; kb >= 0; --kb) {
-        const int j0 = kb * CS_B, nb = min(CS_B, n - j0);
-        if (tid < 64) {
-            // lane t < nb: column j0 + t of the triangle, loaded into registers first
-            const int t = tid;
-            const bool live = t < nb;
-            const double* Lc = L + (size_t)j0 * n + j0 + (live ? t : 0);
-            double l[CS_B];
-#pragma unroll
-            for (int j = 0; j < CS_B; ++j) l[j] = (live && j < nb) ? Lc[(size_t)j * n] : 0.0;
-            const double inv = live ? 1.0 / Lc[(size_t)t * n] : 0.0;
-            double acc = live ? v[j0 + t] : 0.0;
-#pragma unroll
-            for (int j = CS_B - 1; j >= 0; --j) {
-                if (j < nb) {
-                    const double xj = __shfl(acc, j) * __shfl(inv, j);
-                    if (t < j) acc = fma(-l[j], xj, acc);
-                    if (t == j) acc = xj;
-                }
-            }
-            if (live) v[j0 + t] = acc;
-        }
-        __syncthreads();
-        // columns left of the block: v[c] -= sum_r L[j0 + r][c] x[j0 + r]
-        for (int c = tid; c < j0; c += 1024) {
-            double s = 0.0;
-            if (nb == CS_B) {
-                double l[CS_B];
-#pragma unroll
-                for (int r = 0; r < CS_B; ++r) l[r] = L[(size_t)(j0 + r) * n + c];
-#pragma unroll
-                for (int r = 0; r < CS_B; ++r) s = fma(l[r], v[j0 + r], s);
-            } else {
-                for (int r = 0; r < nb; ++r) s = fma(L[(size_t)(j0 + r) * n + c], v[j0 + r], s);
-            }
-            v[c] -= s;
-        }
+    for (int q = 0; q < nblk; ++q) {
+        const int kb = nblk - 1 - q, buf = (nblk + q) & 1;
+        if (tid < 64) solve(buf, kb, kb + 1, false);
+        else if (kb > 0) prepare(buf ^ 1, kb - 1, false);
         __syncthreads();
     }
-    for (int i = tid; i < n; i += 1024) x[i] = v[i];
+    double ss = 0.0;
+    for (int i = tid; i < n; i += CS_NT) {
+        const double d = v[i];
+        x[i] = d;
+        if (a64) {
+            const double a = a64[i] - d;
+            a64[i] = a;
+            a32[i] = (float)a;
+            ss += d * d;
+        }
+    }
+    if (!a64) return;   // uniform
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    __syncthreads();
+    if ((tid & 63) == 0) v[tid >> 6] = ss;
+    __syncthreads();
+    if (tid == 0) {
+        double t = 0.0;
+        for (int w = 0; w < CS_NT / 64; ++w) t += v[w];
+        *norm = sqrt(t);
+    }
 }
 
-int launch_cholesky_solve(svconv_plan* p, const double* L, const double* rhs, double* x, int n) {
-    hipLaunchKernelGGL(chol_solve_kernel, dim3(1), dim3(1024), (size_t)n * sizeof(double), p->stream,
-                       L, rhs, x, n);
+int launch_cholesky_solve(svconv_plan* p, const double* L, const double* rhs, double* x, int n, double* a64,
+                          float* a32, double* norm) {
+    hipLaunchKernelGGL(chol_solve_kernel, dim3(1), dim3(CS_NT), 0, p->stream, L, rhs, x, n, a64, a32, norm);
     return hip_status(hipGetLastError(), "chol_solve_kernel");
 }
 
@@ -872,29 +914,6 @@ __global__ void scale_kernel(double* v, double s, int n) {
 __global__ void copy_a_kernel(const double* a64, float* a32, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) a32[i] = (float)a64[i];
-}
-
-// a64 -= delta, a32 = float(a64), norm = ||delta||_2 (one workgroup)
-__global__ __launch_bounds__(1024) void gn_update_kernel(const double* __restrict__ delta,
-                                                         double* __restrict__ a64,
-                                                         float* __restrict__ a32, int n,
-                                                         double* __restrict__ norm) {
-    __shared__ double red[1024];
-    double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += 1024) {
-        const double d = delta[i];
-        const double v = a64[i] - d;
-        a64[i] = v;
-        a32[i] = (float)v;
-        s += d * d;
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 512; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *norm = sqrt(red[0]);
 }
 
 int launch_scale(svconv_plan* p, double* v, double s, int n) {
@@ -959,13 +978,6 @@ __global__ __launch_bounds__(256) void ls_grad_kernel(const double* __restrict__
 int launch_ls_grad(svconv_plan* p, const double* A, const double* a64, const double* rhs, double* g, int n) {
     hipLaunchKernelGGL(ls_grad_kernel, dim3((n + 3) / 4), dim3(256), 0, p->stream, A, a64, rhs, n, g);
     return hip_status(hipGetLastError(), "ls_grad_kernel");
-}
-
-int launch_gn_update(svconv_plan* p, const double* delta, double* a64, float* a32, int n) {
-    // the step norm lands right after the loss scalar in the plan's vector scratch
-    double* norm = p->dVec + 2 * (size_t)n + 1;
-    hipLaunchKernelGGL(gn_update_kernel, dim3(1), dim3(1024), 0, p->stream, delta, a64, a32, n, norm);
-    return hip_status(hipGetLastError(), "gn_update_kernel");
 }
 
 }  // namespace svc

@@ -267,8 +267,9 @@ int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const u
                          double* JtJ, double* rhs);
 int launch_ls_grad(svconv_plan* p, const double* A, const double* a64, const double* rhs, double* g, int n);
 int launch_cholesky(svconv_plan* p, double* A, int n);
-int launch_cholesky_solve(svconv_plan* p, const double* L, const double* rhs, double* x, int n);
-int launch_gn_update(svconv_plan* p, const double* delta, double* a64, float* a32, int n);
+// with a64: also a64 -= x, a32 = float(a64), *norm = ||x||
+int launch_cholesky_solve(svconv_plan* p, const double* L, const double* rhs, double* x, int n,
+                          double* a64 = nullptr, float* a32 = nullptr, double* norm = nullptr);
 int launch_copy_a(svconv_plan* p, const double* a64, float* a32, int n);
 int launch_scale(svconv_plan* p, double* v, double s, int n);
 

@@ -681,8 +681,8 @@ int svconv_gn_step(svconv_plan* p, const float* R, const float* I, const unsigne
     if (!st) st = launch_adjoint_a(p, R, p->dGrad, ga);
     if (!st && p->bg) st = launch_bg_grad(p, p->dGrad, ga + NK);
     if (!st) st = launch_scale(p, ga, 0.5, NM);
-    if (!st) st = launch_cholesky_solve(p, L, ga, delta, NM);
-    if (!st) st = launch_gn_update(p, delta, a64, a32, NM);
+    // the step norm lands right after the loss scalar
+    if (!st) st = launch_cholesky_solve(p, L, ga, delta, NM, a64, a32, loss + 1);
     if (st) return st;
     if (host_stats) {
         double stats[2] = {0.0, 0.0};
@@ -716,8 +716,8 @@ int svconv_ls_step(svconv_plan* p, const float* R, const float* I, const unsigne
     if (!st) st = launch_loss_grad(p, D, mask, p->dGrad, loss);
     // J^T D = JtJ a - J^T I in float64, then the Newton step of the quadratic loss
     if (!st) st = launch_ls_grad(p, A, a64, rhs, g, NM);
-    if (!st) st = launch_cholesky_solve(p, L, g, delta, NM);
-    if (!st) st = launch_gn_update(p, delta, a64, a32, NM);
+    // the step norm lands right after the loss scalar
+    if (!st) st = launch_cholesky_solve(p, L, g, delta, NM, a64, a32, loss + 1);
     if (st) return st;
     if (host_stats) {
         double stats[2] = {0.0, 0.0};
