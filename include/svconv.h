@@ -122,7 +122,9 @@ enum svconv_form {
  * f_e(-w) = (-1)^e f_e(w)), the adjoint in a as the forward's passes in the
  * plan's split precision with moment sums in place of the epilogue.  At the
  * other precisions, and in the fit entry points (whose steps go through the
- * ill-conditioned normal matrix), the adjoints run in float64, and the basis
+ * ill-conditioned normal matrix), the adjoints run in float64 (the adjoint in
+ * R directly with regrouped filters where that is less work than the passes
+ * through the factors), and the basis
  * responses of the normal matrix always do (the float64 adjoint in a falls
  * back to the dense matrix-core product when its per-round moments do not
  * fit in LDS).  The adjoints in a sum with atomics, so repeated calls agree to

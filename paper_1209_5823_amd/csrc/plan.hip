@@ -577,6 +577,23 @@ static int run_adjoint_a(svconv_plan* p, const float* R, const float* gD, double
     return launch_adjoint_a(p, R, gD, ga);
 }
 
+// The float64 adjoint in R of a separable form, in vector instructions per
+// pixel: through the factors, N times the forming of c_n gD on the 64 x 64 tile
+// and its halo and a column pass, and a row pass per factor; directly, k^2 taps
+// with d_s + 1 products each and their folding.  Both kernels keep the vector
+// units busy for two to three quarters of the time (measured at 4096^2, 31 x
+// 31, 49 bases, third order: 4.74 ms through the factors, 2.9 ms directly; at
+// 517 x 771, 21 x 21, second order: 357 and 24 us), so the counts decide; few
+// bases on a wide kernel (10 at 31 x 31) stay with the factors.
+static bool adjoint_r_direct(const svconv_plan* p) {
+    const double k = p->k, J = p->d_s + 1, halo = 1.0 + p->h / 32.0;
+    int factors = 0;
+    for (int d : p->degrees) factors += d + 1;
+    const double sep = p->N * (halo * halo * (30 + 2 * J) + 1.1 * halo * k) + factors * (k + 10.0);
+    const double rows = J <= 4 ? 16 : 8;
+    return k * k * (J + (1.5 * p->M) / rows) < sep;
+}
+
 int svconv_backward(svconv_plan* p, const float* R, const float* a, const float* gD, float* gR,
                     double* ga) {
     if (!p || !R || !a || !gD) return fail(SVCONV_EINVAL, "NULL argument");
@@ -608,7 +625,7 @@ int svconv_backward(svconv_plan* p, const float* R, const float* a, const float*
         sa.coefpf = reinterpret_cast<const float*>(p->dSepCoef + (size_t)(p->N + 1) * kSepCoefPad);
         st = launch_adjoint_r_sep_mma(sa, p->dSepFrag, p->stream);
         if (st) return st;
-    } else if (gR && sep_form(p)) {
+    } else if (gR && sep_form(p) && !adjoint_r_direct(p)) {
         // through the separable factors (E_n = c_n gD correlated with B_n)
         st = launch_adjoint_r_sep(p, a, gD, gR);
         if (st) return st;

@@ -252,18 +252,32 @@ __global__ __launch_bounds__(64 * SA_NW) void adjoint_a_sep_kernel(SepAdjArgs a)
     }
 }
 
-// ga[n][m] = sum over workgroups (fixed order) + s beta_n gP[m]
-__global__ void adjoint_a_sep_final(const double* __restrict__ part, int n_wg, int N, int M,
-                                    const double* __restrict__ beta, float ped,
-                                    double* __restrict__ ga) {
-    const int nm = blockIdx.x * blockDim.x + threadIdx.x;
-    if (nm >= N * M) return;
-    const int n = nm / M, m = nm - n * M;
+// ga[n][m] = sum over workgroups (fixed order) + s beta_n gP[m].  Lanes take
+// consecutive entries, the 16 waves the partial arrays w, w + 16, ...  (one
+// thread per entry over all partial arrays waited for one load after the other:
+// 57 us for 221 of them -> 6 us.)
+constexpr int SAF_WAVES = 16;
+
+__global__ __launch_bounds__(64 * SAF_WAVES) void adjoint_a_sep_final(const double* __restrict__ part, int n_wg, int N,
+                                                                      int M, const double* __restrict__ beta,
+                                                                      float ped, double* __restrict__ ga) {
+    __shared__ double red[2][SAF_WAVES][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int nm = min((int)(blockIdx.x * 64) + lane, N * M - 1), n = nm / M, m = nm - n * M;
     const size_t stride = (size_t)(N + 1) * M;
     double s = 0.0, gp = 0.0;
-    for (int b = 0; b < n_wg; ++b) {
+#pragma unroll 8
+    for (int b = w; b < n_wg; b += SAF_WAVES) {
         s += part[b * stride + nm];
         gp += part[b * stride + (size_t)N * M + m];
+    }
+    red[0][w][lane] = s;
+    red[1][w][lane] = gp;
+    __syncthreads();
+    if (w || (int)(blockIdx.x * 64) + lane >= N * M) return;
+    for (int q = 1; q < SAF_WAVES; ++q) {
+        s += red[0][q][lane];
+        gp += red[1][q][lane];
     }
     ga[nm] = s + (double)ped * beta[n] * gp;
 }
@@ -350,7 +364,7 @@ int launch_adjoint_a_sep(svconv_plan* p, const float* R, const float* G, double*
         default: st = launch_asep_t<15>(a, n_wg, lds, p->stream); break;
     }
     if (st) return st;
-    hipLaunchKernelGGL(adjoint_a_sep_final, dim3((NM + 255) / 256), dim3(256), 0, p->stream, p->dQpart,
+    hipLaunchKernelGGL(adjoint_a_sep_final, dim3((NM + 63) / 64), dim3(64 * SAF_WAVES), 0, p->stream, p->dQpart,
                        n_wg, p->N, p->M, p->dBeta, p->pedestal, ga);
     return hip_status(hipGetLastError(), "adjoint_a_sep_final");
 }
