@@ -109,11 +109,16 @@ struct SepZArgs {
     double sx, ox, sy, oy;
     int tiles_x, n_tiles;
     int y_begin, n_rows;
-    const int* rinfo;           // [2 R]: family, factor index
     const uint16_t* rtab;       // row-pass tap fragments of the precision
     const uint16_t* ztab;       // [R][3] per-call column-pass fragments
     const float* zinv;          // [6] 1 / (tap scale x data scale) per spatial term
     const double* gam;          // [kSepCoefPad] sum_n a[n][m] beta_n, zero-padded
+};
+
+// The Gaussian families by value: a kernel argument of the per-call tables.
+struct SepZFamilies {
+    int G;
+    int degree[kMaxFilters];
 };
 
 // Regrouped contraction in float64 on the vector units (direct.hip).
@@ -239,8 +244,8 @@ size_t sepz_ztab_entries(int R);
 // only: -1 builds both precisions (fp16 then bf16), 0 only fp16, 1 only bf16
 int build_sepz_rtab(const double* f1d, const int* rinfo, int R, int h, uint16_t* rtab, hipStream_t s,
                     int only = -1);
-int launch_sepz_prep(const SepZArgs& z, const float* a, const double* f1d, const int* fam, const double* beta, int N,
-                     bool fp16, hipStream_t s);
+int launch_sepz_prep(const SepZArgs& z, const float* a, const double* f1d, const SepZFamilies& fam,
+                     const double* beta, int N, bool fp16, hipStream_t s);
 int launch_contract_sepz(SepZArgs a, int precision, hipStream_t s);
 
 // direct.hip

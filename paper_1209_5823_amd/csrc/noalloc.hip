@@ -57,12 +57,11 @@ struct NoAllocSpec {
 
 // The tables a plan would build on the host, built by one workgroup:
 // f1d[g][e][w + h] = exp(-w^2 / 2 sigma_g^2) w^e / sum_w |exp(-w^2 / 2 sigma_g^2) w^e|
-// (the one-dimensional factors of the Gaussian bases, Sec. 2), fam[g] =
-// (degree, first basis), rinfo[r] = (family, factor) of each row factor, and
+// (the one-dimensional factors of the Gaussian bases, Sec. 2), rinfo[r] =
+// (family, factor) of each row factor, and
 // beta_n = sum of basis n = (sum_u f_i(u)) (sum_v f_j(v)).
 __global__ __launch_bounds__(256) void noalloc_tables_kernel(NoAllocSpec spec, double* __restrict__ f1d,
-                                                             int* __restrict__ fam, int* __restrict__ rinfo,
-                                                             double* __restrict__ beta) {
+                                                             int* __restrict__ rinfo, double* __restrict__ beta) {
     __shared__ double fsum[kNoAllocMaxFamilies * kSepMaxFactors];
     const int tid = threadIdx.x, h = spec.h, k = 2 * h + 1;
     const int nf = spec.G * kSepMaxFactors;
@@ -91,8 +90,6 @@ __global__ __launch_bounds__(256) void noalloc_tables_kernel(NoAllocSpec spec, d
         int n = 0, r = 0;
         for (int g = 0; g < spec.G; ++g) {
             const int d = spec.degree[g];
-            fam[2 * g] = d;
-            fam[2 * g + 1] = n;
             for (int i = 0; i <= d; ++i) {
                 rinfo[2 * r] = g;
                 rinfo[2 * r + 1] = i;
@@ -147,8 +144,7 @@ extern "C" int svconv_difference_noalloc(int height, int width, int half_width, 
 
     // scratch layout (256-byte aligned sections)
     const size_t o_f1d = 0;
-    const size_t o_fam = o_f1d + up256((size_t)n_gauss * kSepMaxFactors * k * sizeof(double));
-    const size_t o_rinfo = o_fam + up256((size_t)2 * n_gauss * sizeof(int));
+    const size_t o_rinfo = o_f1d + up256((size_t)n_gauss * kSepMaxFactors * k * sizeof(double));
     const size_t o_beta = o_rinfo + up256((size_t)2 * Rf * sizeof(int));
     const size_t o_rtab = o_beta + up256((size_t)N * sizeof(double));
     const size_t o_ztab = o_rtab + up256(sepz_rtab_entries(Rf) / 2 * sizeof(uint16_t));
@@ -162,7 +158,6 @@ extern "C" int svconv_difference_noalloc(int height, int width, int half_width, 
     if (st) return st;
     unsigned char* sb = static_cast<unsigned char*>(base);
     double* f1d = reinterpret_cast<double*>(sb + o_f1d);
-    int* fam = reinterpret_cast<int*>(sb + o_fam);
     int* rinfo = reinterpret_cast<int*>(sb + o_rinfo);
     double* beta = reinterpret_cast<double*>(sb + o_beta);
     uint16_t* rtab = reinterpret_cast<uint16_t*>(sb + o_rtab);
@@ -175,7 +170,7 @@ extern "C" int svconv_difference_noalloc(int height, int width, int half_width, 
         spec.sigma[g] = sigmas[g];
         spec.degree[g] = degrees[g];
     }
-    hipLaunchKernelGGL(noalloc_tables_kernel, dim3(1), dim3(256), 0, s, spec, f1d, fam, rinfo, beta);
+    hipLaunchKernelGGL(noalloc_tables_kernel, dim3(1), dim3(256), 0, s, spec, f1d, rinfo, beta);
     st = hip_status(hipGetLastError(), "noalloc_tables_kernel");
     const bool h16 = precision != SVCONV_BF16X3;
     if (!st) st = build_sepz_rtab(f1d, rinfo, Rf, half_width, rtab, s, h16 ? 0 : 1);
@@ -198,12 +193,14 @@ extern "C" int svconv_difference_noalloc(int height, int width, int half_width, 
     z.oy = height > 1 ? -1.0 : 0.0;
     z.y_begin = 0;
     z.n_rows = height;
-    z.rinfo = rinfo;
     z.rtab = rtab;
     z.ztab = reinterpret_cast<const uint16_t*>(sb + o_ztab);
     z.zinv = reinterpret_cast<const float*>(sb + o_zinv);
     z.gam = reinterpret_cast<const double*>(sb + o_gam);
-    st = launch_sepz_prep(z, a, f1d, fam, beta, N, h16, s);
+    SepZFamilies families{};
+    families.G = n_gauss;
+    for (int g = 0; g < n_gauss; ++g) families.degree[g] = degrees[g];
+    st = launch_sepz_prep(z, a, f1d, families, beta, N, h16, s);
     if (st) return st;
     return launch_contract_sepz(z, precision, s);
 }

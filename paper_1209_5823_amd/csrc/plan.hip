@@ -272,13 +272,15 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
         z.sx = c.sx; z.ox = c.ox; z.sy = c.sy; z.oy = c.oy;
         z.y_begin = 0;
         z.n_rows = p->H;
-        z.rinfo = p->dSepRinfo;
         const bool h16 = is_fp16(p->precision);
         z.rtab = p->dSepZRow + (h16 ? 0 : sepz_rtab_entries(p->sepR) / 2);
         z.ztab = p->dSepZTab;
         z.zinv = p->dSepZInv;
         z.gam = p->dSepZGam;
-        int st = launch_sepz_prep(z, a, p->dSep1d, p->dSepFam, p->dBeta, p->N, h16, p->stream);
+        SepZFamilies fam{};
+        fam.G = (int)p->degrees.size();
+        for (int g = 0; g < fam.G; ++g) fam.degree[g] = p->degrees[g];
+        int st = launch_sepz_prep(z, a, p->dSep1d, fam, p->dBeta, p->N, h16, p->stream);
         if (st) return st;
         return launch_contract_sepz(z, p->precision, p->stream);
     }

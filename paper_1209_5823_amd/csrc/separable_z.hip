@@ -186,96 +186,81 @@ int build_sepz_rtab(const double* f1d, const int* rinfo, int R, int h, uint16_t*
     return hip_status(hipGetLastError(), "sepz_rtab_kernel");
 }
 
-// Value of the regrouped column filter g_{r,m} at tap u (float64):
-// sum_j a[n(r,j)][m] f_j(u) over the column factors j of row factor r's
-// family (the family's factors are row factors r - i .. r - i + degree), from
-// the block's copies of a and of the factors; i is r's index in its family,
-// deg and base the family's degree and first basis.
-__device__ __forceinline__ double sz_gval(const float* as, const double* fcs, int i, int deg, int base, int M, int k,
-                                          int r, int m, int u) {
-    double s = 0.0;
-    for (int j = 0; j + i <= deg; ++j) {
-        const int tt = i + j;
-        const int n = base + tt * (tt + 1) / 2 + j;
-        s = fma((double)as[n * M + m], fcs[(r - i + j) * k + u], s);
-    }
-    return s;
-}
-
 constexpr int kSzPrepMaxRows = 64;   // row factors (N <= 64)
 
 // Per-call tables: block (r, mp) writes the column-pass fragments of row
 // factor r and spatial terms 2 mp, 2 mp + 1 (both phases, hi and lo):
 // ztab[r][mp][ph][hl][lane][t] = split(S_m g_{r,m}(y + 2h - rho)), m = 2 mp +
 // (lane mod 16) / 8, y = lane mod 8, rho = sz_col_row(ph, lane / 16, t), zero
-// outside [0, 2h] and for m >= M; S_m is the power of two that puts the
-// largest |g_{., m}| in [1, 2).  Blocks of r = 0 also write zinv[m] =
+// outside [0, 2h] and for m >= M; g_{r,m}(u) = sum_j a[n(r,j)][m] f_j(u) over
+// the column factors j of row factor r's family; S_m is the power of two that
+// puts the largest |g_{., m}| in [1, 2).  Blocks of r = 0 also write zinv[m] =
 // 1 / (S_m xscale), and block (0, 0) the padded pedestal sums
-// gam[m] = sum_n a[n][m] beta_n.  a, beta and the factors are first copied
-// into LDS (every load of a phase in flight together), so the sums read no
-// global memory; the maxima reduce across each wave by shuffles.
+// gam[m] = sum_n a[n][m] beta_n.
+//
+// Bound: latency (45 workgroups of work for one).  The families arrive as a
+// kernel argument, so a, beta and the factors are one phase of loads (with the
+// families in memory they were two, the second waiting for the first), and the
+// filters are formed once, for the maxima, and kept.  9.1 -> PREPUS us at 49 bases.
 template <bool FP16>
 __global__ __launch_bounds__(256) void sepz_prep_kernel(const float* __restrict__ a, const double* __restrict__ f1d,
-                                                        const int* __restrict__ rinfo, const int* __restrict__ fam,
-                                                        const double* __restrict__ beta, int R, int N, int M, int h,
-                                                        float xscale, uint16_t* __restrict__ ztab,
-                                                        float* __restrict__ zinv, double* __restrict__ gam) {
+                                                        SepZFamilies fam, const double* __restrict__ beta, int R,
+                                                        int N, int M, int h, float xscale,
+                                                        uint16_t* __restrict__ ztab, float* __restrict__ zinv,
+                                                        double* __restrict__ gam) {
     constexpr int KMAX = 2 * kSepZMaxHalfWidth + 1;
     __shared__ double red[2][4];
-    __shared__ double scale[2];
-    __shared__ double fcs[kSzPrepMaxRows * KMAX];
+    __shared__ double fcs[kSzPrepMaxRows * KMAX], gv[2][kSzPrepMaxRows * KMAX];
     __shared__ double bt[kMaxFilters];
     __shared__ float as[kMaxFilters * 6];
-    __shared__ int ri[2 * kSzPrepMaxRows];
-    __shared__ int rfam[2 * kSzPrepMaxRows];   // per row factor: family degree, first basis
     const int r = blockIdx.x, mp = blockIdx.y, tid = threadIdx.x;
-    const int k = 2 * h + 1;
-    // a, beta and the row factors' (family, index) pairs; clamped addresses,
-    // so that no load is conditional
-    constexpr int NA = (kMaxFilters * 6 + 255) / 256;
-    {
-        float av[NA];
-#pragma unroll
-        for (int i = 0; i < NA; ++i) av[i] = a[min(tid + 256 * i, N * M - 1)];
-        const int rv = rinfo[min(tid, 2 * R - 1)];
-        const double bv = beta[min(tid, N - 1)];
-#pragma unroll
-        for (int i = 0; i < NA; ++i)
-            if (tid + 256 * i < N * M) as[tid + 256 * i] = av[i];
-        if (tid < 2 * R) ri[tid] = rv;
-        if (tid < N) bt[tid] = bv;
+    const int k = 2 * h + 1, n_f = R * k;
+    const float inv_k = 1.f / (float)k;
+    // q / k: exact, as q < 2^11 and (q + 1/2) / k is 1/50 from an integer at least
+    auto row_of = [&](int q) { return (int)(((float)q + 0.5f) * inv_k); };
+    // family g of row factor rr, its degree, its first row factor and its first basis
+    auto family = [&](int rr, int& g, int& deg, int& first, int& base) {
+        g = first = base = 0;
+        deg = fam.degree[0];
+        for (int q = 0; q + 1 < fam.G; ++q) {
+            const int d = fam.degree[q], next = fam.degree[q + 1];   // uniform
+            if (rr > first + d && g == q) {
+                first += d + 1;
+                base += (d + 1) * (d + 2) / 2;
+                deg = next;
+                ++g;
+            }
+        }
+    };
+    for (int q = tid; q < N * M; q += 256) as[q] = a[q];
+    if (tid < N) bt[tid] = beta[tid];
+#pragma unroll 2
+    for (int q = tid; q < n_f; q += 256) {
+        const int rr = row_of(q);
+        int g, deg, first, base;
+        family(rr, g, deg, first, base);
+        fcs[q] = f1d[((size_t)g * kSepMaxFactors + rr - first) * k + q - rr * k];
     }
     __syncthreads();
-    constexpr int NF = (kSzPrepMaxRows * KMAX + 255) / 256;
-    {
-        double fv[NF];
-#pragma unroll
-        for (int i = 0; i < NF; ++i) {
-            const int q = min(tid + 256 * i, R * k - 1);
-            const int rr = q / k, u = q - rr * k;
-            fv[i] = f1d[((size_t)ri[2 * rr] * kSepMaxFactors + ri[2 * rr + 1]) * k + u];
-        }
-        const int fr = min(tid, R - 1);
-        const int fd = fam[2 * ri[2 * fr]], fb = fam[2 * ri[2 * fr] + 1];
-#pragma unroll
-        for (int i = 0; i < NF; ++i)
-            if (tid + 256 * i < R * k) fcs[tid + 256 * i] = fv[i];
-        if (tid < R) {
-            rfam[2 * tid] = fd;
-            rfam[2 * tid + 1] = fb;
-        }
-    }
-    __syncthreads();
-    // largest |g_{r', m}| over every row factor and tap, for m = 2 mp + s
+    // g_{rr, m} for m = 2 mp + s and its largest magnitude over every row factor and tap
     double mx[2] = {0.0, 0.0};
-    for (int q = tid; q < R * k; q += 256) {
-        const int rr = q / k, u = q - rr * k;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int m = 2 * mp + s;
-            if (m < M)
-                mx[s] = fmax(mx[s], fabs(sz_gval(as, fcs, ri[2 * rr + 1], rfam[2 * rr], rfam[2 * rr + 1], M, k, rr, m, u)));
+    const int m0 = 2 * mp, m1 = min(2 * mp + 1, M - 1);
+    for (int q = tid; q < n_f; q += 256) {
+        const int rr = row_of(q), u = q - rr * k;
+        int g, deg, first, base;
+        family(rr, g, deg, first, base);
+        const int i = rr - first;
+        double v0 = 0.0, v1 = 0.0;
+        for (int j = 0; j + i <= deg; ++j) {
+            const int tt = i + j, n = base + tt * (tt + 1) / 2 + j;
+            const double f = fcs[(first + j) * k + u];
+            v0 = fma((double)as[n * M + m0], f, v0);
+            v1 = fma((double)as[n * M + m1], f, v1);
         }
+        gv[0][q] = v0;
+        gv[1][q] = v1;
+        mx[0] = fmax(mx[0], fabs(v0));
+        mx[1] = fmax(mx[1], fabs(v1));
     }
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
@@ -284,33 +269,34 @@ __global__ __launch_bounds__(256) void sepz_prep_kernel(const float* __restrict_
         if ((tid & 63) == 0) red[s][tid >> 6] = mx[s];
     }
     __syncthreads();
-    if (tid < 2) {
-        const double v = fmax(fmax(red[tid][0], red[tid][1]), fmax(red[tid][2], red[tid][3]));
-        double sc = 1.0;
+    double scale[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const double v = fmax(fmax(red[s][0], red[s][1]), fmax(red[s][2], red[s][3]));
+        scale[s] = 1.0;
         if (v > 0.0) {
             int e;
-            (void)frexp(v, &e);          // v = f 2^e, f in [0.5, 1)
-            sc = ldexp(1.0, 1 - e);      // v sc in [1, 2)
+            (void)frexp(v, &e);            // v = f 2^e, f in [0.5, 1)
+            scale[s] = ldexp(1.0, 1 - e);  // v scale in [1, 2)
         }
-        scale[tid] = sc;
-        const int m = 2 * mp + tid;
-        if (r == 0 && m < M) zinv[m] = (float)(1.0 / (sc * (double)xscale));
     }
+    if (tid < 2 && r == 0 && 2 * mp + tid < M)
+        zinv[2 * mp + tid] = (float)(1.0 / ((tid ? scale[1] : scale[0]) * (double)xscale));
     if (r == 0 && mp == 0 && tid < kSepCoefPad) {
         double s = 0.0;
         if (tid < M)
             for (int n = 0; n < N; ++n) s = fma((double)as[n * M + tid], bt[n], s);
         gam[tid] = s;
     }
-    __syncthreads();
     uint16_t* dst = ztab + ((size_t)r * 3 + mp) * SZ_FRAG;
-    for (int q = tid; q < 2 * 64 * 8; q += 256) {
+#pragma unroll
+    for (int q0 = 0; q0 < 2 * 64 * 8; q0 += 256) {
+        const int q = q0 + tid;
         const int t = q & 7, lane = (q >> 3) & 63, ph = q >> 9;
         const int s = (lane & 15) >> 3, y = lane & 7, g = lane >> 4;
-        const int m = 2 * mp + s;
         const int u = y + 2 * h - sz_col_row(ph, g, t);
         double v = 0.0;
-        if (m < M && u >= 0 && u < k) v = scale[s] * sz_gval(as, fcs, ri[2 * r + 1], rfam[2 * r], rfam[2 * r + 1], M, k, r, m, u);
+        if (2 * mp + s < M && u >= 0 && u < k) v = (s ? scale[1] : scale[0]) * gv[s][r * k + u];
         uint16_t hi, lo;
         sz_split_tap<FP16>(v, hi, lo);
         dst[((ph * 2 + 0) * 64 + lane) * 8 + t] = hi;
@@ -318,18 +304,18 @@ __global__ __launch_bounds__(256) void sepz_prep_kernel(const float* __restrict_
     }
 }
 
-int launch_sepz_prep(const SepZArgs& z, const float* a, const double* f1d, const int* fam, const double* beta, int N,
-                     bool fp16, hipStream_t s) {
-    if (z.R > kSzPrepMaxRows || N > kMaxFilters || z.M > 6 || z.h > kSepZMaxHalfWidth)
+int launch_sepz_prep(const SepZArgs& z, const float* a, const double* f1d, const SepZFamilies& fam,
+                     const double* beta, int N, bool fp16, hipStream_t s) {
+    if (z.R > kSzPrepMaxRows || N > kMaxFilters || z.M > 6 || z.h > kSepZMaxHalfWidth || fam.G > kMaxFilters)
         return fail(SVCONV_EUNSUPPORTED, "regrouped separable tables: at most 64 row factors, 64 bases, 6 terms");
     const int MP = (z.M + 1) / 2;
     const float xscale = fp16 ? 0.25f : 1.f;
     if (fp16)
-        hipLaunchKernelGGL(sepz_prep_kernel<true>, dim3(z.R, MP), dim3(256), 0, s, a, f1d, z.rinfo, fam, beta, z.R, N,
+        hipLaunchKernelGGL(sepz_prep_kernel<true>, dim3(z.R, MP), dim3(256), 0, s, a, f1d, fam, beta, z.R, N,
                            z.M, z.h, xscale, const_cast<uint16_t*>(z.ztab), const_cast<float*>(z.zinv),
                            const_cast<double*>(z.gam));
     else
-        hipLaunchKernelGGL(sepz_prep_kernel<false>, dim3(z.R, MP), dim3(256), 0, s, a, f1d, z.rinfo, fam, beta, z.R, N,
+        hipLaunchKernelGGL(sepz_prep_kernel<false>, dim3(z.R, MP), dim3(256), 0, s, a, f1d, fam, beta, z.R, N,
                            z.M, z.h, xscale, const_cast<uint16_t*>(z.ztab), const_cast<float*>(z.zinv),
                            const_cast<double*>(z.gam));
     return hip_status(hipGetLastError(), "sepz_prep_kernel");
