@@ -59,16 +59,23 @@ typedef __bf16 sz_b8 __attribute__((ext_vector_type(8)));
 constexpr int SZ_NW = 4;                  // waves per workgroup (16-column strips)
 constexpr int SZ_NT = 64 * SZ_NW;
 constexpr int SZ_TW = 16 * SZ_NW;         // tile width
-constexpr int SZ_OB = 8;                  // 8-row output blocks of a strip (even)
-constexpr int SZ_MINW = 2;                // waves per SIMD the registers allow
-constexpr int SZ_TH = 8 * SZ_OB;          // tile height
-constexpr int SZ_RB = SZ_OB / 2 + 2;      // 16-row blocks of row responses (16 SZ_RB >= SZ_TH + 2h for h <= 12)
-constexpr int SZ_XR = 16 * SZ_RB;         // staged rows
 constexpr int SZ_XC = SZ_TW + 24;         // staged columns the windows reach (88)
 constexpr int SZ_P = SZ_XC;               // pitch in 16-bit elements: 11 x 16 B (odd)
 constexpr int SZ_FRAG = 2 * 2 * 64 * 8;   // one table entry: [2 (cg or phase)][hi/lo][lane][8]
-constexpr size_t SZ_XLDS = (size_t)2 * SZ_XR * SZ_P * sizeof(uint16_t);     // staged tile
-constexpr size_t SZ_LDS = SZ_XLDS + (size_t)SZ_NW * SZ_RB * 64 * 16;         // + per-wave factor-B rows
+
+// Sizes of a tile of OB (even) 8-row output blocks whose strips are shared by
+// SP waves each.
+template <int OB, int SP>
+struct SzTile {
+    static constexpr int TH = 8 * OB;             // tile height
+    static constexpr int RB = OB / 2 + 2;         // 16-row blocks of row responses (16 RB >= TH + 2h for h <= 12)
+    static constexpr int XR = 16 * RB;            // staged rows
+    static constexpr int NW = SZ_NW * SP;         // waves
+    static constexpr int SROWS = XR / NW;         // staged rows per wave
+    static constexpr int MINW = OB == 8 ? 2 : OB == 4 ? 3 : 4;   // waves per SIMD the registers allow
+    static constexpr size_t XLDS = (size_t)2 * XR * SZ_P * sizeof(uint16_t);          // staged tile
+    static constexpr size_t LDS = XLDS + (size_t)NW * RB * 64 * 16;                   // + per-wave factor-B rows
+};
 
 __device__ __forceinline__ uint32_t sz_f2h(float x) { return (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)x); }
 __device__ __forceinline__ float sz_h2f(uint32_t b) { return (float)__builtin_bit_cast(_Float16, (uint16_t)b); }
@@ -201,7 +208,7 @@ constexpr int kSzPrepMaxRows = 64;   // row factors (N <= 64)
 // Bound: latency (45 workgroups of work for one).  The families arrive as a
 // kernel argument, so a, beta and the factors are one phase of loads (with the
 // families in memory they were two, the second waiting for the first), and the
-// filters are formed once, for the maxima, and kept.  9.1 -> PREPUS us at 49 bases.
+// filters are formed once, for the maxima, and kept.  9.1 -> 7.3 us at 49 bases.
 template <bool FP16>
 __global__ __launch_bounds__(256) void sepz_prep_kernel(const float* __restrict__ a, const double* __restrict__ f1d,
                                                         SepZFamilies fam, const double* __restrict__ beta, int R,
@@ -359,10 +366,11 @@ __device__ __forceinline__ void sz_load_tab(const uint16_t* __restrict__ tab, in
 // Phase 1 column windows of one row factor, formed once for every spatial
 // term: block b + 1, then block b + 2 (lane groups 0, 1) or block b (groups
 // 2, 3).
-__device__ __forceinline__ void sz_phase1_windows(const uint32_t (&Uh)[2 * SZ_RB], const uint32_t (&Ul)[2 * SZ_RB],
-                                                  uint4 (&w1h)[SZ_OB / 2], uint4 (&w1l)[SZ_OB / 2]) {
+template <int OB>
+__device__ __forceinline__ void sz_phase1_windows(const uint32_t (&Uh)[OB + 4], const uint32_t (&Ul)[OB + 4],
+                                                  uint4 (&w1h)[OB / 2], uint4 (&w1l)[OB / 2]) {
 #pragma unroll
-    for (int b = 0; b < SZ_OB / 2; ++b) {
+    for (int b = 0; b < OB / 2; ++b) {
         w1h[b] = make_uint4(Uh[2 * b + 2], Uh[2 * b + 3], sz_sel_low(Uh[2 * b + 4], Uh[2 * b]),
                             sz_sel_low(Uh[2 * b + 5], Uh[2 * b + 1]));
         w1l[b] = make_uint4(Ul[2 * b + 2], Ul[2 * b + 3], sz_sel_low(Ul[2 * b + 4], Ul[2 * b]),
@@ -376,12 +384,12 @@ __device__ __forceinline__ void sz_phase1_windows(const uint32_t (&Uh)[2 * SZ_RB
 // rows 16 b + 8.., phase 1, window block b + 1, then block b + 2 in lane
 // groups 0, 1 or block b in groups 2, 3).  Uh / Ul: the lane's row responses,
 // two packed registers per 16-row block; za: the fragments [phase][hi/lo].
-template <bool FP16, int NT>
-__device__ __forceinline__ void sz_colpass(sz_f4 (&Z)[SZ_OB], const uint32_t (&Uh)[2 * SZ_RB],
-                                           const uint32_t (&Ul)[2 * SZ_RB], const uint4 (&W1h)[SZ_OB / 2],
-                                           const uint4 (&W1l)[SZ_OB / 2], const uint4 (&za)[2][2]) {
+template <bool FP16, int NT, int OB>
+__device__ __forceinline__ void sz_colpass(sz_f4 (&Z)[OB], const uint32_t (&Uh)[OB + 4],
+                                           const uint32_t (&Ul)[OB + 4], const uint4 (&W1h)[OB / 2],
+                                           const uint4 (&W1l)[OB / 2], const uint4 (&za)[2][2]) {
 #pragma unroll
-    for (int b = 0; b < SZ_OB / 2; ++b) {
+    for (int b = 0; b < OB / 2; ++b) {
         const uint4 w0h = make_uint4(Uh[2 * b], Uh[2 * b + 1], Uh[2 * b + 2], Uh[2 * b + 3]);
         const uint4 w0l = make_uint4(Ul[2 * b], Ul[2 * b + 1], Ul[2 * b + 2], Ul[2 * b + 3]);
         const uint4 w1h = W1h[b], w1l = W1l[b];
@@ -404,12 +412,13 @@ __device__ __forceinline__ void sz_colpass(sz_f4 (&Z)[SZ_OB], const uint32_t (&U
 // column offset (clamped into the image) is formed once per tile; no load is
 // conditional, so all of them are in flight together.  Samples outside the
 // image or past the halo are masked when they are stored.
-constexpr int SZ_SROWS = SZ_XR / SZ_NW;   // staged rows per wave
-
 // The samples of tile t this lane stages.
-__device__ __forceinline__ void sz_load_tile(const SepZArgs& a, int t, int w, int lane, float (&sv)[SZ_SROWS][2]) {
+template <int OB, int SP>
+__device__ __forceinline__ void sz_load_tile(const SepZArgs& a, int t, int w, int lane,
+                                             float (&sv)[SzTile<OB, SP>::SROWS][2]) {
+    typedef SzTile<OB, SP> S;
     const int h = a.h;
-    const int X0 = (t % a.tiles_x) * SZ_TW, Y0 = a.y_begin + (t / a.tiles_x) * SZ_TH;
+    const int X0 = (t % a.tiles_x) * SZ_TW, Y0 = a.y_begin + (t / a.tiles_x) * S::TH;
     // the per-lane offsets are formed anew for every tile rather than kept in
     // registers across the tile loop
     asm volatile("" : "+v"(lane));
@@ -417,8 +426,8 @@ __device__ __forceinline__ void sz_load_tile(const SepZArgs& a, int t, int w, in
 #pragma unroll
     for (int e = 0; e < 2; ++e) xb[e] = 4u * (uint32_t)min(max(X0 - h + 2 * min(lane, SZ_XC / 2 - 1) + e, 0), a.W - 1);
 #pragma unroll
-    for (int k = 0; k < SZ_SROWS; ++k) {
-        const int gy = Y0 - h + w + SZ_NW * k;
+    for (int k = 0; k < S::SROWS; ++k) {
+        const int gy = Y0 - h + w + S::NW * k;
         const char* row = reinterpret_cast<const char*>(a.X + (size_t)min(max(gy, 0), a.H - 1) * a.W);
 #pragma unroll
         for (int e = 0; e < 2; ++e) sv[k][e] = *reinterpret_cast<const float*>(row + xb[e]);
@@ -428,15 +437,16 @@ __device__ __forceinline__ void sz_load_tile(const SepZArgs& a, int t, int w, in
 // The staged samples of tile t as (R - s) xscale split into hi / lo rows of the
 // staged tile, with R = 0 outside the image; 0 past the halo (zero taps meet
 // it).
-template <bool FP16>
+template <bool FP16, int OB, int SP>
 __device__ __forceinline__ void sz_store_tile(const SepZArgs& a, int t, int w, int lane,
-                                              const float (&sv)[SZ_SROWS][2], uint16_t* xs) {
+                                              const float (&sv)[SzTile<OB, SP>::SROWS][2], uint16_t* xs) {
+    typedef SzTile<OB, SP> S;
     if (lane >= SZ_XC / 2) return;
     const float xscale = FP16 ? 0.25f : 1.f;
     const float pscaled = a.ped * xscale;
     const int h = a.h;
-    const int X0 = (t % a.tiles_x) * SZ_TW, Y0 = a.y_begin + (t / a.tiles_x) * SZ_TH;
-    const int RA = SZ_TH + 2 * h, CA = SZ_TW + 2 * h;
+    const int X0 = (t % a.tiles_x) * SZ_TW, Y0 = a.y_begin + (t / a.tiles_x) * S::TH;
+    const int RA = S::TH + 2 * h, CA = SZ_TW + 2 * h;
     asm volatile("" : "+v"(lane));
     const int c = 2 * lane;
     bool cin[2], cimg[2];
@@ -447,8 +457,8 @@ __device__ __forceinline__ void sz_store_tile(const SepZArgs& a, int t, int w, i
     }
     uint16_t* dst = xs + w * SZ_P + c;
 #pragma unroll
-    for (int k = 0; k < SZ_SROWS; ++k) {
-        const int r = w + SZ_NW * k, gy = Y0 - h + r;
+    for (int k = 0; k < S::SROWS; ++k) {
+        const int r = w + S::NW * k, gy = Y0 - h + r;
         const bool rin = r < RA, rimg = gy >= 0 && gy < a.H;
         float v[2];
 #pragma unroll
@@ -458,8 +468,8 @@ __device__ __forceinline__ void sz_store_tile(const SepZArgs& a, int t, int w, i
         }
         uint32_t hi2, lo2;
         sz_split2<FP16>(v[0], v[1], hi2, lo2);
-        *reinterpret_cast<uint32_t*>(dst + SZ_NW * k * SZ_P) = hi2;
-        *reinterpret_cast<uint32_t*>(dst + (SZ_XR + SZ_NW * k) * SZ_P) = lo2;
+        *reinterpret_cast<uint32_t*>(dst + S::NW * k * SZ_P) = hi2;
+        *reinterpret_cast<uint32_t*>(dst + (S::XR + S::NW * k) * SZ_P) = lo2;
     }
 }
 
@@ -467,10 +477,11 @@ __device__ __forceinline__ void sz_store_tile(const SepZArgs& a, int t, int w, i
 // the grid) in the XCD-aware order; each wave requests its rows of the next
 // tile once the current tile's epilogue is issued, and they are staged after
 // the barrier that ends the current tile.
-template <bool FP16, int NT, int MP>
-__global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs a) {
+template <bool FP16, int NT, int MP, int OB, int SP>
+__global__ __launch_bounds__(SZ_NT * SP, (SzTile<OB, SP>::MINW)) void contract_sepz_kernel(SepZArgs a) {
+    typedef SzTile<OB, SP> S;
     extern __shared__ uint4 sz_lds[];
-    uint16_t* xs = reinterpret_cast<uint16_t*>(sz_lds);   // [2][SZ_XR][SZ_P]
+    uint16_t* xs = reinterpret_cast<uint16_t*>(sz_lds);   // [2][S::XR][SZ_P]
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int g4 = lane >> 4, j16 = lane & 15;
@@ -480,10 +491,12 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
     const int off1 = g4 == 0 ? 32 : 8 * g4;
     // this lane's staged row in block 0 at the strip start, as an LDS-space
     // pointer so that the row loads stay LDS loads through the asm barrier below
-    const lds_u16 xrow = (lds_u16)(xs + j16 * SZ_P + 16 * w);
-    // this wave's area for the second factor's row responses: [SZ_RB][64 lanes] uint4
-    uint4* ubw = sz_lds + SZ_XLDS / 16 + (size_t)w * SZ_RB * 64 + lane;
-    const int n_pairs = (a.R + 1) / 2;
+    const int strip = SP > 1 ? w & (SZ_NW - 1) : w, share = SP > 1 ? w / SZ_NW : 0;
+    const lds_u16 xrow = (lds_u16)(xs + j16 * SZ_P + 16 * strip);
+    // this wave's area for the second factor's row responses: [S::RB][64 lanes] uint4
+    uint4* ubw = sz_lds + S::XLDS / 16 + (size_t)w * S::RB * 64 + lane;
+    // the pairs of row factors this wave takes: pp_first, pp_first + SP, ...
+    const int n_pairs = (a.R + 1) / 2, pp_first = SP > 1 ? __builtin_amdgcn_readfirstlane(share) : 0;
 
     // The tap tables are read one stage ahead: a stage is the row pass of a
     // pair of row factors or the column passes of one row factor for one pair
@@ -492,7 +505,7 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
     // own), so its latency overlaps their execution (the tables are read from
     // L2).  The stage after a tile's last is the first one of the next tile.
     uint4 cur[2][2], nxt[2][2];
-    sz_load_tab(a.rtab, lane, cur);
+    sz_load_tab(a.rtab + (size_t)min(pp_first, n_pairs - 1) * SZ_FRAG, lane, cur);
 
     // the per-call epilogue constants in LDS: zinv (zero for m >= M) and the
     // pedestal sums gamma_m as float32
@@ -504,41 +517,41 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
     int it = blockIdx.x;
     if (it < a.n_tiles) {
         const int t = sep_xcd_remap(it, a.n_tiles);
-        float sv[SZ_SROWS][2];
-        sz_load_tile(a, t, ws, lane, sv);
-        sz_store_tile<FP16>(a, t, ws, lane, sv, xs);
+        float sv[S::SROWS][2];
+        sz_load_tile<OB, SP>(a, t, ws, lane, sv);
+        sz_store_tile<FP16, OB, SP>(a, t, ws, lane, sv, xs);
     }
     __syncthreads();
     for (; it < a.n_tiles; it += G) {
         const int t = sep_xcd_remap(it, a.n_tiles);
         const int X0 = (t % a.tiles_x) * SZ_TW;
-        const int Y0 = a.y_begin + (t / a.tiles_x) * SZ_TH;
+        const int Y0 = a.y_begin + (t / a.tiles_x) * S::TH;
         const bool more = it + G < a.n_tiles;
         const int tn = more ? sep_xcd_remap(it + G, a.n_tiles) : t;
 
-        sz_f4 Z[MP][SZ_OB];
+        sz_f4 Z[MP][OB];
 #pragma unroll
         for (int s = 0; s < MP; ++s)
 #pragma unroll
-            for (int b = 0; b < SZ_OB; ++b) Z[s][b] = sz_f4{0.f, 0.f, 0.f, 0.f};
+            for (int b = 0; b < OB; ++b) Z[s][b] = sz_f4{0.f, 0.f, 0.f, 0.f};
 
-        for (int pp = 0; pp < n_pairs; ++pp) {
+        for (int pp = pp_first; pp < n_pairs; pp += SP) {
             const bool has_b = 2 * pp + 1 < a.R;
             const uint16_t* ztA = a.ztab + (size_t)(2 * pp) * 3 * SZ_FRAG;
             const uint16_t* ztB = ztA + 3 * SZ_FRAG;
             // the entry after the last column stage of this pair: the next pair's
             // row-pass entry (the first one again after the last pair)
-            const uint16_t* rnext = a.rtab + (size_t)(pp + 1 < n_pairs ? pp + 1 : 0) * SZ_FRAG;
+            const uint16_t* rnext = a.rtab + (size_t)(pp + SP < n_pairs ? pp + SP : pp_first) * SZ_FRAG;
             sz_load_tab(ztA, lane, nxt);
             // the staged rows are re-read for every pair rather than held in
             // registers across the loop (they would cost 48 registers per lane)
             lds_u16 xr = xrow;
             asm volatile("" : "+v"(xr));
-            // ---- row pass: two row factors x two 8-column groups, SZ_RB row blocks.
+            // ---- row pass: two row factors x two 8-column groups, S::RB row blocks.
             // The products of row block rb + 1 are issued before the split of
             // block rb, so the vector work of one block overlaps the matrix-core
             // work of the next.
-            uint32_t UAh[2 * SZ_RB], UAl[2 * SZ_RB];
+            uint32_t UAh[2 * S::RB], UAl[2 * S::RB];
             sz_f4 acc[2][2];   // [rb parity][cg]
             auto issue = [&](int rb, sz_f4 (&ac)[2]) {
                 // the second 8-column group reuses the samples of lane groups 1..3
@@ -546,9 +559,9 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
                 const lds_u16 rp = xr + (16 * rb) * SZ_P;
                 uint4 dh[2], dl[2];
                 dh[0] = sz_lds16(rp + 8 * g4);
-                dl[0] = sz_lds16(rp + SZ_XR * SZ_P + 8 * g4);
+                dl[0] = sz_lds16(rp + S::XR * SZ_P + 8 * g4);
                 dh[1] = sz_lds16(rp + off1);
-                dl[1] = sz_lds16(rp + SZ_XR * SZ_P + off1);
+                dl[1] = sz_lds16(rp + S::XR * SZ_P + off1);
 #pragma unroll
                 for (int cg = 0; cg < 2; ++cg) ac[cg] = sz_mfma<FP16>(dh[cg], cur[cg][0], sz_f4{0.f, 0.f, 0.f, 0.f});
                 if (NT >= 2)
@@ -582,17 +595,17 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
             __builtin_amdgcn_s_setprio(1);
             issue(0, acc[0]);
 #pragma unroll
-            for (int rb = 1; rb < SZ_RB; ++rb) {
+            for (int rb = 1; rb < S::RB; ++rb) {
                 issue(rb, acc[rb & 1]);
                 split(rb - 1, acc[(rb - 1) & 1]);
             }
-            split(SZ_RB - 1, acc[(SZ_RB - 1) & 1]);
+            split(S::RB - 1, acc[(S::RB - 1) & 1]);
             __builtin_amdgcn_s_setprio(0);
 
             // ---- column passes: Z[s][ob] += g_{r, 2 mp + s} (x)_y U_r for both factors
             {
-                uint4 w1h[SZ_OB / 2], w1l[SZ_OB / 2];
-                sz_phase1_windows(UAh, UAl, w1h, w1l);
+                uint4 w1h[OB / 2], w1l[OB / 2];
+                sz_phase1_windows<OB>(UAh, UAl, w1h, w1l);
 #pragma unroll
                 for (int mp = 0; mp < MP; ++mp) {
 #pragma unroll
@@ -600,21 +613,21 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
 #pragma unroll
                         for (int hl = 0; hl < 2; ++hl) cur[c][hl] = nxt[c][hl];
                     sz_load_tab(mp + 1 < MP ? ztA + (size_t)(mp + 1) * SZ_FRAG : (has_b ? ztB : rnext), lane, nxt);
-                    sz_colpass<FP16, NT>(Z[mp], UAh, UAl, w1h, w1l, cur);
+                    sz_colpass<FP16, NT, OB>(Z[mp], UAh, UAl, w1h, w1l, cur);
                 }
             }
             if (has_b) {
-                uint32_t UBh[2 * SZ_RB], UBl[2 * SZ_RB];
+                uint32_t UBh[2 * S::RB], UBl[2 * S::RB];
 #pragma unroll
-                for (int rb = 0; rb < SZ_RB; ++rb) {
+                for (int rb = 0; rb < S::RB; ++rb) {
                     const uint4 v = ubw[rb * 64];
                     UBh[2 * rb] = v.x;
                     UBh[2 * rb + 1] = v.y;
                     UBl[2 * rb] = v.z;
                     UBl[2 * rb + 1] = v.w;
                 }
-                uint4 w1h[SZ_OB / 2], w1l[SZ_OB / 2];
-                sz_phase1_windows(UBh, UBl, w1h, w1l);
+                uint4 w1h[OB / 2], w1l[OB / 2];
+                sz_phase1_windows<OB>(UBh, UBl, w1h, w1l);
 #pragma unroll
                 for (int mp = 0; mp < MP; ++mp) {
 #pragma unroll
@@ -622,7 +635,7 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
 #pragma unroll
                         for (int hl = 0; hl < 2; ++hl) cur[c][hl] = nxt[c][hl];
                     sz_load_tab(mp + 1 < MP ? ztB + (size_t)(mp + 1) * SZ_FRAG : rnext, lane, nxt);
-                    sz_colpass<FP16, NT>(Z[mp], UBh, UBl, w1h, w1l, cur);
+                    sz_colpass<FP16, NT, OB>(Z[mp], UBh, UBl, w1h, w1l, cur);
                 }
             }
 #pragma unroll
@@ -635,9 +648,29 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
         // 8 ob + 4 (g4 mod 2) + e of column j16 of its strip.  Lanes g4 and
         // g4 ^ 2 hold the two halves of the same pixels: lane groups 0, 1 finish
         // the first half of the output blocks, groups 2, 3 the second.
-        constexpr int HB = SZ_OB / 2;
+        if constexpr (SP > 1) {
+            // the sums of the SP waves of a strip, added in order by the first
+            // (through the LDS of the staged tile, which every wave is done with)
+            sz_f4* zs = reinterpret_cast<sz_f4*>(sz_lds) + lane;
+            __syncthreads();
+            if (share > 0) {
+#pragma unroll
+                for (int q = 0; q < MP * OB; ++q)
+                    zs[(((share - 1) * SZ_NW + strip) * MP * OB + q) * 64] = Z[q / OB][q % OB];
+            }
+            __syncthreads();
+            if (share == 0) {
+#pragma unroll
+                for (int o = 0; o + 1 < SP; ++o)
+#pragma unroll
+                    for (int q = 0; q < MP * OB; ++q)
+                        Z[q / OB][q % OB] += zs[((o * SZ_NW + strip) * MP * OB + q) * 64];
+            }
+        }
+        if (share == 0) {
+        constexpr int HB = OB / 2;
         const bool lowg = g4 < 2;
-        const int x = X0 + 16 * w + j16;
+        const int x = X0 + 16 * strip + j16;
         // I at the pixels this lane finishes, requested before the vector work
         // below from clamped addresses (values past the image are loaded but
         // never used), so that its latency overlaps it; without I, R stands in
@@ -669,9 +702,9 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
 #pragma unroll
             for (int qq = 0; qq < 3; ++qq) wq[mp][qq] = (q == qq) ? c : 0.f;
         }
-        float part[SZ_OB][4];
+        float part[OB][4];
 #pragma unroll
-        for (int ob = 0; ob < SZ_OB; ++ob)
+        for (int ob = 0; ob < OB; ++ob)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int y = Y0 + 8 * ob + 4 * (g4 & 1) + e;
@@ -716,32 +749,22 @@ __global__ __launch_bounds__(SZ_NT, SZ_MINW) void contract_sepz_kernel(SepZArgs 
                 }
         }
 
+        }
+
         // the next tile's samples (their registers would not fit beside Z);
         // once every wave is done with the staged tile, stage them.  Loads,
         // barrier and stores sit under one branch (`more` is uniform), so the
         // samples are not live across the passes.
         if (more) {
-            float sv[SZ_SROWS][2];
-            sz_load_tile(a, tn, ws, lane, sv);
+            float sv[S::SROWS][2];
+            sz_load_tile<OB, SP>(a, tn, ws, lane, sv);
             __syncthreads();
-            sz_store_tile<FP16>(a, tn, ws, lane, sv, xs);
+            sz_store_tile<FP16, OB, SP>(a, tn, ws, lane, sv, xs);
             __syncthreads();
         } else {
             __syncthreads();
         }
     }
-}
-
-template <bool FP16, int NT>
-static int launch_sepz_p(const SepZArgs& a, int grid, hipStream_t s) {
-    const int MP = (a.M + 1) / 2;
-    if (MP <= 1)
-        hipLaunchKernelGGL((contract_sepz_kernel<FP16, NT, 1>), dim3(grid), dim3(SZ_NT), SZ_LDS, s, a);
-    else if (MP == 2)
-        hipLaunchKernelGGL((contract_sepz_kernel<FP16, NT, 2>), dim3(grid), dim3(SZ_NT), SZ_LDS, s, a);
-    else
-        hipLaunchKernelGGL((contract_sepz_kernel<FP16, NT, 3>), dim3(grid), dim3(SZ_NT), SZ_LDS, s, a);
-    return hip_status(hipGetLastError(), "contract_sepz_kernel");
 }
 
 // Compute units of the current device (cached per device).
@@ -757,21 +780,54 @@ static int device_cus() {
     return cus[dev];
 }
 
+template <bool FP16, int NT, int MP, int OB, int SP>
+static void launch_sepz_t(SepZArgs a, hipStream_t s) {
+    typedef SzTile<OB, SP> S;
+    a.n_tiles = a.tiles_x * ((a.n_rows + S::TH - 1) / S::TH);
+    // persistent workgroups: as many per compute unit as the registers allow,
+    // each walking its share of the tiles
+    const int slots = (SP > 1 ? 1 : S::MINW) * device_cus();
+    const int grid = a.n_tiles < slots ? a.n_tiles : slots;
+    constexpr size_t sums = SP > 1 ? (size_t)(SP - 1) * SZ_NW * MP * OB * 64 * 16 : 0;
+    constexpr size_t lds = S::LDS > sums ? S::LDS : sums;
+    hipLaunchKernelGGL((contract_sepz_kernel<FP16, NT, MP, OB, SP>), dim3(grid), dim3(SZ_NT * SP), lds, s, a);
+}
+
+// The tile height.  A tile's time is a serial chain of row-factor pairs, so a
+// frame that does not fill the chip with 64-row tiles runs on lower ones: 32
+// rows up to three tiles per CU, 16 rows, with four waves sharing the pairs of
+// each strip, up to one per CU.  Measured (21 x 21, 49 bases, fp16x3, tables
+// included): 512 x 512 32 us in 64 rows, 24.5 in 32, 21.6 in 16, 18.2 with
+// shared pairs; 1024 x 1024 33.1, 31.1, 40.4; 1024 x 1536 42.6, 40.1, 52.3; 1024
+// x 2048 44.7, 49.5, 67.0.
+template <bool FP16, int NT, int MP>
+static void launch_sepz_ob(const SepZArgs& a, hipStream_t s) {
+    const int cus = device_cus();
+    auto tiles = [&](int th) { return (long)a.tiles_x * ((a.n_rows + th - 1) / th); };
+    if (tiles(16) <= cus) launch_sepz_t<FP16, NT, MP, 2, 4>(a, s);
+    else if (tiles(32) <= 3 * cus) launch_sepz_t<FP16, NT, MP, 4, 1>(a, s);
+    else launch_sepz_t<FP16, NT, MP, 8, 1>(a, s);
+}
+
+template <bool FP16, int NT>
+static int launch_sepz_p(const SepZArgs& a, hipStream_t s) {
+    const int MP = (a.M + 1) / 2;
+    if (MP <= 1) launch_sepz_ob<FP16, NT, 1>(a, s);
+    else if (MP == 2) launch_sepz_ob<FP16, NT, 2>(a, s);
+    else launch_sepz_ob<FP16, NT, 3>(a, s);
+    return hip_status(hipGetLastError(), "contract_sepz_kernel");
+}
+
 int launch_contract_sepz(SepZArgs a, int precision, hipStream_t s) {
     if (a.h < 1 || a.h > kSepZMaxHalfWidth)
         return fail(SVCONV_EUNSUPPORTED, "regrouped separable form needs 1 <= half-width <= 12");
     if (a.M > 6) return fail(SVCONV_EUNSUPPORTED, "regrouped separable form needs spatial degree <= 2");
     a.tiles_x = (a.W + SZ_TW - 1) / SZ_TW;
-    a.n_tiles = a.tiles_x * ((a.n_rows + SZ_TH - 1) / SZ_TH);
-    if (a.n_tiles == 0) return SVCONV_OK;
-    // persistent workgroups: SZ_MINW per compute unit (one 4-wave workgroup per
-    // wave slot of a SIMD the registers allow), each walking its share of the tiles
-    const int slots = SZ_MINW * device_cus();
-    const int grid = a.n_tiles < slots ? a.n_tiles : slots;
+    if (a.n_rows <= 0) return SVCONV_OK;
     switch (precision) {
-        case SVCONV_FP16X3: return launch_sepz_p<true, 3>(a, grid, s);
-        case SVCONV_BF16X3: return launch_sepz_p<false, 3>(a, grid, s);
-        case SVCONV_FP16X2: return launch_sepz_p<true, 2>(a, grid, s);
+        case SVCONV_FP16X3: return launch_sepz_p<true, 3>(a, s);
+        case SVCONV_BF16X3: return launch_sepz_p<false, 3>(a, s);
+        case SVCONV_FP16X2: return launch_sepz_p<true, 2>(a, s);
         default: return fail(SVCONV_EUNSUPPORTED, "regrouped separable form needs a split 16-bit precision");
     }
 }

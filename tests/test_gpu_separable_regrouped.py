@@ -170,3 +170,22 @@ def test_rejects_outside_range(svc, what):
         with pytest.raises(SvconvError) as ei:
             plan.forward(R, a)
         assert ei.value.status == EUNSUPPORTED
+
+
+@pytest.mark.parametrize("H,W,h,degrees,d_s", [
+    # 16-row tiles with shared pairs: up to 256 of them; 32-row tiles: up to 768; then 64-row tiles
+    (16, 64, 12, (2, 0), 2), (17, 65, 3, (0,), 0), (4096, 3, 5, (1, 0), 1), (4097, 5, 7, (6, 1), 2),
+    (4111, 64, 1, (3,), 0), (24576, 2, 2, (1,), 1), (24577, 2, 2, (1,), 2)])
+@pytest.mark.parametrize("precision", ["fp16x3", "bf16x3"])
+def test_tile_heights(svc, orc, H, W, h, degrees, d_s, precision):
+    sig = (0.8, 1.6)[:len(degrees)]
+    R = synth.star_field(H, W, max(2, H * W // 2000), seed=H + W)
+    I = synth.star_field(H, W, max(2, H * W // 2000), seed=H + W + 1)
+    a = synth.coefficients(synth.n_basis(degrees), synth.n_spatial(d_s), 0, seed=h)
+    Dref = orc.difference(R, I, h, orc.basis(h, sig, degrees), d_s, a)
+    say("tile heights", (H, W), h, degrees, d_s, precision)
+    D = run_difference(svc, R, I, a, h, sig, degrees, d_s, precision=precision, form=FORM,
+                       pedestal=synth.SKY_LEVEL)
+    mx, _ = err_stats(D, Dref)
+    say("  max %.3e" % mx)
+    assert mx <= TOL_MFMA
