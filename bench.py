@@ -303,9 +303,9 @@ def main():
 
     def roof(key):
         r = results[key]
-        if key[0] == "basis":
+        if key[0] == "basis" and key[1] != "fp32":
             per_px = flops.flops_per_pixel(N, M, k)
-        elif key[0] == "regrouped":
+        elif key[0] in ("basis", "regrouped"):
             per_px = flops.regrouped_flops_per_pixel(M, k)
         elif key[1] == "f64":
             per_px = flops.separable_flops_per_pixel(wl.degrees, M, k)
@@ -318,9 +318,10 @@ def main():
         return per_px, ach
 
     def bound_of(key):
-        # float64 on the vector units: the separable form's passes and the
-        # regrouped form at the FP32 precision
-        return "alu" if key in (("separable", "f64"), ("regrouped", "fp32")) else "mfma"
+        # float64 on the vector units: the separable form's passes, and the
+        # regrouped filters that the basis and regrouped forms take at the FP32
+        # precision
+        return "alu" if key == ("separable", "f64") or key[1] == "fp32" else "mfma"
 
     def summary(key):
         pp, ach = roof(key)

@@ -64,9 +64,8 @@ enum svconv_status {
 /* Arithmetic of the basis contraction (the dominant step); for the
  * SEPARABLE form see below. */
 enum svconv_precision {
-    SVCONV_FP32 = 0,    /* float32 matrix cores (v_mfma_f32_16x16x4_f32); the
-                           regrouped form and delta bases in float64 on the
-                           vector units                                        */
+    SVCONV_FP32 = 0,    /* float32 matrix cores (v_mfma_f32_16x16x4_f32), or
+                           float64 on the vector units (see svconv_form)       */
     SVCONV_BF16 = 1,    /* bf16 inputs, fp32 accumulation, 1 product          */
     SVCONV_FP16 = 2,    /* fp16 inputs, fp32 accumulation, 1 product          */
     SVCONV_BF16X3 = 3,  /* R and B split hi+lo in bf16: hh + lh + hl          */
@@ -97,7 +96,12 @@ enum svconv_precision {
  * to rounding).  BASIS: N basis responses T_n = B_n (x) R, then
  * D = sum_n c_n T_n - I.  REGROUPED: Kt_m = sum_n a[n][m] B_n (built on the
  * device per call), then D = sum_m P_m (Kt_m (x) R) - I, which needs M
- * instead of N filters because P_m depends only on the output pixel. */
+ * instead of N filters because P_m depends only on the output pixel.  At
+ * SVCONV_FP32 the regrouped form runs in float64 on the vector units, and so do
+ * delta bases; the basis form takes the same route where it is faster than N
+ * dense responses in float32 (all but few bases with many spatial terms), and
+ * the separable form on frames too small to fill the chip with its tiles.  D is
+ * the same up to rounding, and never less accurate. */
 enum svconv_form {
     SVCONV_FORM_BASIS = 0,
     SVCONV_FORM_REGROUPED = 1,

@@ -236,6 +236,53 @@ static int finish_plan(svconv_plan* p, svconv_plan** out) {
 
 namespace svc {
 
+// Vector instructions per pixel of the direct float64 contraction (direct.hip):
+// k^2 taps with d_s + 1 products each and their folding over a thread's rows.
+static double direct_count(const svconv_plan* p) {
+    const double J = p->d_s + 1, rows = J <= 4 ? 16 : 8;
+    return (double)p->k * p->k * (J + 1.5 * p->M / rows);
+}
+
+// Whether D of a plan in the basis or the separable form, at a precision that
+// does not ask for 16-bit parts, is contracted directly with regrouped filters
+// in float64: the same D of Eq. 1 (P_m depends on the output pixel only), at
+// least as accurate as either form, where that is faster.
+//
+// Basis form: the dense float32 product takes 0.5 matrix-core cycles per tap,
+// pixel and 16 filters (0.25 with at most 8 filters, which pack two rows) and
+// keeps the matrix cores busy for 55 to 60 % of the time, a vector instruction
+// 4.25 / 64 cycles at 72 %.  Measured at 2048 x 4096, 21 x 21, 49 bases, second
+// order: 6.37 ms densely, 0.43 ms directly; 1021 x 1533: 1206 and 94 us; error
+// against float64 3.7e-8 and 2.5e-8 of D.  Few filters on many spatial terms (8
+// at third order) stay dense.
+//
+// Separable form: its float64 kernel has one 64 x 64 tile per CU at a time, so
+// its time is the number of rounds of 256 tiles times one tile's chain; it
+// does less work per pixel, but up to a few hundred tiles the direct kernel is
+// better spread (us, separable and direct, 256 x 256, 700 x 760, 900 x 1000):
+// 21 x 21, 49 bases, second order 58 / 22, 59 / 52, 59 / 68; 15 x 15, 22 bases
+// 30 / 16, 30 / 33, 31 / 43; 31 x 31, third order 96 / 46, 95 / 143, 96 / 179;
+// 31 x 31, first order 76 / 28, 77 / 74, 78 / 90; 21 x 21 at 1024 x 1400, two
+// rounds, 112 / 96.  Both times are modelled on these.
+static bool direct_beats_basis(const svconv_plan* p) {
+    const double dense = (p->N <= 8 ? 0.25 / 0.6 : 0.5 / 0.55 * ((p->N + 15) / 16)) * p->k * p->k;
+    return direct_count(p) * 4.25 / 64 / 0.72 < dense;
+}
+
+static bool direct_beats_separable(const svconv_plan* p) {
+    double fold = 0;   // float64 operations of the folded passes per pixel
+    auto window = [&](int j) { return p->h * (j < 2 ? j : 2) + j * p->h + 1.0; };
+    for (int d : p->degrees) {
+        fold += window(d + 1);
+        for (int i = 0; i <= d; ++i) fold += window(d - i + 1);
+    }
+    fold += p->N * (p->d_s + 4.0);
+    const long tiles = (long)((p->W + 63) / 64) * ((p->H + 63) / 64);
+    const double separable = (double)((tiles + 255) / 256) * (5.0 + 0.042 * fold);
+    const double n = direct_count(p), direct = 12.0 + 0.0125 * n + 2.7e-8 * n * p->H * p->W;
+    return direct < separable;
+}
+
 // Shared body of svconv_forward, svconv_difference, svconv_gn_step and the
 // tile pipeline: enqueue one forward pass on the plan's stream.
 int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, float* out) {
@@ -254,9 +301,8 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
     coords(p, c);
     const bool lowp = is_lowp(p->precision);
     if (p->form == SVCONV_FORM_SEPARABLE_REGROUPED) {
-        const bool split = p->precision == SVCONV_FP16X3 || p->precision == SVCONV_BF16X3 ||
-                           p->precision == SVCONV_FP16X2;
-        if (!split) return fail(SVCONV_EUNSUPPORTED, "regrouped separable form needs a split 16-bit precision");
+        if (p->precision != SVCONV_FP16X3 && p->precision != SVCONV_BF16X3 && p->precision != SVCONV_FP16X2)
+            return fail(SVCONV_EUNSUPPORTED, "regrouped separable form needs a split 16-bit precision");
         if (!p->dSepZRow) return fail(SVCONV_EUNSUPPORTED, "regrouped separable form needs 1 <= half-width <= 12 "
                                                           "and spatial degree <= 2");
         SepZArgs z{};
@@ -283,6 +329,33 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
         int st = launch_sepz_prep(z, a, p->dSep1d, fam, p->dBeta, p->N, h16, p->stream);
         if (st) return st;
         return launch_contract_sepz(z, p->precision, p->stream);
+    }
+    const bool split = p->precision == SVCONV_FP16X3 || p->precision == SVCONV_BF16X3 || p->precision == SVCONV_FP16X2;
+    const bool direct = p->form == SVCONV_FORM_SEPARABLE ? !split && direct_beats_separable(p)
+                        : lowp                           ? false
+                        : p->form == SVCONV_FORM_BASIS   ? p->N <= kMaxFilters && (p->dfb || direct_beats_basis(p))
+                                                         : true;
+    if (direct) {
+        // regrouped in float64 on the vector units.  The responses of a delta
+        // basis are shifted pixels, so its basis form is the same sum anyhow.
+        DirectArgs d{};
+        d.X = R;
+        d.I = I;
+        d.out = out;
+        d.H = p->H;
+        d.W = p->W;
+        d.h = p->h;
+        d.d_s = p->d_s;
+        d.sx = c.sx; d.ox = c.ox; d.sy = c.sy; d.oy = c.oy;
+        if (p->dfb) {
+            d.taps = a;
+        } else {
+            double* taps = reinterpret_cast<double*>(p->dFt32);
+            int st = regroup_filters64(p->dF64, a, p->N, p->M, p->k, taps, p->stream);
+            if (st) return st;
+            d.taps64 = taps;
+        }
+        return launch_contract_direct(d, p->stream);
     }
     if (p->form == SVCONV_FORM_SEPARABLE) {
         SepArgs sa{};
@@ -315,33 +388,11 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
         sa.gammap = p->dSepCoef + (size_t)p->N * kSepCoefPad;
         sa.coefpf = reinterpret_cast<const float*>(p->dSepCoef + (size_t)(p->N + 1) * kSepCoefPad);
         // the split 16-bit precisions take the matrix-core passes, the others float64
-        if (p->precision == SVCONV_FP16X3 || p->precision == SVCONV_BF16X3 || p->precision == SVCONV_FP16X2) {
+        if (split) {
             if (!p->dSepFrag) return fail(SVCONV_EUNSUPPORTED, "separable matrix-core form needs half-width <= 15");
             return launch_contract_sep_mma(sa, p->dSepFrag, p->precision, p->stream);
         }
         return launch_contract_sep(sa, p->stream);
-    }
-    if (!lowp && (p->form == SVCONV_FORM_REGROUPED || (p->dfb && p->N <= kMaxFilters))) {
-        // regrouped in float64 on the vector units.  The responses of a delta
-        // basis are shifted pixels, so its basis form is the same sum.
-        DirectArgs d{};
-        d.X = R;
-        d.I = I;
-        d.out = out;
-        d.H = p->H;
-        d.W = p->W;
-        d.h = p->h;
-        d.d_s = p->d_s;
-        d.sx = c.sx; d.ox = c.ox; d.sy = c.sy; d.oy = c.oy;
-        if (p->dfb) {
-            d.taps = a;
-        } else {
-            double* taps = reinterpret_cast<double*>(p->dFt32);
-            int st = regroup_filters64(p->dF64, a, p->N, p->M, p->k, taps, p->stream);
-            if (st) return st;
-            d.taps64 = taps;
-        }
-        return launch_contract_direct(d, p->stream);
     }
     if (p->form == SVCONV_FORM_BASIS) {
         if (p->N > kMaxFilters) return fail(SVCONV_EUNSUPPORTED, "basis form needs N <= 64");
@@ -588,12 +639,11 @@ static int run_adjoint_a(svconv_plan* p, const float* R, const float* gD, double
 // 517 x 771, 21 x 21, second order: 357 and 24 us), so the counts decide; few
 // bases on a wide kernel (10 at 31 x 31) stay with the factors.
 static bool adjoint_r_direct(const svconv_plan* p) {
-    const double k = p->k, J = p->d_s + 1, halo = 1.0 + p->h / 32.0;
+    const double k = p->k, halo = 1.0 + p->h / 32.0;
     int factors = 0;
     for (int d : p->degrees) factors += d + 1;
-    const double sep = p->N * (halo * halo * (30 + 2 * J) + 1.1 * halo * k) + factors * (k + 10.0);
-    const double rows = J <= 4 ? 16 : 8;
-    return k * k * (J + (1.5 * p->M) / rows) < sep;
+    const double sep = p->N * (halo * halo * (32 + 2 * p->d_s) + 1.1 * halo * k) + factors * (k + 10.0);
+    return direct_count(p) < sep;
 }
 
 int svconv_backward(svconv_plan* p, const float* R, const float* a, const float* gD, float* gR,
