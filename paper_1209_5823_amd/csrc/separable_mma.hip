@@ -115,15 +115,6 @@ __device__ __forceinline__ float smm_row16_sum(float v) {
     return v;
 }
 
-// bf16 hi by truncation (the low 16 bits of the float32 cleared), lo the
-// remainder x - hi (exact in float32) rounded to nearest even: 2^-16 |x|, as
-// the rounded split, at fewer instructions.
-__device__ __forceinline__ void smm_split_bft(float x, uint32_t& hi, uint32_t& lo) {
-    const uint32_t u = __float_as_uint(x) & 0xffff0000u;
-    hi = u >> 16;
-    lo = smm_f2bf(x - __uint_as_float(u));
-}
-
 template <bool FP16>
 __device__ __forceinline__ smm_f4 smm_mfma(const uint4& a, const uint4& b, smm_f4 c) {
     if constexpr (FP16) {
@@ -592,20 +583,32 @@ int launch_adjoint_a_sep_mma(SepArgs a, const uint16_t* frag, int precision, con
 // row factor i in the matrix-core accumulators (4 x 6 blocks, 3 per wave); then
 // CE_i is split row-major into LDS and the row pass dR += f_i (x)_x CE_i
 // accumulates over all rounds (4 x 4 blocks, 2 per wave).  bf16 keeps the
-// float32 range of c_n G (hi by truncation, lo rounded); three products per
-// pass as in the forward.
-constexpr int SA_NI = 9;                  // E entries per thread and basis, as row pairs
-static_assert(SM_XR * (SM_XR / 2) == SA_NI * SM_NT, "E row pairs must spread evenly over the threads");
-constexpr int SA_CYP = 8;                 // Cy entries per staged column (spatial degree <= 7)
-constexpr size_t SA_LDS = SM_LDS + (size_t)SM_XR * SA_CYP * sizeof(float);   // 78 KB: two workgroups per CU
-static_assert(kMaxSpatialDegree + 1 <= SA_CYP, "Cy table too narrow");
+// float32 range of c_n G (hi and lo rounded to nearest even); three products
+// per pass as in the forward.
+//
+// Bound: the vector work of forming E_n, once per basis on (64 + 2h)^2 samples.
+// A thread keeps three columns and three row pairs, so c_n's coefficients in yh
+// take 10 FMAs per column (third order), yh is held, and a sample costs its Horner steps, one
+// product and half a packed split.  (Nine row pairs in nine columns per thread
+// took the coefficients from a table in LDS, with a barrier of its own, and
+// formed indices, yh and the bf16 roundings by integer arithmetic: 2048 x 2048,
+// 31 x 31, third order 311 -> ADJRUS us.)
+constexpr int SA_NC = 3, SA_NP = 3;       // columns and row pairs per thread
+static_assert(SM_XR == 32 * SA_NC && SM_XR / 2 == 16 * SA_NP && SM_NW == 8, "E entries must spread evenly over the threads");
+constexpr size_t SA_LDS = SM_LDS;         // 77 KB: two workgroups per CU
+
+// Two float32 values rounded to bf16 (nearest even), packed
+__device__ __forceinline__ uint32_t smm_pk_bf16(float x0, float x1) {
+    uint32_t r;
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(x0), "v"(x1));
+    return r;
+}
 
 template <int DSM>
 __global__ __launch_bounds__(SM_NT, SM_MINW) void adjoint_r_sepmm_kernel(SepArgs a, const uint16_t* __restrict__ frag) {
     extern __shared__ uint4 smm_lds[];
     uint16_t* et = reinterpret_cast<uint16_t*>(smm_lds);   // [2][SM_XR columns][SM_P]: E_n, rows contiguous
     uint16_t* ce = et + 2 * SM_XR * SM_P;                    // [2][64 rows][SM_P]: CE_i, columns contiguous
-    float* cyt = reinterpret_cast<float*>(ce + 2 * 64 * SM_P);  // [SM_XR][SA_CYP]: Cy of the basis per column
 
     const int h = a.h;
     const int CA = 64 + 2 * h;
@@ -625,29 +628,34 @@ __global__ __launch_bounds__(SM_NT, SM_MINW) void adjoint_r_sepmm_kernel(SepArgs
         *reinterpret_cast<uint4*>(et + (q >> 1) * SM_P + SM_XR + 8 * (q & 1)) = make_uint4(0u, 0u, 0u, 0u);
     for (int q = tid; q < 2 * 64 * 2; q += SM_NT)
         *reinterpret_cast<uint4*>(ce + (q >> 1) * SM_P + SM_XR + 8 * (q & 1)) = make_uint4(0u, 0u, 0u, 0u);
-    // G on the staged region (row pairs q = tid + k SM_NT: column q / 48, rows
-    // 2 (q mod 48) + 0, 1); zero outside the image and past the halo
-    float gv[SA_NI][2];
+    // this thread's staged columns xq = 32 c + w + 8 g4 and row pairs pr = j16 + 16 s:
+    // xh, yh and G there; G is zero outside the image and past the halo (loaded
+    // from clamped addresses so that no load is conditional, masked after)
+    float gv[SA_NC][SA_NP][2], xh[SA_NC], yh[SA_NP][2];
 #pragma unroll
-    for (int k = 0; k < SA_NI; ++k) {
-        const int q = tid + k * SM_NT, xq = q / (SM_XR / 2), pr = q - xq * (SM_XR / 2);
+    for (int c = 0; c < SA_NC; ++c) {
+        const int gx = X0 - h + 32 * c + w + 8 * g4;
+        xh[c] = fmaf(sxf, (float)gx, oxf);
+#pragma unroll
+        for (int s = 0; s < SA_NP; ++s)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int gy = Y0 - h + 2 * (j16 + 16 * s) + e;
+                gv[c][s][e] = a.X[(size_t)min(max(gy, 0), a.H - 1) * a.W + min(max(gx, 0), a.W - 1)];
+            }
+    }
+#pragma unroll
+    for (int s = 0; s < SA_NP; ++s)
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            const int yq = 2 * pr + e, gx = X0 - h + xq, gy = Y0 - h + yq;
-            gv[k][e] = a.X[(size_t)min(max(gy, 0), a.H - 1) * a.W + min(max(gx, 0), a.W - 1)];
-        }
-    }
-    // (loaded from clamped addresses above so that no load is conditional;
-    // masked here)
+            const int yq = 2 * (j16 + 16 * s) + e, gy = Y0 - h + yq;
+            yh[s][e] = fmaf(syf, (float)gy, oyf);
 #pragma unroll
-    for (int k = 0; k < SA_NI; ++k) {
-        const int q = tid + k * SM_NT, xq = q / (SM_XR / 2), pr = q - xq * (SM_XR / 2);
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int yq = 2 * pr + e, gx = X0 - h + xq, gy = Y0 - h + yq;
-            if (!(xq < CA && yq < CA && gx >= 0 && gx < a.W && gy >= 0 && gy < a.H)) gv[k][e] = 0.f;
+            for (int c = 0; c < SA_NC; ++c) {
+                const int xq = 32 * c + w + 8 * g4, gx = X0 - h + xq;
+                if (!(xq < CA && yq < CA && gx >= 0 && gx < a.W && gy >= 0 && gy < a.H)) gv[c][s][e] = 0.f;
+            }
         }
-    }
     smm_f4 accR[2];   // dR blocks w and w + 8 of the 4 x 4 output blocks
 #pragma unroll
     for (int k = 0; k < 2; ++k) accR[k] = smm_f4{0.f, 0.f, 0.f, 0.f};
@@ -662,47 +670,49 @@ __global__ __launch_bounds__(SM_NT, SM_MINW) void adjoint_r_sepmm_kernel(SepArgs
             for (int j = 0; j + i <= deg; ++j) {
                 const int n = base + (i + j) * (i + j + 1) / 2 + j;
                 const float sgn = (j & 1) ? -1.f : 1.f;
-                __syncthreads();   // previous basis' E and Cy consumed
-                // c_n(x, y) = sum_q Cy[q](x) yh^q with Cy[q] = sum_{t >= q} c[t (t + 1) / 2 + q] xh^(t - q)
-                // (the monomial x^(t-q) y^q), per staged column into LDS
-                {
-                    const cptr<float> cn_ = coefpf + (size_t)n * kSepCoefPad;
-                    for (int e = tid; e < SM_XR * (DSM + 1); e += SM_NT) {
-                        const int xq = e / (DSM + 1), qq = e - xq * (DSM + 1);
-                        const float xh = fmaf(sxf, (float)(X0 - h + xq), oxf);
-                        float cy = 0.f;
-                        for (int tt = DSM; tt >= qq; --tt) cy = fmaf(cy, xh, cn_[tt * (tt + 1) / 2 + qq]);
-                        cyt[xq * SA_CYP + qq] = cy;
+                // (-1)^j c_n(x, y) = sum_q Cy[q](x) yh^q with Cy[q] = sum_{t >= q} c[t (t + 1) / 2 + q] xh^(t - q)
+                // (the monomial x^(t-q) y^q)
+                float cy[SA_NC][DSM + 1];
+                const cptr<float> cn_ = coefpf + (size_t)n * kSepCoefPad;
+#pragma unroll
+                for (int c = 0; c < SA_NC; ++c)
+#pragma unroll
+                    for (int qq = 0; qq <= DSM; ++qq) {
+                        float v = 0.f;
+#pragma unroll
+                        for (int tt = DSM; tt >= qq; --tt) v = fmaf(v, xh[c], cn_[tt * (tt + 1) / 2 + qq]);
+                        cy[c][qq] = sgn * v;
                     }
-                }
-                __syncthreads();
+                __syncthreads();   // previous basis' E consumed
                 // E_n = (-1)^j c_n G
 #pragma unroll
-                for (int k = 0; k < SA_NI; ++k) {
-                    const int q = tid + k * SM_NT, xq = q / (SM_XR / 2), pr = q - xq * (SM_XR / 2);
-                    float cy[DSM + 1];
+                for (int c = 0; c < SA_NC; ++c) {
+                    uint16_t* dst = et + (32 * c + w + 8 * g4) * SM_P + 2 * j16;
 #pragma unroll
-                    for (int qq = 0; qq <= DSM; ++qq) cy[qq] = cyt[xq * SA_CYP + qq];
-                    float v[2];
+                    for (int s = 0; s < SA_NP; ++s) {
+                        float v[2];
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const float yh = fmaf(syf, (float)(Y0 - h + 2 * pr + e), oyf);
-                        float cn = cy[DSM];
+                        for (int e = 0; e < 2; ++e) {
+                            float cn = cy[c][DSM];
 #pragma unroll
-                        for (int qq = DSM - 1; qq >= 0; --qq) cn = fmaf(cn, yh, cy[qq]);
-                        v[e] = sgn * cn * gv[k][e];
+                            for (int qq = DSM - 1; qq >= 0; --qq) cn = fmaf(cn, yh[s][e], cy[c][qq]);
+                            v[e] = cn * gv[c][s][e];
+                        }
+                        const uint32_t hi = smm_pk_bf16(v[0], v[1]);
+                        const uint32_t lo = smm_pk_bf16(v[0] - __uint_as_float(hi << 16),
+                                                        v[1] - __uint_as_float(hi & 0xffff0000u));
+                        *reinterpret_cast<uint32_t*>(dst + 32 * s) = hi;
+                        *reinterpret_cast<uint32_t*>(dst + SM_XR * SM_P + 32 * s) = lo;
                     }
-                    uint32_t h0, l0, h1, l1;
-                    smm_split_bft(v[0], h0, l0);
-                    smm_split_bft(v[1], h1, l1);
-                    *reinterpret_cast<uint32_t*>(et + xq * SM_P + 2 * pr) = h0 | (h1 << 16);
-                    *reinterpret_cast<uint32_t*>(et + (SM_XR + xq) * SM_P + 2 * pr) = l0 | (l1 << 16);
                 }
+                // the taps are requested before the barrier, so that their latency
+                // passes while the other waves finish E
+                uint4 tf[2][2];
+                smm_load_frag(fg + (size_t)j * SM_FRAG, lane, tf);
+                __builtin_amdgcn_sched_barrier(0);
                 __syncthreads();
                 // column pass: block (rb, cb) = (blk mod 4, blk / 4), A = taps of f_j,
                 // B = E at columns 16 cb + (lane mod 16), rows 16 rb + [0, 64)
-                uint4 tf[2][2];
-                smm_load_frag(fg + (size_t)j * SM_FRAG, lane, tf);
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     uint4 eh[SM_IB], el[SM_IB];
@@ -731,8 +741,9 @@ __global__ __launch_bounds__(SM_NT, SM_MINW) void adjoint_r_sepmm_kernel(SepArgs
                     const int blk = w + k * SM_NW, rb = blk & 3, cb = blk >> 2;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        uint32_t hi, lo;
-                        smm_split_bft(sgi * accC[k][e], hi, lo);
+                        const float v = sgi * accC[k][e];
+                        const uint32_t hi = smm_pk_bf16(v, v);
+                        const uint32_t lo = smm_pk_bf16(v - __uint_as_float(hi << 16), 0.f);
                         const int off = (16 * rb + 4 * g4 + e) * SM_P + 16 * cb + j16;
                         ce[off] = (uint16_t)hi;
                         ce[64 * SM_P + off] = (uint16_t)lo;
