@@ -79,10 +79,19 @@ __device__ __forceinline__ void smm_split(float x, uint32_t& hi, uint32_t& lo) {
     }
 }
 
+// Two float32 values rounded to bf16 (nearest even), packed
+__device__ __forceinline__ uint32_t smm_pk_bf16(float x0, float x1) {
+    // by conversion, not inline asm: the compiler must see the read of a
+    // matrix-core result to put the wait states before it
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{x0, x1}), b2));
+}
+
 // Two values split into packed hi and lo parts.  fp16: hi by the packed
 // truncating conversion, lo the remainder x - hi (exact in float32) rounded to
 // nearest even by one mixed-precision FMA per value (into the low, then the
-// high half); bf16: rounded to nearest even one at a time.
+// high half); bf16: both parts rounded to nearest even by the packed conversion.
 template <bool FP16>
 __device__ __forceinline__ void smm_split2(float x0, float x1, uint32_t& hi2, uint32_t& lo2) {
     if (FP16) {
@@ -92,11 +101,8 @@ __device__ __forceinline__ void smm_split2(float x0, float x1, uint32_t& hi2, ui
         asm("v_fma_mixhi_f16 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(lo) : "v"(hi2), "v"(x1));
         lo2 = lo;
     } else {
-        uint32_t h0, l0, h1, l1;
-        smm_split<false>(x0, h0, l0);
-        smm_split<false>(x1, h1, l1);
-        hi2 = h0 | (h1 << 16);
-        lo2 = l0 | (l1 << 16);
+        hi2 = smm_pk_bf16(x0, x1);
+        lo2 = smm_pk_bf16(x0 - __uint_as_float(hi2 << 16), x1 - __uint_as_float(hi2 & 0xffff0000u));
     }
 }
 
@@ -592,17 +598,10 @@ int launch_adjoint_a_sep_mma(SepArgs a, const uint16_t* frag, int precision, con
 // product and half a packed split.  (Nine row pairs in nine columns per thread
 // took the coefficients from a table in LDS, with a barrier of its own, and
 // formed indices, yh and the bf16 roundings by integer arithmetic: 2048 x 2048,
-// 31 x 31, third order 311 -> ADJRUS us.)
+// 31 x 31, third order 311 -> 272 us.)
 constexpr int SA_NC = 3, SA_NP = 3;       // columns and row pairs per thread
 static_assert(SM_XR == 32 * SA_NC && SM_XR / 2 == 16 * SA_NP && SM_NW == 8, "E entries must spread evenly over the threads");
 constexpr size_t SA_LDS = SM_LDS;         // 77 KB: two workgroups per CU
-
-// Two float32 values rounded to bf16 (nearest even), packed
-__device__ __forceinline__ uint32_t smm_pk_bf16(float x0, float x1) {
-    uint32_t r;
-    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(x0), "v"(x1));
-    return r;
-}
 
 template <int DSM>
 __global__ __launch_bounds__(SM_NT, SM_MINW) void adjoint_r_sepmm_kernel(SepArgs a, const uint16_t* __restrict__ frag) {
