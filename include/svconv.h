@@ -88,8 +88,8 @@ enum svconv_precision {
  * filter tap round to nearest even: |x - hi - lo| <= 2^-22 |x| (fp16) or
  * 2^-16 |x| (bf16).  The separable forms take the fp16 hi part of image data
  * and row responses toward zero (one instruction for two values) and round
- * lo to nearest even: |x - hi - lo| < 2^-21 |x|; the adjoint in R truncates
- * the bf16 hi part: < 2^-15 |x|.  The measured errors above include these
+ * lo to nearest even: |x - hi - lo| < 2^-21 |x|.  Their bf16 parts are both
+ * rounded to nearest even.  The measured errors above include these
  * roundings. */
 
 /* How the per-pixel kernel is contracted (both give D of Eq. 1 exactly, up
@@ -128,12 +128,11 @@ enum svconv_form {
  * other precisions, and in the fit entry points (whose steps go through the
  * ill-conditioned normal matrix), the adjoints run in float64 (the adjoint in
  * R directly with regrouped filters where that is less work than the passes
- * through the factors), and the basis
- * responses of the normal matrix always do (the float64 adjoint in a falls
- * back to the dense matrix-core product when its per-round moments do not
- * fit in LDS).  The adjoints in a sum with atomics, so repeated calls agree to
- * float64 rounding rather than bit for bit.  EUNSUPPORTED for delta-basis
- * plans. */
+ * through the factors), and the basis responses of the normal matrix always
+ * do (the float64 adjoint in a falls back to the dense matrix-core product
+ * when its per-round moments do not fit in LDS).  The adjoints in a sum with
+ * atomics, so repeated calls agree to float64 rounding rather than bit for
+ * bit.  EUNSUPPORTED for delta-basis plans. */
 
 /* SEPARABLE_REGROUPED (Gaussian bases, 1 <= half_width <= 12, spatial
  * degree <= 2, precision SVCONV_FP16X3, SVCONV_BF16X3 or SVCONV_FP16X2; other

@@ -7,7 +7,8 @@
 //   T_f(p) = sum_{dv,du} F_f[dv][du] * X(p + (du - h, dv - h)),
 //
 // with w_f(p) = sum_m coef[f][m] P_m(p) (basis form, Eq. 2 - Eq. 3) or
-// w_f(p) = P_f(p) (regrouped form and the adjoint in R).  The T_f of a tile
+// w_f(p) = P_f(p) (regrouped form and the adjoint in R).  In the kernel below
+// (basis form, and the basis responses of the normal matrix) the T_f of a tile
 // of output pixels are a dense product (filters x taps) . (taps x pixels) run
 // on the matrix cores; the patch matrix is never stored: its columns are read
 // straight out of an LDS copy of the input tile plus its halo.
@@ -28,14 +29,6 @@ __device__ __forceinline__ int xcd_remap(int bid, int n) {
     const int x = bid & 7, t = bid >> 3;
     const int q = n >> 3, r = n & 7;
     return x * q + (x < r ? x : r) + t;
-}
-
-__device__ __forceinline__ double ipow_d(double x, int e) {
-    double r = 1.0;
-#pragma unroll
-    for (int t = 0; t < kMaxSpatialDegree; ++t)
-        if (t < e) r *= x;
-    return r;
 }
 
 // Exponents (i, j) of spatial term m: t = 0..d, i = t..0, j = t - i.
@@ -121,7 +114,7 @@ int build_f32_fragments(const float* F, int NF, int k, float* frag, hipStream_t 
 
 // ------------------------------------------------ FP32 contraction ----
 
-template <int NB, int TH, bool REG, bool PACK>
+template <int NB, int TH, bool PACK>
 __global__ __launch_bounds__(256, 2) void contract_f32_kernel(ContractArgs a,
                                                            const float* __restrict__ frag, int k,
                                                            int n_rg, int rows, int cols,
@@ -143,7 +136,7 @@ __global__ __launch_bounds__(256, 2) void contract_f32_kernel(ContractArgs a,
     const int h = a.h;
 
     const bool want_d = (a.out != nullptr);   // false: only the T_f planes are written
-    if (!REG && want_d)
+    if (want_d)
         for (int q = tid; q < a.NF * a.M; q += 256) coef_s[q] = a.coef[q];
 
     // Stage X[Y0-h .. Y0-h+rows) x [X0-h .. X0-h+cols) minus the pedestal;
@@ -314,26 +307,13 @@ __global__ __launch_bounds__(256, 2) void contract_f32_kernel(ContractArgs a,
 #pragma unroll
     for (int q = 1; q <= kMaxSpatialDegree; ++q) xp[q] = xp[q - 1] * xh;
 
-    // Per-filter terms of this lane's accumulator entries, formed once per
-    // tile: ped * beta_f (loaded together from clamped indices) and, in the
-    // regrouped form, the x power of monomial f and the exponent of its y power.
-    double pbf[NB][4], wxf[NB][4];
-    int jyf[NB][4];
+    // ped * beta_f of this lane's accumulator entries, formed once per tile
+    // (loaded together from clamped indices)
+    double pbf[NB][4];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int f = 16 * b + fo + e;
-            pbf[b][e] = 0.0;
-            wxf[b][e] = 0.0;
-            jyf[b][e] = 0;
-            if (REG && want_d) {
-                int ii, jj;
-                term_exponents(f < a.NF ? f : 0, ii, jj);
-                wxf[b][e] = ipow_d(xh, ii);
-                jyf[b][e] = jj;
-            }
-        }
+        for (int e = 0; e < 4; ++e) pbf[b][e] = 0.0;
     if (a.beta != nullptr) {
 #pragma unroll
         for (int b = 0; b < NB; ++b)
@@ -352,8 +332,6 @@ __global__ __launch_bounds__(256, 2) void contract_f32_kernel(ContractArgs a,
         yp[0] = 1.0;
 #pragma unroll
         for (int q = 1; q <= kMaxSpatialDegree; ++q) yp[q] = yp[q - 1] * yh;
-        // yh^j for j <= 7 from its binary digits, without branches
-        const double yh2 = yh * yh, yh4 = yh2 * yh2;
         double part = 0.0;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
@@ -362,12 +340,7 @@ __global__ __launch_bounds__(256, 2) void contract_f32_kernel(ContractArgs a,
                 const int f = 16 * b + fo + e;
                 if (f < a.NF) {
                     double wgt = 0.0;
-                    if (!want_d) {
-                    } else if (REG) {
-                        const int jj = jyf[b][e];
-                        wgt = wxf[b][e] * (((jj & 1) ? yh : 1.0) * ((jj & 2) ? yh2 : 1.0)) *
-                              ((jj & 4) ? yh4 : 1.0);
-                    } else {
+                    if (want_d) {
                         const float* cf = coef_s + f * a.M;
                         int m = 0;
 #pragma unroll
@@ -393,7 +366,7 @@ __global__ __launch_bounds__(256, 2) void contract_f32_kernel(ContractArgs a,
     }
 }
 
-template <int NB, bool REG, bool PACK = false>
+template <int NB, bool PACK = false>
 static int launch_f32_t(const ContractArgs& a, const float* frag, hipStream_t s) {
     constexpr int TH = f32_tile_h(NB);
     const int k = 2 * a.h + 1;
@@ -403,24 +376,19 @@ static int launch_f32_t(const ContractArgs& a, const float* frag, hipStream_t s)
     const int n_tiles = tiles_x * tiles_y;
     if (n_tiles == 0) return SVCONV_OK;
     if (g.lds_bytes > 64 * 1024) return fail(SVCONV_EUNSUPPORTED, "FP32 tile exceeds 64 KiB of LDS");
-    hipLaunchKernelGGL((contract_f32_kernel<NB, TH, REG, PACK>), dim3(n_tiles), dim3(256),
+    hipLaunchKernelGGL((contract_f32_kernel<NB, TH, PACK>), dim3(n_tiles), dim3(256),
                        g.lds_bytes, s, a, frag, k, g.n_rg, g.lds_rows, g.lds_cols,
                        tiles_x, n_tiles);
     return hip_status(hipGetLastError(), "contract_f32_kernel");
 }
 
 int launch_contract_f32(const ContractArgs& a, const float* frag, int nb, hipStream_t s) {
-    const bool reg = (a.coef == nullptr);
-    if (nb == 1 && f32_packed(a.NF))
-        return reg ? launch_f32_t<1, true, true>(a, frag, s)
-                   : launch_f32_t<1, false, true>(a, frag, s);
+    if (a.coef == nullptr) return fail(SVCONV_EINVAL, "no coefficients");
     switch (nb) {
-        case 1: return reg ? launch_f32_t<1, true>(a, frag, s) : launch_f32_t<1, false>(a, frag, s);
-        case 2: return reg ? launch_f32_t<2, true>(a, frag, s) : launch_f32_t<2, false>(a, frag, s);
-        case 3: return reg ? fail(SVCONV_EUNSUPPORTED, "regrouped form needs M <= 32")
-                           : launch_f32_t<3, false>(a, frag, s);
-        case 4: return reg ? fail(SVCONV_EUNSUPPORTED, "regrouped form needs M <= 32")
-                           : launch_f32_t<4, false>(a, frag, s);
+        case 1: return f32_packed(a.NF) ? launch_f32_t<1, true>(a, frag, s) : launch_f32_t<1>(a, frag, s);
+        case 2: return launch_f32_t<2>(a, frag, s);
+        case 3: return launch_f32_t<3>(a, frag, s);
+        case 4: return launch_f32_t<4>(a, frag, s);
         default: return fail(SVCONV_EUNSUPPORTED, "more than 64 filters");
     }
 }
@@ -465,7 +433,7 @@ int regroup_filters(const double* F64, const double* beta, const float* a, int N
 //   dL/dR(q) = sum_m' P_m'(q) sum_{u,v} H_m'[u][v] G(q + (u,v))
 // with H_(i',j') = sum_{i>=i', j>=j'} C(i,i') C(j,j') (u sx)^(i-i') (v sy)^(j-j') Kt_(i,j):
 // a correlation of G with M filters weighted by P_m'(q), i.e. the same
-// contraction as the regrouped forward.  In correlation orientation
+// contraction as the regrouped forward in float64.  In correlation orientation
 // F'_m'[dv][du] = H_m'[u = du - h][v = dv - h].  The float64 basis table holds
 // F_n[dv][du] = B_n[2h - dv][2h - du], so B_n[u][v] (row v+h, column u+h)
 // = F_n[h - v][h - u].

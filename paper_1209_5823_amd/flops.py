@@ -38,6 +38,13 @@ def regrouped_flops_per_pixel(M, k):
     return 2 * M * k * k + 2 * M + 1
 
 
+def regrouped_folded_flops_per_pixel(d_s, k):
+    """FLOP per pixel of the regrouped form with the taps folded per column: the
+    M taps of a kernel pixel become d_s + 1, one per power of yh, and the folding
+    itself is shared by the pixels of a column."""
+    return 2 * (d_s + 1) * k * k + 2 * (d_s + 1) + 1
+
+
 def executed_flops_per_pixel(n_filters_padded, taps_padded, passes=1):
     """MFMA FLOP actually issued per pixel by a padded contraction."""
     return 2 * n_filters_padded * taps_padded * passes
