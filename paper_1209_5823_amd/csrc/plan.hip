@@ -263,7 +263,11 @@ static double direct_count(const svconv_plan* p) {
 // 21 x 21, 49 bases, second order 58 / 22, 59 / 52, 59 / 68; 15 x 15, 22 bases
 // 30 / 16, 30 / 33, 31 / 43; 31 x 31, third order 96 / 46, 95 / 143, 96 / 179;
 // 31 x 31, first order 76 / 28, 77 / 74, 78 / 90; 21 x 21 at 1024 x 1400, two
-// rounds, 112 / 96.  Both times are modelled on these.
+// rounds, 112 / 96.  Both times are modelled on these.  On frames of many
+// rounds, whose tiles overlap, the two are even at 21 x 21 (2048 x 4096: 437 /
+// 431 in a loop of its own, 480 / 514 right after other kernels, when the
+// higher rate of float64 products lowers the clock), and the model leaves them
+// to the separable kernel.
 static bool direct_beats_basis(const svconv_plan* p) {
     const double dense = (p->N <= 8 ? 0.25 / 0.6 : 0.5 / 0.55 * ((p->N + 15) / 16)) * p->k * p->k;
     return direct_count(p) * 4.25 / 64 / 0.72 < dense;
@@ -278,8 +282,9 @@ static bool direct_beats_separable(const svconv_plan* p) {
     }
     fold += p->N * (p->d_s + 4.0);
     const long tiles = (long)((p->W + 63) / 64) * ((p->H + 63) / 64);
-    const double separable = (double)((tiles + 255) / 256) * (5.0 + 0.042 * fold);
-    const double n = direct_count(p), direct = 12.0 + 0.0125 * n + 2.7e-8 * n * p->H * p->W;
+    const double rounds = (double)((tiles + 255) / 256);
+    const double separable = rounds * (rounds > 2 ? 0.93 : 1.0) * (5.0 + 0.042 * fold);
+    const double n = direct_count(p), direct = 10.0 + 0.006 * n + 3.5e-8 * n * p->H * p->W;
     return direct < separable;
 }
 
