@@ -40,6 +40,10 @@
  *
  * Threads: a plan must not be used by two threads at once; distinct plans
  * are independent.  No entry point aborts or exits.
+ *
+ * Streams: a plan's calls share its scratch, so calls of one plan on different
+ * streams must not overlap in time, except svconv_forward and
+ * svconv_difference in the basis form and (at SVCONV_FP32) of delta bases.
  */
 #ifndef SVCONV_H
 #define SVCONV_H

@@ -134,6 +134,15 @@ struct DirectArgs {
     int tiles_x;
 };
 
+// Whose the plan's table of regrouped filters at an index is: one stream's,
+// outside capture or in one capture of it.
+constexpr int kTapSlots = 64;
+struct TapSlot {
+    bool taken = false, capturing = false;
+    hipStream_t stream = nullptr;
+    unsigned long long capture = 0;
+};
+
 }  // namespace svc
 
 struct svconv_plan {
@@ -177,6 +186,8 @@ struct svconv_plan {
     // per-call scratch (allocated once)
     float* dFt32 = nullptr;             // [kMaxFilters][k][k] per-call filters (regrouped / adjoint; 8-byte
                                         // taps of the direct kernel: 2 M <= kMaxFilters)
+    double* dTaps = nullptr;            // [kTapSlots][k][k][M] regrouped filters of the basis form's direct route
+    svc::TapSlot tap_slots[svc::kTapSlots];
     double* dBetaT = nullptr;           // [kMaxFilters]
     uint16_t* dFragTB = nullptr;        // per-call bf16 fragments
     uint16_t* dFragTH = nullptr;        // per-call fp16 fragments
@@ -260,6 +271,8 @@ inline bool sep_form(const svconv_plan* p) {
 
 // plan.hip
 int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, float* out);
+// give back the filter tables of a stream that is drained
+void release_tap_slots(svconv_plan* p, hipStream_t stream);
 
 // backward.hip
 size_t adjoint_scratch_doubles(int H, int W, int k, int M);

@@ -133,6 +133,7 @@ int svconv_pipeline_run(svconv_pipeline* q, int n_tiles, const float* const* R_h
     int st2 = hip_status(hipStreamSynchronize(q->s_in), "synchronize");
     int st3 = hip_status(hipStreamSynchronize(q->s_comp), "synchronize");
     int st4 = hip_status(hipStreamSynchronize(q->s_out), "synchronize");
+    if (!st3) release_tap_slots(p, q->s_comp);
     if (st) return st;
     return st2 ? st2 : (st3 ? st3 : st4);
 }

@@ -74,7 +74,7 @@ static void free_plan(svconv_plan* p) {
     void* ptrs[] = {p->dSep1d, p->dSepFam, p->dSepCoef, p->dSepFrag, p->dSepMom, p->dSepRinfo,
                     p->dSepZRow, p->dSepZTab, p->dSepZInv, p->dSepZGam,
                     p->dF32,   p->dF64,   p->dBeta,   p->dFragF32, p->dFragLoB, p->dFragLoH,
-                    p->dScaleB, p->dScaleH, p->dFt32, p->dBetaT, p->dFragTB,  p->dFragTH,
+                    p->dScaleB, p->dScaleH, p->dFt32, p->dTaps, p->dBetaT, p->dFragTB,  p->dFragTH,
                     p->dScaleT, p->dQpart, p->dQ,    p->dGrad,    p->dVec,     p->dStatus,
                     p->dNMpart, p->dTband, p->dRed};
     for (void* q : ptrs)
@@ -104,6 +104,8 @@ static bool is_lowp(int precision) { return precision >= SVCONV_BF16 && precisio
 static bool is_fp16(int precision) {
     return precision == SVCONV_FP16 || precision == SVCONV_FP16X2 || precision == SVCONV_FP16X3;
 }
+
+static bool direct_beats_basis(const svconv_plan* p);
 
 }  // namespace svc
 
@@ -227,6 +229,8 @@ static int finish_plan(svconv_plan* p, svconv_plan** out) {
         st = build_f32_fragments(p->dF32, p->N, k, p->dFragF32, nullptr);
         if (!st) st = build_lowp_fragments(p->dF32, p->N, k, 0, p->dScaleB, p->dFragLoB, nullptr);
         if (!st) st = build_lowp_fragments(p->dF32, p->N, k, 1, p->dScaleH, p->dFragLoH, nullptr);
+        if (!st && !p->dfb && direct_beats_basis(p))
+            st = dalloc(&p->dTaps, (size_t)kTapSlots * p->M * kk, "regrouped filters of the basis form");
     }
     if (!st) st = hip_status(hipDeviceSynchronize(), "plan table build");
     if (st) { free_plan(p); return st; }
@@ -288,6 +292,42 @@ static bool direct_beats_separable(const svconv_plan* p) {
     return direct < separable;
 }
 
+// The table of regrouped filters this call may fill, or NULL if there is none.
+// The dense basis form keeps no per-call state, so calls of one plan on several
+// streams, and replays of several graphs captured from it, may overlap; its
+// direct route keeps that: work on one stream is in order and shares a table, a
+// capture has its own (its replays run beside whatever the streams do later).
+// 64 tables: a stream pool of 32, the default stream, and graphs.  The calls of
+// any further stream or capture take the dense product, as do those on the
+// per-thread default stream, one handle for the streams of all threads.
+static double* tap_slot(svconv_plan* p) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    TapSlot want;
+    if (!p->dTaps || p->stream == hipStreamPerThread) return nullptr;
+    if (hipStreamGetCaptureInfo(p->stream, &status, &want.capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    want.taken = true;
+    want.capturing = status != hipStreamCaptureStatusNone;
+    if (!want.capturing) want.capture = 0;
+    want.stream = p->stream;
+    int at = -1;
+    for (int i = 0; i < kTapSlots && (at < 0 || !p->tap_slots[at].taken); ++i) {
+        const TapSlot& t = p->tap_slots[i];
+        const bool mine = t.taken && t.stream == want.stream && t.capturing == want.capturing && t.capture == want.capture;
+        if (mine || (!t.taken && at < 0)) at = i;
+    }
+    if (at < 0) return nullptr;
+    p->tap_slots[at] = want;
+    return p->dTaps + (size_t)at * p->M * p->k * p->k;
+}
+
+void release_tap_slots(svconv_plan* p, hipStream_t stream) {
+    for (TapSlot& t : p->tap_slots)
+        if (t.taken && !t.capturing && t.stream == stream) t = TapSlot{};
+}
+
 // Shared body of svconv_forward, svconv_difference, svconv_gn_step and the
 // tile pipeline: enqueue one forward pass on the plan's stream.
 int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, float* out) {
@@ -336,11 +376,14 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
         return launch_contract_sepz(z, p->precision, p->stream);
     }
     const bool split = p->precision == SVCONV_FP16X3 || p->precision == SVCONV_BF16X3 || p->precision == SVCONV_FP16X2;
-    const bool direct = p->form == SVCONV_FORM_SEPARABLE ? !split && direct_beats_separable(p)
-                        : lowp                           ? false
-                        : p->form == SVCONV_FORM_BASIS   ? p->N <= kMaxFilters && (p->dfb || direct_beats_basis(p))
-                                                         : true;
-    if (direct) {
+    // Gaussian plans: the regrouped filters of the direct route, none where it is not taken
+    double* taps = nullptr;
+    if (p->form == SVCONV_FORM_SEPARABLE ? !split && direct_beats_separable(p)
+                                         : !lowp && p->form == SVCONV_FORM_REGROUPED)
+        taps = reinterpret_cast<double*>(p->dFt32);
+    else if (p->form == SVCONV_FORM_BASIS && !lowp)
+        taps = tap_slot(p);
+    if (taps || (p->dfb && !lowp)) {
         // regrouped in float64 on the vector units.  The responses of a delta
         // basis are shifted pixels, so its basis form is the same sum anyhow.
         DirectArgs d{};
@@ -355,7 +398,6 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
         if (p->dfb) {
             d.taps = a;
         } else {
-            double* taps = reinterpret_cast<double*>(p->dFt32);
             int st = regroup_filters64(p->dF64, a, p->N, p->M, p->k, taps, p->stream);
             if (st) return st;
             d.taps64 = taps;

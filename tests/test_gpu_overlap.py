@@ -1,0 +1,125 @@
+"""Calls of one basis-form plan that overlap: on several streams, and in the
+replays of several graphs captured from it.  Every call has its own table of
+regrouped filters, so each gives what it gives alone, bit for bit."""
+
+import numpy as np
+import pytest
+
+import synth
+from tests.graph_nodes import capture, kernels
+from tests.helpers import TOL_FP32, err_stats, say, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+H, W, HALF, SIG, DEG, DS = 300, 333, 10, (0.7, 1.5, 2.0), (6, 4, 2), 2
+
+
+def _case(n):
+    R, I = synth.star_field(H, W, 40, seed=1), synth.star_field(H, W, 40, seed=2)
+    a = [synth.coefficients(synth.n_basis(DEG), synth.n_spatial(DS), 28, seed=i) for i in range(n)]
+    return R, I, a
+
+
+def _plan(svc):
+    return svc.Plan(H, W, HALF, SIG, DEG, DS, pedestal=1000.0)
+
+
+def _table(graph):
+    """Where a captured call's filters are written (None: it has no such table)."""
+    k = [k for k in kernels(graph) if "regroup64_kernel" in k.name]
+    return k[0].pointer(5) if k else None
+
+
+def test_each_capture_has_its_own_filters(svc):
+    import torch
+    R, I, a = _case(2)
+    Rd, Id, ad = to_dev(R), to_dev(I), [to_dev(x) for x in a]
+    say("captures of a basis-form plan")
+    with _plan(svc) as plan:
+        alone = [to_host(plan.difference(Rd, Id, x)) for x in ad]
+        out = [torch.empty_like(Rd) for _ in ad]
+        graphs = [capture(lambda: plan.difference(Rd, Id, ad[i], out=out[i])) for i in range(2)]
+        assert _table(graphs[0]) != _table(graphs[1])
+        # two branches of one capture
+        side, forked = torch.cuda.Stream(), [torch.empty_like(Rd) for _ in ad]
+
+        def both():
+            side.wait_stream(torch.cuda.current_stream())
+            plan.difference(Rd, Id, ad[0], out=forked[0])
+            with torch.cuda.stream(side):
+                plan.difference(Rd, Id, ad[1], out=forked[1])
+            torch.cuda.current_stream().wait_stream(side)
+        fork = capture(both)
+        tables = [k.pointer(5) for k in kernels(fork) if "regroup64_kernel" in k.name]
+        assert len(tables) == 2 and tables[0] != tables[1]
+        streams = [torch.cuda.Stream() for _ in range(3)]
+        eager = torch.empty_like(Rd)
+        for g in graphs + [fork]:
+            g.instantiate()
+        torch.cuda.synchronize()
+        for _ in range(20):
+            for s, g in zip(streams, graphs + [fork]):
+                with torch.cuda.stream(s):
+                    g.replay()
+            plan.difference(Rd, Id, ad[1], out=eager)
+        torch.cuda.synchronize()
+        for got in (out, forked):
+            assert np.array_equal(to_host(got[0]), alone[0]) and np.array_equal(to_host(got[1]), alone[1])
+        assert np.array_equal(to_host(eager), alone[1])
+
+
+def test_streams_overlap(svc):
+    import torch
+    R, I, a = _case(4)
+    Rd, Id, ad = to_dev(R), to_dev(I), [to_dev(x) for x in a]
+    say("streams of a basis-form plan")
+    with _plan(svc) as plan:
+        alone = [to_host(plan.difference(Rd, Id, x)) for x in ad]
+        streams, out = [torch.cuda.Stream() for _ in ad], [torch.empty_like(Rd) for _ in ad]
+        torch.cuda.synchronize()
+        for _ in range(20):
+            for s, x, o in zip(streams, ad, out):
+                with torch.cuda.stream(s):
+                    plan.difference(Rd, Id, x, out=o)
+        torch.cuda.synchronize()
+        for got, want in zip(out, alone):
+            assert np.array_equal(to_host(got), want)
+
+
+def test_more_captures_than_tables(svc, orc):
+    """Past the last table a call takes the dense product, which needs none; the
+    streams that hold one keep it."""
+    import torch
+    R, I, a = _case(1)
+    Rd, Id, ad = to_dev(R), to_dev(I), to_dev(a[0])
+    say("captures past the last table")
+    with _plan(svc) as plan:
+        first, out = to_host(plan.difference(Rd, Id, ad)), torch.empty_like(Rd)
+        tables = [_table(capture(lambda: plan.difference(Rd, Id, ad, out=out))) for _ in range(70)]
+        had = [t for t in tables if t is not None]
+        assert 32 <= len(had) < 70 and len(set(had)) == len(had)
+        assert tables[len(had):] == [None] * (70 - len(had))
+        dense = capture(lambda: plan.difference(Rd, Id, ad, out=out))
+        assert any("contract_f32_kernel" in k.name for k in kernels(dense))
+        dense.instantiate()
+        dense.replay()
+        want = orc.difference(R, I, HALF, orc.basis(HALF, SIG, DEG), DS, a[0])
+        assert err_stats(to_host(out), want)[0] <= TOL_FP32
+        assert np.array_equal(to_host(plan.difference(Rd, Id, ad)), first)
+
+
+def test_pipelines_give_their_table_back(svc):
+    """A pipeline's compute stream is drained when its run returns."""
+    import torch
+    R, I, a = _case(1)
+    host = [torch.from_numpy(x) for x in (R, I, a[0])]
+    dev = [x.cuda() for x in host]
+    say("pipelines of a basis-form plan")
+    with _plan(svc) as plan:
+        want = to_host(plan.difference(*dev))
+        for _ in range(70):
+            D = torch.empty(H, W)
+            with svc.Pipeline(plan, depth=1) as q:
+                q.run([host[0]], [host[1]], [host[2]], [D])
+            assert np.array_equal(D.numpy(), want)
+        assert _table(capture(lambda: plan.difference(*dev))) is not None
