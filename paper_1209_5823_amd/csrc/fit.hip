@@ -746,7 +746,7 @@ __global__ __launch_bounds__(256) void chol_finish_kernel(double* __restrict__ A
 
 int launch_cholesky(svconv_plan* p, double* A, int n) {
     int st = SVCONV_OK;
-    double* diag = p->dVec;   // [n]
+    double* diag = p->dVec + kVecPivots;   // [n]
     for (int k0 = 0; k0 < n && !st; k0 += CH_NB) {
         const int nt = n - k0 > CH_NB ? (n - k0 - 1) / CH_NB : 0;   // tiles of the rows below the block
         hipLaunchKernelGGL(chol_step_kernel, dim3(nt ? nt * (nt + 1) / 2 : 1), dim3(256), 0, p->stream, A, n, k0, diag,

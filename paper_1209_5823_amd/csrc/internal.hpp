@@ -134,6 +134,19 @@ struct DirectArgs {
     int tiles_x;
 };
 
+// The plan's vector scratch, in doubles: the vectors of a fit step or of
+// conjugate gradients (four, 8 scalars and one float32 copy), the pivots of a
+// factorisation, and the per-call coefficients of the separable form.  Parts
+// of their own: entry points that shared none of it may run on streams of
+// their own beside each other.
+constexpr size_t kVecPivots = 5 * (size_t)kMaxCoefficients;
+constexpr size_t kVecSepCoef = 7 * (size_t)kMaxCoefficients;
+constexpr size_t kVecSepGamma = 8 * (size_t)kMaxCoefficients;
+constexpr size_t kVecDoubles = kVecSepGamma + 64;
+static_assert(4 * kMaxCoefficients + 8 + kMaxCoefficients / 2 <= kVecPivots, "fit vectors reach the pivots");
+static_assert(kVecPivots + kMaxCoefficients <= kVecSepCoef && kVecSepCoef + kMaxCoefficients <= kVecSepGamma,
+              "parts of the vector scratch overlap");
+
 // Whose the plan's table of regrouped filters at an index is: one stream's,
 // outside capture or in one capture of it.
 constexpr int kTapSlots = 64;

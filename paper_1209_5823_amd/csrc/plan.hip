@@ -155,7 +155,7 @@ static int finish_plan(svconv_plan* p, svconv_plan** out) {
         (st = dalloc(&p->dFragTB, fraglT, "per-call bf16 fragments")) ||
         (st = dalloc(&p->dFragTH, fraglT, "per-call fp16 fragments")) ||
         (st = dalloc(&p->dScaleT, (size_t)2 * kMaxFilters, "per-call scales")) ||
-        (st = dalloc(&p->dVec, (size_t)8 * kMaxCoefficients + 64, "vector scratch")) ||
+        (st = dalloc(&p->dVec, kVecDoubles, "vector scratch")) ||
         (st = dalloc(&p->dStatus, (size_t)4, "status word")) ||
         (st = dalloc(&p->dGrad, (size_t)p->H * p->W, "loss gradient")) ||
         (st = dalloc(&p->dRed, (size_t)2048, "reduction scratch")) ||
@@ -425,8 +425,8 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
         sa.n_rows = p->H;
         sa.tout = nullptr;
         // per-call tables in the plan's vector scratch, past what the fit uses
-        double* coefd = p->dVec + 7 * (size_t)kMaxCoefficients;
-        double* gamma = p->dVec + 8 * (size_t)kMaxCoefficients;
+        double* coefd = p->dVec + kVecSepCoef;
+        double* gamma = p->dVec + kVecSepGamma;
         int st = launch_sep_prep(a, p->dBeta, p->N, p->M, coefd, gamma, p->dSepCoef, p->stream);
         if (st) return st;
         sa.coefd = coefd;
@@ -717,8 +717,8 @@ int svconv_backward(svconv_plan* p, const float* R, const float* a, const float*
         sa.M = p->M;
         sa.d_s = p->d_s;
         sa.sx = c.sx; sa.ox = c.ox; sa.sy = c.sy; sa.oy = c.oy;
-        double* coefd = p->dVec + 7 * (size_t)kMaxCoefficients;
-        double* gamma = p->dVec + 8 * (size_t)kMaxCoefficients;
+        double* coefd = p->dVec + kVecSepCoef;
+        double* gamma = p->dVec + kVecSepGamma;
         st = launch_sep_prep(a, p->dBeta, p->N, p->M, coefd, gamma, p->dSepCoef, p->stream);
         if (st) return st;
         sa.coefpf = reinterpret_cast<const float*>(p->dSepCoef + (size_t)(p->N + 1) * kSepCoefPad);

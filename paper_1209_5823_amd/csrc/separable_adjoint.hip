@@ -569,8 +569,8 @@ int launch_adjoint_r_sep(svconv_plan* p, const float* a32, const float* G, float
     if (!p->dSep1d || p->h < 1 || p->h > 15)
         return fail(SVCONV_EUNSUPPORTED, "separable adjoint needs Gaussian bases and 1 <= half-width <= 15");
     const int h = p->h;
-    double* coefd = p->dVec + 7 * (size_t)kMaxCoefficients;
-    double* gamma = p->dVec + 8 * (size_t)kMaxCoefficients;
+    double* coefd = p->dVec + kVecSepCoef;
+    double* gamma = p->dVec + kVecSepGamma;
     int st = launch_sep_prep(a32, p->dBeta, p->N, p->M, coefd, gamma, nullptr, p->stream);
     if (st) return st;
     SepRArgs a{};

@@ -123,3 +123,39 @@ def test_pipelines_give_their_table_back(svc):
                 q.run([host[0]], [host[1]], [host[2]], [D])
             assert np.array_equal(D.numpy(), want)
         assert _table(capture(lambda: plan.difference(*dev))) is not None
+
+
+def test_factor_beside_a_fit_step(svc):
+    """A factorisation on one stream while a Gauss-Newton step of the same plan is
+    in flight on another: they share no scratch."""
+    import torch
+    h, w, half, sig, deg, d_s = 96, 112, 3, (1.2,), (3,), 2
+    n = synth.n_basis(deg) * synth.n_spatial(d_s)
+    R, I = to_dev(synth.star_field(h, w, 30, seed=3)), to_dev(synth.star_field(h, w, 30, seed=4))
+    A = torch.from_numpy(np.eye(n) * 4.0 + 1.0 / n).cuda()
+    say("factor beside a step")
+    with svc.Plan(h, w, half, sig, deg, d_s, pedestal=1000.0) as plan:
+        L = plan.cholesky_factor(plan.normal_matrix(R))
+        a0 = torch.zeros(plan._fit_coef, dtype=torch.float64).cuda()
+        a0[6, 0] = 1.0
+
+        def state():
+            return a0.clone(), torch.empty_like(a0, dtype=torch.float32), torch.empty_like(R)
+
+        def step(a64, a32, D):
+            plan.gn_step(R, I, L, a64, a32, D, stats=False)
+        alone = state()
+        step(*alone)
+        alone = to_host(alone[0])
+        fit, other = torch.cuda.Stream(), torch.cuda.Stream()
+        for _ in range(20):
+            st, factors = state(), [A.clone() for _ in range(6)]
+            torch.cuda.synchronize()
+            with torch.cuda.stream(fit):
+                step(*st)
+            with torch.cuda.stream(other):
+                for M in factors:
+                    plan.cholesky_factor(M)
+            # the adjoint's sums agree to float64 rounding from call to call, and
+            # the step takes them through the normal matrix of a star field
+            assert np.max(np.abs(to_host(st[0]) - alone)) <= 1e-6 * np.abs(alone).max()
