@@ -440,6 +440,26 @@ static int band_responses(svconv_plan* p, const float* R, int y0, int rows) {
     return launch_contract_f32(c, p->dFragF32, (p->N + 15) / 16, p->stream);
 }
 
+// Scratch of the normal matrix, kept by the plan: allocated on its first call,
+// and grown by a later call that needs more.  Each buffer on its own, and never
+// smaller: calls with and without a mask, a background or a right-hand side
+// need different shares of the two, and would otherwise free and allocate both
+// on every change from one to the other.
+template <class T>
+static int grow(T*& ptr, size_t& have, size_t need) {
+    if (have >= need) return SVCONV_OK;
+    if (ptr) (void)hipFree(ptr);
+    ptr = nullptr;
+    have = 0;
+    if (hipMalloc((void**)&ptr, need) != hipSuccess) {
+        (void)hipGetLastError();
+        ptr = nullptr;
+        return fail(SVCONV_ENOMEM, "normal-matrix scratch");
+    }
+    have = need;
+    return SVCONV_OK;
+}
+
 // With a background polynomial the fit has one more "basis" whose response
 // is the constant 1 (bg = sum_m b_m P_m * 1), so the same Gram sums give the
 // background rows and columns of the normal matrix.  With I and rhs given, one
@@ -483,25 +503,9 @@ int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const u
     const size_t s_elems = (size_t)n_mu * E, xw_elems = (size_t)n_a * p->W, ones_elems = ((size_t)p->W + 16 + 1) / 2;
     const size_t tband_bytes = shifts ? 0 : band * row_bytes;
     const size_t nmpart_bytes = (part_elems + part2_elems + s_elems + xw_elems + ones_elems) * sizeof(double);
-    // scratch of the normal matrix: allocated on its first call (grown when
-    // a later call needs more), kept by the plan
-    if (p->tband_bytes < tband_bytes || p->nmpart_bytes < nmpart_bytes) {
-        if (p->dTband) (void)hipFree(p->dTband);
-        if (p->dNMpart) (void)hipFree(p->dNMpart);
-        p->dTband = nullptr;
-        p->dNMpart = nullptr;
-        p->tband_bytes = p->nmpart_bytes = 0;
-        if ((tband_bytes && hipMalloc((void**)&p->dTband, tband_bytes) != hipSuccess) ||
-            hipMalloc((void**)&p->dNMpart, nmpart_bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            if (p->dTband) (void)hipFree(p->dTband);
-            p->dTband = nullptr;
-            p->dNMpart = nullptr;
-            return fail(SVCONV_ENOMEM, "normal-matrix scratch");
-        }
-        p->tband_bytes = tband_bytes;
-        p->nmpart_bytes = nmpart_bytes;
-    }
+    int st = grow(p->dTband, p->tband_bytes, tband_bytes);
+    if (!st) st = grow(p->dNMpart, p->nmpart_bytes, nmpart_bytes);
+    if (st) return st;
     double* part2 = p->dNMpart + part_elems;
     double* S = part2 + part2_elems;
     double* xw = S + s_elems;
@@ -515,7 +519,7 @@ int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const u
         hipLaunchKernelGGL(gram_tables_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, p->stream, p->W, x_in,
                            x_hi, sx, ox, n_a, xw, ones, S, (int)s_elems);
     }
-    int st = hip_status(hipGetLastError(), "gram_tables_kernel");
+    st = hip_status(hipGetLastError(), "gram_tables_kernel");
     if (st) return st;
 
     GramArgs g{};
