@@ -258,7 +258,8 @@ static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
     // above third order the totals of 16 rows no longer fit the registers.
     // (8 rows at second order: more waves, but 13 % more instructions per pixel,
     // 435 -> 471 us at 21 x 21, 2048 x 4096)
-    constexpr int ROWS = J <= 4 ? 16 : 8, CUS = 256;
+    constexpr int ROWS = J <= 4 ? 16 : 8;
+    const int cus = device_cus();
     // whole tiles per wave while they give every CU three workgroups (what the
     // registers hold); then four waves on the same pixels, and eight where there
     // is at most one such tile per CU (21 x 21 at 512 x 512: 127 us with one
@@ -266,10 +267,10 @@ static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
     // 771, 429 tiles, 40 us with four, 47 us with eight).  A 3 x 3 or 5 x 5
     // kernel has no eight items to share.  Tiles of half the rows where even
     // those give a CU at most one (256 x 256: 23 -> 19 us).
-    if (direct_tiles(a, 4 * ROWS) >= 3 * CUS) return launch_direct<J, ROWS, 4, 1>(a, s);
-    if (direct_tiles(a, ROWS) > CUS || a.h < 3) return launch_direct<J, ROWS, 4, 4>(a, s);
+    if (direct_tiles(a, 4 * ROWS) >= 3 * cus) return launch_direct<J, ROWS, 4, 1>(a, s);
+    if (direct_tiles(a, ROWS) > cus || a.h < 3) return launch_direct<J, ROWS, 4, 4>(a, s);
     if constexpr (ROWS == 16) {
-        if (direct_tiles(a, 8) <= CUS) return launch_direct<J, 8, 8, 8>(a, s);
+        if (direct_tiles(a, 8) <= cus) return launch_direct<J, 8, 8, 8>(a, s);
     }
     launch_direct<J, ROWS, 8, 8>(a, s);
 }

@@ -24,6 +24,9 @@ int fail(int status, const std::string& msg);
 // Map a HIP error to SVCONV_EDEVICE with a message (hipSuccess -> OK).
 int hip_status(hipError_t e, const char* what);
 
+// Compute units of the current device (looked up once per device).
+int device_cus();
+
 // Dense filters in correlation orientation:
 //   T_f(x,y) = sum_{dv,du} F[f][dv][du] X(x + du - h, y + dv - h).
 // The basis form uses F_n[dv][du] = B_n[2h-dv][2h-du] (true convolution).

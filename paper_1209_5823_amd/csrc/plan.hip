@@ -1,5 +1,6 @@
 // C ABI of libsvconv: plan construction (float64 basis on the host,
 // device tables), argument validation and dispatch to the kernel families.
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -19,6 +20,18 @@ int fail(int status, const std::string& msg) {
 int hip_status(hipError_t e, const char* what) {
     if (e == hipSuccess) return SVCONV_OK;
     return fail(SVCONV_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
+}
+
+int device_cus() {
+    static std::atomic<int> cus[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int n = cus[dev].load(std::memory_order_relaxed);
+    if (!n) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        cus[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
 }
 
 // Basis functions (Sec. 2, Eq. 2; Gaussian basis of Alard & Lupton):
@@ -285,8 +298,8 @@ static bool direct_beats_separable(const svconv_plan* p) {
         for (int i = 0; i <= d; ++i) fold += window(d - i + 1);
     }
     fold += p->N * (p->d_s + 4.0);
-    const long tiles = (long)((p->W + 63) / 64) * ((p->H + 63) / 64);
-    const double rounds = (double)((tiles + 255) / 256);
+    const long tiles = (long)((p->W + 63) / 64) * ((p->H + 63) / 64), cus = device_cus();
+    const double rounds = (double)((tiles + cus - 1) / cus);
     const double separable = rounds * (rounds > 2 ? 0.93 : 1.0) * (5.0 + 0.042 * fold);
     const double n = direct_count(p), direct = 10.0 + 0.006 * n + 3.5e-8 * n * p->H * p->W;
     return direct < separable;

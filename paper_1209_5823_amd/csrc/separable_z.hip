@@ -772,19 +772,6 @@ __global__ __launch_bounds__(SZ_NT * SP, (SzTile<OB, SP>::MINW)) void contract_s
     }
 }
 
-// Compute units of the current device (cached per device).
-static int device_cus() {
-    static int cus[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (!cus[dev]) {
-        int n = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        cus[dev] = n;
-    }
-    return cus[dev];
-}
-
 template <bool FP16, int NT, int MP, int OB, int SP>
 static void launch_sepz_t(SepZArgs a, hipStream_t s) {
     typedef SzTile<OB, SP> S;
