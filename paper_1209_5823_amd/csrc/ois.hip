@@ -31,7 +31,17 @@ namespace svc {
 // 10: 650 us as one lane per pixel with its own window loop and 64-bit index
 // divisions -> 32 us (40 us with the windows read from L2 instead of LDS, 42 us
 // with clamped row addresses in every tile and the neighbours tested one by one).
-constexpr int CENTRE_TX = 64, CENTRE_TY = 32, CENTRE_STAGE = 14;
+//
+// Windows above CENTRE_WHOLE are scanned in two steps: the part within
+// CENTRE_NEAR from LDS, and only for the candidates that it leaves, which are
+// then far from each other, all of the window that lies inside the image from
+// L2.  In one step the halo of r_iso = 64 takes 123 KiB of LDS (four waves per
+// CU) and 15 times the tile, and every scan starts at the far corner: crowded
+// fields (sky noise above 0.6 sigma, frac 0.1) at r_iso = 64 took 911 us at 64
+// x 64 and 3714 at 2048 x 4096, now 45 and 151 (whole calls).
+// A wave takes the candidates of its rows one after the other, so on frames of
+// at most one tile per CU 16 waves share a tile.
+constexpr int CENTRE_TX = 64, CENTRE_TY = 32, CENTRE_WHOLE = 24, CENTRE_NEAR = 16, CENTRE_FAR = 4;
 constexpr int COUNT_SLOTS = 64, COUNT_STRIDE = 32;   // counters on 128-byte lines of their own
 
 // t[0] strictly larger than each of its neighbours
@@ -43,10 +53,30 @@ __device__ __forceinline__ bool strict_local_max(const float* t, int pitch) {
     return (v > a0) & (v > a1) & (v > a2) & (v > b0) & (v > b2) & (v > c0) & (v > c1) & (v > c2);
 }
 
-__global__ __launch_bounds__(256) void centre_kernel(const float* __restrict__ R, int H, int W, double sky,
+// the same at (x, y) of the image, from memory; neighbours outside it do not count
+__device__ __forceinline__ bool strict_local_max(const float* __restrict__ R, int H, int W, int x, int y) {
+    const float v = R[(size_t)y * W + x];
+    const int xl = max(x - 1, 0), xr = min(x + 1, W - 1);
+    bool ok = true;
+#pragma unroll
+    for (int d = -1; d <= 1; ++d) {
+        const float* row = R + (size_t)min(max(y + d, 0), H - 1) * W;
+        const float l = row[xl], c = row[x], r = row[xr];
+        const bool in = y + d >= 0 && y + d < H;
+        ok &= !in | x == 0 | v > l;
+        ok &= !in | x == W - 1 | v > r;
+        if (d) ok &= !in | v > c;
+    }
+    return ok;
+}
+
+// FAR: the window reaches past the staged halo
+template <int NW, bool FAR>
+__global__ __launch_bounds__(64 * NW) void centre_kernel(const float* __restrict__ R, int H, int W, double sky,
                                                      double thr, double frac, int r_iso, int margin,
                                                      unsigned* __restrict__ bits, int wpr, int tiles_x,
                                                      int* __restrict__ count) {
+    constexpr int CENTRE_STAGE = NW == 4 ? 14 : 5;   // rows requested together
     extern __shared__ float tile[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // consecutive tiles on one XCD (workgroups go round the 8 XCDs), whose L2 then serves the halos
@@ -56,7 +86,7 @@ __global__ __launch_bounds__(256) void centre_kernel(const float* __restrict__ R
     const int x0 = tx * CENTRE_TX, y0 = ty * CENTRE_TY;
     // the counters are added to by the next kernel on the stream
     if (blockIdx.x == 0 && threadIdx.x < COUNT_SLOTS) count[threadIdx.x * COUNT_STRIDE] = 0;
-    const int halo = r_iso + 1, pitch = CENTRE_TX + 2 * halo, rows = CENTRE_TY + 2 * halo;
+    const int r_near = FAR ? CENTRE_NEAR : r_iso, halo = r_near + 1, pitch = CENTRE_TX + 2 * halo, rows = CENTRE_TY + 2 * halo;
     // columns 0..63 of each row by a whole wave, the others by half a wave per row
     const bool inner = x0 >= halo && x0 + CENTRE_TX + halo <= W && y0 >= halo && y0 + CENTRE_TY + halo <= H;
     auto stage = [&](int r0, int r_step, int col) {
@@ -85,16 +115,17 @@ __global__ __launch_bounds__(256) void centre_kernel(const float* __restrict__ R
                 if (r0 + r_step * b < rows) dst[r_step * b * pitch] = v[b];
         }
     };
-    for (int r0 = wave; r0 < rows; r0 += 4 * CENTRE_STAGE) stage(r0, 4, lane);
+    for (int r0 = wave; r0 < rows; r0 += NW * CENTRE_STAGE) stage(r0, NW, lane);
     for (int c0 = 64; c0 < pitch; c0 += 32)
-        for (int r0 = 2 * wave + (lane >> 5); r0 < rows; r0 += 8 * CENTRE_STAGE) stage(r0, 8, c0 + (lane & 31));
+        for (int r0 = 2 * wave + (lane >> 5); r0 < rows; r0 += 2 * NW * CENTRE_STAGE)
+            stage(r0, 2 * NW, c0 + (lane & 31));
     __syncthreads();
     // this lane's first pixel of a window, and the step to its next (64 on)
-    const int ww = 2 * r_iso + 1, total = ww * ww;
+    const int ww = 2 * r_near + 1;
     const int col_first = lane % ww, row_first = lane / ww, row_step = 64 / ww, col_step = 64 - row_step * ww;
     const int x = x0 + lane;
     const bool inx = x < W && x >= margin && x <= W - 1 - margin;
-    constexpr int ROWS = CENTRE_TY / 4;
+    constexpr int ROWS = CENTRE_TY / NW;
     const float* mine = tile + (wave * ROWS + halo) * pitch + lane + halo;
     float v[ROWS];
 #pragma unroll
@@ -108,12 +139,14 @@ __global__ __launch_bounds__(256) void centre_kernel(const float* __restrict__ R
         if (__any(above)) {
             const float* here = mine + r * pitch;
             found = __ballot(above && strict_local_max(here, pitch));
-            // isolation: the wave scans the window of one candidate at a time
-            for (unsigned long long todo = found; todo; todo &= todo - 1) {
+            // isolation: the wave scans the window's rows inside the image, one
+            // candidate at a time (a neighbour of a strict maximum is none)
+            const int up = min(r_near, y), total = (up + min(r_near, H - 1 - y) + 1) * ww;
+            for (unsigned long long todo = r_iso > 1 ? found : 0; todo; todo &= todo - 1) {
                 const int c = __ffsll(todo) - 1;
                 const float* centre = here - lane + c;
                 const double lim = frac * ((double)centre[0] - sky);
-                const float* corner = centre - r_iso * pitch - r_iso;
+                const float* corner = centre - up * pitch - r_near;
                 int row = row_first, col = col_first;
                 for (int t = lane; t - lane < total; t += 64) {
                     const float* q = corner + row * pitch + col;
@@ -127,6 +160,37 @@ __global__ __launch_bounds__(256) void centre_kernel(const float* __restrict__ R
                     if (col >= ww) {
                         col -= ww;
                         ++row;
+                    }
+                }
+            }
+            // the whole window of those left, as far as it lies inside the image
+            if (FAR) {
+                for (unsigned long long todo = found; todo; todo &= todo - 1) {
+                    const int c = __ffsll(todo) - 1, cx = x0 + c;
+                    const double lim = frac * ((double)here[c - lane] - sky);
+                    const int wx = max(cx - r_iso, 0), wy = max(y - r_iso, 0);
+                    const int nx = min(cx + r_iso, W - 1) - wx + 1, n = nx * (min(y + r_iso, H - 1) - wy + 1);
+                    const float inv = 1.f / (float)nx;
+                    for (int t0 = 0; t0 < n; t0 += 64 * CENTRE_FAR) {
+                        int qx[CENTRE_FAR], qy[CENTRE_FAR];
+                        float q[CENTRE_FAR];
+#pragma unroll
+                        for (int b = 0; b < CENTRE_FAR; ++b) {
+                            // t / nx: exact, as t < 129^2 + 256 and (t + 1/2) / nx is 1/258 from an integer at least
+                            const int t = min(t0 + 64 * b + lane, n - 1), row = (int)(((float)t + 0.5f) * inv);
+                            qy[b] = wy + row;
+                            qx[b] = wx + t - row * nx;
+                            q[b] = R[(size_t)qy[b] * W + qx[b]];
+                        }
+                        bool bright = false;
+#pragma unroll
+                        for (int b = 0; b < CENTRE_FAR; ++b)
+                            if ((double)q[b] - sky >= lim && !(qx[b] == cx && qy[b] == y))
+                                bright |= strict_local_max(R, H, W, qx[b], qy[b]);
+                        if (__any(bright)) {
+                            found &= ~(1ull << c);
+                            break;
+                        }
                     }
                 }
             }
@@ -438,8 +502,12 @@ int svconv_stamp_mask(svconv_plan* p, const float* R, double sky, double thresho
     const int wpr = (p->W + 31) / 32;
     int* count = reinterpret_cast<int*>(p->dRed);
     const int cx = (p->W + CENTRE_TX - 1) / CENTRE_TX, cy = (p->H + CENTRE_TY - 1) / CENTRE_TY;
-    const size_t lds = (size_t)(CENTRE_TX + 2 * r_iso + 2) * (CENTRE_TY + 2 * r_iso + 2) * sizeof(float);   // <= 123 KiB
-    hipLaunchKernelGGL(centre_kernel, dim3((unsigned)cx * cy), dim3(256), lds, p->stream, R, p->H, p->W, sky,
+    const int halo = (r_iso > CENTRE_WHOLE ? CENTRE_NEAR : r_iso) + 1;
+    const size_t lds = (size_t)(CENTRE_TX + 2 * halo) * (CENTRE_TY + 2 * halo) * sizeof(float);   // <= 37 KB
+    const bool few = (long)cx * cy <= device_cus(), far = r_iso > CENTRE_WHOLE;
+    auto kernel = few ? (far ? centre_kernel<16, true> : centre_kernel<16, false>)
+                      : (far ? centre_kernel<4, true> : centre_kernel<4, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)cx * cy), dim3(few ? 1024 : 256), lds, p->stream, R, p->H, p->W, sky,
                        threshold, frac, r_iso, margin, bits, wpr, cx, count);
     int st = hip_status(hipGetLastError(), "centre_kernel");
     if (st) return st;

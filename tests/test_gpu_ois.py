@@ -237,3 +237,32 @@ def test_normal_equations_with_background_match_oracle_fit(svc, orc, form, preci
     assert e_m <= 2e-6 and e_r <= 2e-6
     assert rms_model <= 1e-2
     assert hist[-1][1] <= 1e-6 * hist[0][1]
+
+
+@pytest.mark.parametrize("shape", [(40, 50), (150, 333), (700, 1100)])
+@pytest.mark.parametrize("r_iso,frac", [(2, 0.1), (16, 0.5), (24, 0.9), (25, 0.9), (25, 3.0), (40, 0.3), (64, 0.9)])
+def test_stamp_mask_crowded(svc, orc, shape, r_iso, frac):
+    """Fields where most local maxima are candidates, with windows on both sides of
+    the staged halo; frames of few tiles and of more than one per CU; bit-exact."""
+    H, W = shape
+    r = np.random.default_rng(H + r_iso)
+    R = (SKY + r.normal(size=shape) * 30).astype(np.float32)
+    R[r.random(shape) < 0.001] += 500
+    R[0, 0], R[H - 1, W - 1], R[5, 7] = np.nan, np.inf, -np.inf
+    thr = 20.0 if H < 500 else 120.0
+    say("stamps, crowded", shape, r_iso, frac)
+    # the oracle's definition, a window at a time (its loops take minutes here)
+    R64 = R.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        lmax = orc._strict_local_max(R64)
+        want = []
+        for y, x in np.argwhere(lmax & (R64 - SKY > thr)):
+            if 1 <= x <= W - 2 and 1 <= y <= H - 2:
+                win = (slice(max(0, y - r_iso), y + r_iso + 1), slice(max(0, x - r_iso), x + r_iso + 1))
+                if np.count_nonzero(lmax[win] & (R64[win] - SKY >= frac * (R64[y, x] - SKY))) == (frac <= 1):
+                    want.append((int(x), int(y)))
+    with svc.Plan(H, W, 1, (1.5,), (0,), 1) as plan:
+        mask, n = plan.stamp_mask(to_dev(R), SKY, thr, frac, r_iso=r_iso, margin=1, stamp_half=3)
+        say("  centres", n, len(want))
+        assert n == len(want)
+        assert np.array_equal(to_host(mask), orc.stamp_mask(H, W, want, 3))
