@@ -519,9 +519,10 @@ int svconv_stamp_mask(svconv_plan* p, const float* R, double sky, double thresho
     int parts[COUNT_SLOTS * COUNT_STRIDE], total = 0;
     st = hip_status(hipMemcpyAsync(parts, count, sizeof(parts), hipMemcpyDeviceToHost, p->stream), "copy count");
     if (!st) st = hip_status(hipStreamSynchronize(p->stream), "hipStreamSynchronize");
+    if (st) return st;
     for (int i = 0; i < COUNT_SLOTS; ++i) total += parts[i * COUNT_STRIDE];
-    if (!st) *n_centres = total;
-    return st;
+    *n_centres = total;
+    return SVCONV_OK;
 }
 
 int svconv_plan_set_background(svconv_plan* p, int enable) {
