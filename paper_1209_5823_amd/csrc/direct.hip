@@ -13,12 +13,15 @@
 // column.  Everything is float64: on this chip a float64 FMA issues at the rate
 // of an unpacked float32 one (4 cycles a wave), so what float32 products with
 // float64 row sums spent on conversions and additions is saved as well, and D
-// is rounded once.  The taps arrive by scalar loads (uniform over the wave).
+// is rounded once.  The taps arrive by scalar loads (uniform over the wave),
+// requested once the ones before are folded: two sets at once overflow the
+// scalar registers at high order (31 x 31, sixth order, 256 x 256: 148 -> 58 us;
+// 31 x 31, third order, 2048 x 2048: 705 -> 616 us).
 //
 // Bound: the float64 FMA rate (161 FMAs and 74 other vector instructions per
 // pixel at 7 x 7, second order; the vector units issue on about three quarters
 // of the cycles).  7 x 7 delta basis, second order, 4846 x 4868: 315 us
-// (float32 FMAs over six terms, float64 row sums) -> 189 us, error against
+// (float32 FMAs over six terms, float64 row sums) -> 182 us, error against
 // float64 4.0e-8 -> 2.5e-8 of D; 21 x 21, 49 bases, second order, 2048 x 4096:
 // 741 us (float32 matrix cores) -> 432 us; 31 x 31, third order, 2048 x 2048:
 // 1323 -> 715 us.
@@ -152,20 +155,21 @@ __global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs 
 #pragma unroll
         for (int i = 0; i < DR_CH; ++i) {
             if (i < n) {   // uniform
-                // the taps of the next kernel pixel are requested before the
-                // products of this one
-                const Taps t = next;
-                off = (i + 1 < DR_CH && i + 1 < n) ? off + down : off_item;
-                next = load_taps(off);
-                __builtin_amdgcn_sched_barrier(0);
                 // spatial term m = q (q + 1) / 2 + j is xh^(q - j) yh^j
                 double b[J];
 #pragma unroll
                 for (int j = 0; j < J; ++j) {
-                    b[j] = (double)t.v[DS * (DS + 1) / 2 + j];
+                    b[j] = (double)next.v[DS * (DS + 1) / 2 + j];
 #pragma unroll
-                    for (int q = DS - 1; q >= j; --q) b[j] = fma(b[j], xh, (double)t.v[q * (q + 1) / 2 + j]);
+                    for (int q = DS - 1; q >= j; --q) b[j] = fma(b[j], xh, (double)next.v[q * (q + 1) / 2 + j]);
                 }
+                // the taps of the next kernel pixel, once these are folded (two
+                // sets do not fit the scalar registers from fourth order on) and
+                // before the products of this one
+                __builtin_amdgcn_sched_barrier(0);
+                off = (i + 1 < DR_CH && i + 1 < n) ? off + down : off_item;
+                next = load_taps(off);
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int r = 0; r < ROWS; ++r)
 #pragma unroll
