@@ -63,9 +63,9 @@ __device__ __forceinline__ bool strict_local_max(const float* __restrict__ R, in
         const float* row = R + (size_t)min(max(y + d, 0), H - 1) * W;
         const float l = row[xl], c = row[x], r = row[xr];
         const bool in = y + d >= 0 && y + d < H;
-        ok &= !in | x == 0 | v > l;
-        ok &= !in | x == W - 1 | v > r;
-        if (d) ok &= !in | v > c;
+        ok &= !in | (x == 0) | (v > l);
+        ok &= !in | (x == W - 1) | (v > r);
+        if (d) ok &= !in | (v > c);
     }
     return ok;
 }
