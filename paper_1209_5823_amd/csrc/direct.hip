@@ -51,12 +51,14 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
 
 // DFB: taps is a itself (float32), tap (m, dv, du) = a[(k^2 - 1 - (dv k + du)) M + m]
 // (the delta basis in correlation orientation); otherwise taps64[du][dv][m].
-template <int J, int ROWS, int WAVES, int S, bool DFB>
+// HC: the half-width where it is known at compile time, else 0.
+template <int J, int ROWS, int WAVES, int S, bool DFB, int HC>
 __global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs a) {
     constexpr int DS = J - 1, M = J * (J + 1) / 2;
     constexpr int NT = 64 * WAVES, TH = ROWS * WAVES / S;
     extern __shared__ float tile[];
-    const int h = a.h, K = 2 * h + 1;
+    constexpr int CH = HC && 2 * HC + 1 < DR_CH ? 2 * HC + 1 : DR_CH;   // kernel rows of an item
+    const int h = HC ? HC : a.h, K = 2 * h + 1;
     const int SC = DR_TW + 2 * h, SR = TH + 2 * h;
 
     const int tid = threadIdx.x, c = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -132,28 +134,28 @@ __global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs 
     const unsigned down = DFB ? 0u - (unsigned)K * TB : TB;
     const int group = S == 1 ? wave : wave / S, member = S == 1 ? 0 : wave % S;
     // items in order of du, then dv0; this wave takes items member, member + S, ...
-    const unsigned n_ch = (K + DR_CH - 1) / DR_CH, inv_ch = 65536u / n_ch + 1u;
+    const unsigned n_ch = (K + CH - 1) / CH, inv_ch = 65536u / n_ch + 1u;
     unsigned item = member;
     int du, dv0;
     auto place = [&]() {
         du = (int)((item * inv_ch) >> 16);   // item / n_ch: exact, as item <= 63 x 9 + 8
-        dv0 = (int)(item - du * n_ch) * DR_CH;
+        dv0 = (int)(item - du * n_ch) * CH;
     };
     place();
     unsigned off = offset(dv0, min(du, K - 1));
     Taps next = load_taps(off);
 #pragma unroll 1
     while (du < K) {
-        double s[ROWS + DR_CH - 1];
+        double s[ROWS + CH - 1];
         const float* col = tile + (group * ROWS + dv0) * SC + c + du;
 #pragma unroll
-        for (int i = 0; i < ROWS + DR_CH - 1; ++i) s[i] = (double)col[i * SC];
-        const int n = K - dv0;   // taps of this item, if fewer than DR_CH
+        for (int i = 0; i < ROWS + CH - 1; ++i) s[i] = (double)col[i * SC];
+        const int n = K - dv0;   // taps of this item, if fewer than CH
         item += S;
         place();
         const unsigned off_item = offset(dv0, min(du, K - 1));
 #pragma unroll
-        for (int i = 0; i < DR_CH; ++i) {
+        for (int i = 0; i < CH; ++i) {
             if (i < n) {   // uniform
                 // spatial term m = q (q + 1) / 2 + j is xh^(q - j) yh^j
                 double b[J];
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs 
                 // sets do not fit the scalar registers from fourth order on) and
                 // before the products of this one
                 __builtin_amdgcn_sched_barrier(0);
-                off = (i + 1 < DR_CH && i + 1 < n) ? off + down : off_item;
+                off = (i + 1 < CH && i + 1 < n) ? off + down : off_item;
                 next = load_taps(off);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -243,7 +245,7 @@ int regroup_filters64(const double* F64, const float* a, int N, int M, int k, do
 
 static int direct_tiles(const DirectArgs& a, int th) { return a.tiles_x * ((a.H + th - 1) / th); }
 
-template <int J, int ROWS, int WAVES, int S>
+template <int J, int ROWS, int WAVES, int S, int HC = 0>
 static void launch_direct(const DirectArgs& a, hipStream_t s) {
     constexpr int TH = ROWS * WAVES / S;
     // the rows of the last window are read past the tile's 2 h halo rows, unused
@@ -252,9 +254,9 @@ static void launch_direct(const DirectArgs& a, hipStream_t s) {
     if (S > 1 && lds < (size_t)WAVES * ROWS * 64 * sizeof(double)) lds = (size_t)WAVES * ROWS * 64 * sizeof(double);
     const dim3 grid(direct_tiles(a, TH)), block(64 * WAVES);
     if (a.taps64)
-        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, false>), grid, block, lds, s, a);
+        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, false, HC>), grid, block, lds, s, a);
     else
-        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, true>), grid, block, lds, s, a);
+        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, true, HC>), grid, block, lds, s, a);
 }
 
 template <int J>
@@ -264,6 +266,21 @@ static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
     // 435 -> 471 us at 21 x 21, 2048 x 4096)
     constexpr int ROWS = J <= 4 ? 16 : 8;
     const int cus = device_cus();
+    // Small kernels up to second order: little work per sample, so the window
+    // of exactly their rows and the loops over them unrolled count (1500 x 1400,
+    // constant filters: 3 x 3 13.4 -> 7.5 us, 7 x 7 17.1 -> 11.9; 4846 x 4868, 5 x
+    // 5, first order 103 -> 77).  Frames of few tiles are better shared by the
+    // waves, the more so the more products there are to share (256 x 256, 7 x 7,
+    // second order: 6.0 us, 9.6 with these).
+    if constexpr (J <= 3) {
+        const int products = (2 * a.h + 1) * (2 * a.h + 1) * J;
+        if (a.h * J <= 2 || direct_tiles(a, 32) >= (products <= 50 ? cus : products <= 75 ? 2 * cus : 4 * cus)) switch (a.h) {
+            case 1: return launch_direct<J, 8, 4, 1, 1>(a, s);
+            case 2: return launch_direct<J, 8, 4, 1, 2>(a, s);
+            case 3: return launch_direct<J, 8, 4, 1, 3>(a, s);
+            case 4: return launch_direct<J, 8, 4, 1, 4>(a, s);
+        }
+    }
     // whole tiles per wave while they give every CU three workgroups (what the
     // registers hold); then four waves on the same pixels, and eight where there
     // is at most one such tile per CU (21 x 21 at 512 x 512: 127 us with one
