@@ -49,10 +49,26 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
     return x * q + (x < r ? x : r) + (b >> 3);
 }
 
-// DFB: taps is a itself (float32), tap (m, dv, du) = a[(k^2 - 1 - (dv k + du)) M + m]
-// (the delta basis in correlation orientation); otherwise taps64[du][dv][m].
+// Where the taps are: TAPS_DELTA: in a itself (float32), tap (m, dv, du) =
+// a[(k^2 - 1 - (dv k + du)) M + m] (the delta basis in correlation orientation);
+// TAPS_TABLE: taps64[du][dv][m]; TAPS_FORMED: the same table in LDS, formed by
+// every workgroup.
+enum { TAPS_TABLE = 0, TAPS_DELTA = 1, TAPS_FORMED = 2 };
 // HC: the half-width where it is known at compile time, else 0.
-template <int J, int ROWS, int WAVES, int S, bool DFB, int HC>
+// Filter entry idx of M k^2 (m, then dv, du): sum_n a[n][m] F_n[dv][du], and its
+// place in a table [du][dv][m].
+__device__ __forceinline__ double regrouped_tap(const double* __restrict__ F64, const float* __restrict__ a, int N,
+                                                int M, int k, int idx, int& at) {
+    const int kk = k * k, m = idx / kk, q = idx - m * kk;
+    double s = 0.0;
+#pragma unroll 8
+    for (int n = 0; n < N; ++n) s += (double)a[n * M + m] * F64[(size_t)n * kk + q];
+    const int dv = q / k, du = q - dv * k;
+    at = (du * k + dv) * M + m;
+    return s;
+}
+
+template <int J, int ROWS, int WAVES, int S, int SRC, int HC>
 __global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs a) {
     constexpr int DS = J - 1, M = J * (J + 1) / 2;
     constexpr int NT = 64 * WAVES, TH = ROWS * WAVES / S;
@@ -66,6 +82,14 @@ __global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs 
     const int ty = tile_id / a.tiles_x, tx = tile_id - ty * a.tiles_x;
     const int X0 = tx * DR_TW, Y0 = ty * TH;
 
+    double* formed = reinterpret_cast<double*>(tile + a.taps_at);
+    if constexpr (SRC == TAPS_FORMED) {
+        for (int i = tid; i < M * K * K; i += NT) {
+            int at;
+            const double t = regrouped_tap(a.F64, a.coef, a.N, M, K, i, at);
+            formed[at] = t;
+        }
+    }
     // stage R, 0 outside the image: loads from clamped addresses, several rows
     // in flight, masks at the store.  First 64 columns of whole rows (scalar
     // row addresses), then the 2 h columns right of them.
@@ -115,15 +139,23 @@ __global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs 
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) acc[j][r] = 0.0;
 
-    // taps of a kernel pixel at a byte offset: uniform, so they arrive by scalar loads
+    // taps of a kernel pixel at a byte offset: uniform, so they arrive by scalar
+    // loads (or one LDS read for the whole wave)
+    constexpr bool DFB = SRC == TAPS_DELTA;
     typedef typename std::conditional<DFB, float, double>::type tap_t;
     struct Taps { tap_t v[M]; };
     const cptr<char> taps = (cptr<char>)(DFB ? (const void*)a.taps : (const void*)a.taps64);
     auto load_taps = [&](unsigned off) {
         Taps t;
-        const cptr<tap_t> p = (cptr<tap_t>)(taps + off);
+        if constexpr (SRC == TAPS_FORMED) {
+            const double* p = formed + off / sizeof(double);
 #pragma unroll
-        for (int m = 0; m < M; ++m) t.v[m] = p[m];
+            for (int m = 0; m < M; ++m) t.v[m] = p[m];
+        } else {
+            const cptr<tap_t> p = (cptr<tap_t>)(taps + off);
+#pragma unroll
+            for (int m = 0; m < M; ++m) t.v[m] = p[m];
+        }
         return t;
     };
     // byte offset of (dv, du), and from there to (dv + 1, du)
@@ -227,15 +259,11 @@ __global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs 
 // taps64[du][dv][m] = sum_n a[n][m] F_n[dv][du] (the regrouped filters)
 __global__ void regroup64_kernel(const double* __restrict__ F64, const float* __restrict__ a, int N, int M, int k,
                                  double* __restrict__ taps) {
-    const int kk = k * k;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= M * kk) return;
-    const int m = idx / kk, q = idx - m * kk;
-    double s = 0.0;
-#pragma unroll 8
-    for (int n = 0; n < N; ++n) s += (double)a[n * M + m] * F64[(size_t)n * kk + q];
-    const int dv = q / k, du = q - dv * k;
-    taps[(du * k + dv) * M + m] = s;
+    if (idx >= M * k * k) return;
+    int at;
+    const double t = regrouped_tap(F64, a, N, M, k, idx, at);
+    taps[at] = t;
 }
 
 int regroup_filters64(const double* F64, const float* a, int N, int M, int k, double* taps, hipStream_t s) {
@@ -245,18 +273,40 @@ int regroup_filters64(const double* F64, const float* a, int N, int M, int k, do
 
 static int direct_tiles(const DirectArgs& a, int th) { return a.tiles_x * ((a.H + th - 1) / th); }
 
+// Few bases on a small kernel and frame: the workgroups form the filters, in at
+// most a few rounds of loads each, which saves the launch before (whole calls in
+// the default form, 256 x 256: 3 x 3, six bases, second order 12.9 us with it,
+// 10.3 without; the dense product takes 10.1).  More rounds only where few
+// workgroups repeat them (700 x 760, 7 x 7, 22 bases, second order: 13.8 us with
+// the launch, 16.3 without).
+constexpr int FORMED_J = 3;
+
+bool direct_forms_taps(int H, int W, int h, int d_s, int N, int cus) {
+    const int M = (d_s + 1) * (d_s + 2) / 2, taps = M * (2 * h + 1) * (2 * h + 1);
+    const long tiles = (long)((W + DR_TW - 1) / DR_TW) * ((H + 31) / 32);
+    const int rounds = (taps + 255) / 256 * ((N + 7) / 8);
+    return d_s < FORMED_J && tiles <= 2L * cus && rounds <= (tiles <= cus && (N <= 8 || taps <= 75) ? 8 : 3);
+}
+
 template <int J, int ROWS, int WAVES, int S, int HC = 0>
-static void launch_direct(const DirectArgs& a, hipStream_t s) {
+static void launch_direct(DirectArgs a, hipStream_t s) {
     constexpr int TH = ROWS * WAVES / S;
     // the rows of the last window are read past the tile's 2 h halo rows, unused
     const int k = 2 * a.h + 1, rows = TH + (k + DR_CH - 1) / DR_CH * DR_CH - 1;
-    size_t lds = (size_t)rows * (DR_TW + 2 * a.h) * sizeof(float);
+    a.taps_at = (rows * (DR_TW + 2 * a.h) + 1) / 2 * 2;
+    size_t lds = (size_t)a.taps_at * sizeof(float) + (a.coef ? (size_t)k * k * J * (J + 1) / 2 * sizeof(double) : 0);
     if (S > 1 && lds < (size_t)WAVES * ROWS * 64 * sizeof(double)) lds = (size_t)WAVES * ROWS * 64 * sizeof(double);
     const dim3 grid(direct_tiles(a, TH)), block(64 * WAVES);
+    if constexpr (J <= FORMED_J) {
+        if (a.coef) {
+            hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, TAPS_FORMED, HC>), grid, block, lds, s, a);
+            return;
+        }
+    }
     if (a.taps64)
-        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, false, HC>), grid, block, lds, s, a);
-    else
-        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, true, HC>), grid, block, lds, s, a);
+        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, TAPS_TABLE, HC>), grid, block, lds, s, a);
+    else if (a.taps)
+        hipLaunchKernelGGL((contract_direct_kernel<J, ROWS, WAVES, S, TAPS_DELTA, HC>), grid, block, lds, s, a);
 }
 
 template <int J>
@@ -265,7 +315,7 @@ static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
     // (8 rows at second order: more waves, but 13 % more instructions per pixel,
     // 435 -> 471 us at 21 x 21, 2048 x 4096)
     constexpr int ROWS = J <= 4 ? 16 : 8;
-    const int cus = device_cus();
+    const int cus = a.cus;
     // Small kernels up to second order: little work per sample, so the window
     // of exactly their rows and the loops over them unrolled count (1500 x 1400,
     // constant filters: 3 x 3 13.4 -> 7.5 us, 7 x 7 17.1 -> 11.9; 4846 x 4868, 5 x
@@ -298,7 +348,8 @@ static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
 
 int launch_contract_direct(DirectArgs a, hipStream_t s) {
     a.tiles_x = (a.W + DR_TW - 1) / DR_TW;
-    if (a.h < 0 || a.h > kMaxHalfWidth || a.H <= 0 || a.W <= 0 || !a.taps == !a.taps64)
+    if (a.h < 0 || a.h > kMaxHalfWidth || a.H <= 0 || a.W <= 0 || a.cus <= 0 || !!a.taps + !!a.taps64 + !!a.coef != 1 ||
+        (a.coef && (!a.F64 || !direct_forms_taps(a.H, a.W, a.h, a.d_s, a.N, a.cus))))
         return fail(SVCONV_EUNSUPPORTED, "direct regrouped kernel: bad arguments");
     switch (a.d_s) {
         case 0: launch_direct_rows<1>(a, s); break;

@@ -130,11 +130,16 @@ struct DirectArgs {
     const float* I;             // nullable
     float* out;                 // [H][W]
     int H, W, h, d_s;
-    // exactly one of the two is set:
+    // exactly one of the three is set:
     const float* taps;          // Dirac delta basis: a [k^2][M]
-    const double* taps64;       // otherwise: regrouped filters [du][dv][M] (regroup_filters64)
+    const double* taps64;       // regrouped filters [du][dv][M] (regroup_filters64)
+    const float* coef;          // a [N][M]: the kernel forms the filters from F64 [N][k][k] (direct_forms_taps)
+    const double* F64;
+    int N;
     double sx, ox, sy, oy;
     int tiles_x;
+    int taps_at;                // where in LDS, in floats
+    int cus;                    // compute units
 };
 
 // The plan's vector scratch, in doubles: the vectors of a fit step or of
@@ -172,6 +177,7 @@ struct svconv_plan {
     float pedestal = 0.f;
     hipStream_t stream = nullptr;
     int device = 0;
+    int cus = 0;                        // its compute units
 
     std::vector<double> sigmas;
     std::vector<int> degrees;
@@ -278,6 +284,8 @@ int launch_contract_sepz(SepZArgs a, int precision, hipStream_t s);
 // direct.hip
 int regroup_filters64(const double* F64, const float* a, int N, int M, int k, double* taps, hipStream_t s);
 int launch_contract_direct(DirectArgs a, hipStream_t s);
+// whether the kernel had better form the filters of N bases itself
+bool direct_forms_taps(int H, int W, int h, int d_s, int N, int cus);
 
 // Both separable forms go through the one-dimensional factors in the adjoints
 // and the fit.

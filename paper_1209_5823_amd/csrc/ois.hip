@@ -504,7 +504,7 @@ int svconv_stamp_mask(svconv_plan* p, const float* R, double sky, double thresho
     const int cx = (p->W + CENTRE_TX - 1) / CENTRE_TX, cy = (p->H + CENTRE_TY - 1) / CENTRE_TY;
     const int halo = (r_iso > CENTRE_WHOLE ? CENTRE_NEAR : r_iso) + 1;
     const size_t lds = (size_t)(CENTRE_TX + 2 * halo) * (CENTRE_TY + 2 * halo) * sizeof(float);   // <= 37 KB
-    const bool few = (long)cx * cy <= device_cus(), far = r_iso > CENTRE_WHOLE;
+    const bool few = (long)cx * cy <= p->cus, far = r_iso > CENTRE_WHOLE;
     auto kernel = few ? (far ? centre_kernel<16, true> : centre_kernel<16, false>)
                       : (far ? centre_kernel<4, true> : centre_kernel<4, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)cx * cy), dim3(few ? 1024 : 256), lds, p->stream, R, p->H, p->W, sky,

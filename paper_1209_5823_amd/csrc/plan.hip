@@ -132,6 +132,7 @@ static int finish_plan(svconv_plan* p, svconv_plan** out) {
 
     int st = hip_status(hipGetDevice(&p->device), "hipGetDevice");
     if (st) { free_plan(p); return st; }
+    p->cus = device_cus();
 
     const int k = p->k, kk = k * k;
     // correlation-oriented tables: F_n[dv][du] = B_n[2h-dv][2h-du]
@@ -298,7 +299,7 @@ static bool direct_beats_separable(const svconv_plan* p) {
         for (int i = 0; i <= d; ++i) fold += window(d - i + 1);
     }
     fold += p->N * (p->d_s + 4.0);
-    const long tiles = (long)((p->W + 63) / 64) * ((p->H + 63) / 64), cus = device_cus();
+    const long tiles = (long)((p->W + 63) / 64) * ((p->H + 63) / 64), cus = p->cus;
     const double rounds = (double)((tiles + cus - 1) / cus);
     const double separable = rounds * (rounds > 2 ? 0.93 : 1.0) * (5.0 + 0.042 * fold);
     const double n = direct_count(p), direct = 10.0 + 0.006 * n + 3.5e-8 * n * p->H * p->W;
@@ -391,12 +392,14 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
     const bool split = p->precision == SVCONV_FP16X3 || p->precision == SVCONV_BF16X3 || p->precision == SVCONV_FP16X2;
     // Gaussian plans: the regrouped filters of the direct route, none where it is not taken
     double* taps = nullptr;
+    const bool formed = p->form == SVCONV_FORM_BASIS && !lowp && p->dTaps &&
+                        direct_forms_taps(p->H, p->W, p->h, p->d_s, p->N, p->cus);
     if (p->form == SVCONV_FORM_SEPARABLE ? !split && direct_beats_separable(p)
                                          : !lowp && p->form == SVCONV_FORM_REGROUPED)
         taps = reinterpret_cast<double*>(p->dFt32);
-    else if (p->form == SVCONV_FORM_BASIS && !lowp)
+    else if (p->form == SVCONV_FORM_BASIS && !lowp && !formed)
         taps = tap_slot(p);
-    if (taps || (p->dfb && !lowp)) {
+    if (taps || formed || (p->dfb && !lowp)) {
         // regrouped in float64 on the vector units.  The responses of a delta
         // basis are shifted pixels, so its basis form is the same sum anyhow.
         DirectArgs d{};
@@ -407,9 +410,14 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
         d.W = p->W;
         d.h = p->h;
         d.d_s = p->d_s;
+        d.cus = p->cus;
         d.sx = c.sx; d.ox = c.ox; d.sy = c.sy; d.oy = c.oy;
         if (p->dfb) {
             d.taps = a;
+        } else if (formed) {
+            d.coef = a;
+            d.F64 = p->dF64;
+            d.N = p->N;
         } else {
             int st = regroup_filters64(p->dF64, a, p->N, p->M, p->k, taps, p->stream);
             if (st) return st;
@@ -754,6 +762,7 @@ int svconv_backward(svconv_plan* p, const float* R, const float* a, const float*
         d.W = p->W;
         d.h = p->h;
         d.d_s = p->d_s;
+        d.cus = p->cus;
         d.taps64 = taps;
         d.sx = c.sx; d.ox = c.ox; d.sy = c.sy; d.oy = c.oy;
         st = launch_contract_direct(d, p->stream);

@@ -18,7 +18,9 @@ pytestmark = pytest.mark.gpu
 
 
 def _instance(name):
-    """(J, rows, waves, waves per pixel, delta basis, half-width) of a kernel's name."""
+    """(J, rows, waves, waves per pixel, source of the taps, half-width) of a kernel's
+    name; the source is 0 a table, 1 the coefficients of a delta basis, 2 formed by
+    the kernel."""
     assert "contract_direct_kernel" in name
     return tuple(int(v) for v in re.findall(r"L[ib](\d+)E", name))
 
@@ -79,3 +81,38 @@ def test_small_kernels(svc, orc, h, d_s, delta):
 @pytest.mark.parametrize("h,d_s", [(5, 0), (7, 1), (10, 2), (6, 3)])
 def test_wave_splits(svc, orc, shape, instance, h, d_s):
     assert _run(svc, orc, shape, h, d_s, False) == (d_s + 1,) + instance + (0, 0)
+
+
+# the default form: the kernel forms its filters (one launch, no table) up to 3
+# rounds of 256 entries x 8 bases, and up to 8 with few of either, on frames of at
+# most 512 tiles of 64 x 32 (256 for more than 3 rounds)
+@pytest.mark.parametrize("shape,h,deg,d_s,formed", [
+    ((1, 1), 0, (0,), 0, True), ((48, 40), 2, (2,), 2, True), ((64, 65), 5, (2,), 2, True),
+    ((256, 256), 7, (0,), 2, True), ((33, 129), 1, (6, 4, 2), 0, True), ((90, 70), 2, (4, 2, 0), 2, True),
+    ((90, 70), 3, (6, 4, 2), 2, False), ((8192, 63), 7, (0,), 1, True), ((8193, 64), 9, (0,), 1, False),
+    ((16384, 60), 2, (2,), 1, True), ((16385, 60), 2, (2,), 1, False), ((20, 49200), 1, (2,), 1, False),
+    ((30, 33000), 1, (2,), 1, False), ((30, 32768), 3, (1,), 0, True)])
+def test_filters_formed_by_the_kernel(svc, orc, shape, h, deg, d_s, formed):
+    import torch
+    H, W = shape
+    sig, frame = (0.9, 1.6, 2.4)[:len(deg)], (3, 2, W + 50, H + 60)
+    r = np.random.default_rng(H + W)
+    R = (1000 + 60 * r.normal(size=shape)).astype(np.float32)
+    I = (1000 + 60 * r.normal(size=shape)).astype(np.float32)
+    B = orc.basis(h, sig, deg)
+    a = r.normal(size=(len(B), synth.n_spatial(d_s))).astype(np.float32)
+    say("direct, filters of the kernel's own", shape, h, deg, d_s)
+    with svc.Plan(H, W, h, sig, deg, d_s, frame=frame, pedestal=1000.0) as plan:
+        Rd, Id, ad = to_dev(R), to_dev(I), to_dev(a)
+        out = torch.empty_like(Rd)
+        names = kernel_names(lambda: plan.difference(Rd, Id, ad, out=out))
+        assert len(names) == (1 if formed else 2)
+        assert (_instance(names[-1])[4] == 2) == formed
+        D = to_host(plan.difference(Rd, Id, ad))
+        plan.set_form("regrouped")
+        # the same filters through a table: the same bits
+        assert np.array_equal(to_host(plan.difference(Rd, Id, ad)), D)
+    xs, ys = sample_pixels(H, W, 400, seed=2, h=h)
+    want = orc.convolve_at(R, h, B, d_s, a, xs, ys, frame=frame) - I[ys, xs]
+    bound = 2.0 ** -24 * np.abs(want) * (1 + 1e-6) + 1e-12 * 1100.0 * np.abs(a).sum()
+    assert np.all(np.abs(D[ys, xs].astype(np.float64) - want) <= bound)
