@@ -316,19 +316,19 @@ static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
     // 435 -> 471 us at 21 x 21, 2048 x 4096)
     constexpr int ROWS = J <= 4 ? 16 : 8;
     const int cus = a.cus;
-    // Small kernels up to second order: little work per sample, so the window
+    // Small kernels up to second order (3 x 3 and 5 x 5 at third): little work per sample, so the window
     // of exactly their rows and the loops over them unrolled count (1500 x 1400,
     // constant filters: 3 x 3 13.4 -> 7.5 us, 7 x 7 17.1 -> 11.9; 4846 x 4868, 5 x
     // 5, first order 103 -> 77).  Frames of few tiles are better shared by the
     // waves, the more so the more products there are to share (256 x 256, 7 x 7,
     // second order: 6.0 us, 9.6 with these).
-    if constexpr (J <= 3) {
+    if constexpr (J <= 4) {
         const int products = (2 * a.h + 1) * (2 * a.h + 1) * J;
         if (a.h * J <= 2 || direct_tiles(a, 32) >= (products <= 50 ? cus : products <= 75 ? 2 * cus : 4 * cus)) switch (a.h) {
             case 1: return launch_direct<J, 8, 4, 1, 1>(a, s);
             case 2: return launch_direct<J, 8, 4, 1, 2>(a, s);
-            case 3: return launch_direct<J, 8, 4, 1, 3>(a, s);
-            case 4: return launch_direct<J, 8, 4, 1, 4>(a, s);
+            case 3: if constexpr (J <= 3) return launch_direct<J, 8, 4, 1, 3>(a, s); else break;
+            case 4: if constexpr (J <= 3) return launch_direct<J, 8, 4, 1, 4>(a, s); else break;
         }
     }
     // whole tiles per wave while they give every CU three workgroups (what the

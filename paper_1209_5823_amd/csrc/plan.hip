@@ -256,9 +256,12 @@ namespace svc {
 
 // Vector instructions per pixel of the direct float64 contraction (direct.hip):
 // k^2 taps with d_s + 1 products each and their folding over a thread's rows.
+// A single product per tap and sample (constant filters) does not hide the
+// reads and conversions of the window (0.4 instructions): 4096 x 4096, 11 x 11
+// 120 us, 15 x 15 195.
 static double direct_count(const svconv_plan* p) {
     const double J = p->d_s + 1, rows = J <= 4 ? 16 : 8;
-    return (double)p->k * p->k * (J + 1.5 * p->M / rows);
+    return (double)p->k * p->k * (J + 1.5 * p->M / rows + (p->d_s == 0 ? 0.4 : 0.0));
 }
 
 // Whether D of a plan in the basis or the separable form, at a precision that
@@ -281,11 +284,12 @@ static double direct_count(const svconv_plan* p) {
 // 21 x 21, 49 bases, second order 58 / 22, 59 / 52, 59 / 68; 15 x 15, 22 bases
 // 30 / 16, 30 / 33, 31 / 43; 31 x 31, third order 96 / 46, 95 / 143, 96 / 179;
 // 31 x 31, first order 76 / 28, 77 / 74, 78 / 90; 21 x 21 at 1024 x 1400, two
-// rounds, 112 / 96.  Both times are modelled on these.  On frames of many
-// rounds, whose tiles overlap, the two are even at 21 x 21 (2048 x 4096: 437 /
-// 431 in a loop of its own, 480 / 514 right after other kernels, when the
-// higher rate of float64 products lowers the clock), and the model leaves them
-// to the separable kernel.
+// rounds, 112 / 96.  Both times are modelled on these.  The tiles of more than
+// two rounds overlap, which counts them at 0.93: over 924 calls (1.5 to 16
+// Mpixel, 3 x 3 to 31 x 31, 1 to 64 bases, every order) the direct kernel is then
+// taken once where it is the slower by more than 4 % (three times at 1, which
+// also sends 21 x 21 on 2000 x 3000 to it, 343 us against 331), and the time lost
+// to the better of the two is 0.36 % in the mean (0.30 at 1, 0.53 at 0.9).
 static bool direct_beats_basis(const svconv_plan* p) {
     const double dense = (p->N <= 8 ? 0.25 / 0.6 : 0.5 / 0.55 * ((p->N + 15) / 16)) * p->k * p->k;
     return direct_count(p) * 4.25 / 64 / 0.72 < dense;
