@@ -581,7 +581,8 @@ int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const u
 // Workgroups still read the lower triangle of the block column while others
 // finish it, so the results go where nobody reads: L21^T and the strict lower
 // part of L11, transposed, into the upper triangle, the diagonal into `diag`.
-// chol_finish_kernel moves them to their places and clears the upper triangle.
+// chol_finish_kernel moves them to their places and clears the upper triangle
+// (a matrix of one block is written in place: n = 6 39.1 -> 32.5 us a call).
 constexpr int CH_NB = 32;
 
 // v of lane `l` (uniform), through scalar registers
@@ -650,6 +651,7 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* __restrict__ A, 
         double my_inv = 1.0;
 #pragma unroll
         for (int j = 0; j < CH_NB; ++j) {
+            if (j % 8 == 0 && j >= nb) break;   // uniform: a short block's identity rows need no pivots
             double d = lane_value(row[j], j);
             if (!(d > 0.0) || !isfinite(d)) {   // uniform
                 if (!bad) bad = k0 + j + 1;
@@ -679,6 +681,14 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* __restrict__ A, 
         }
     }
     __syncthreads();
+    if (n <= CH_NB) {   // uniform: the whole matrix, and no other workgroup reads it
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = rq + 8 * i;
+            if (r < n && cc < n) A[(size_t)r * n + cc] = L11[r][cc];
+        }
+        return;
+    }
     if (blockIdx.x == 0) {
         if (tid < nb) diag[k0 + tid] = L11[tid][tid];
 #pragma unroll
@@ -758,10 +768,12 @@ int launch_cholesky(svconv_plan* p, double* A, int n) {
         st = hip_status(hipGetLastError(), "chol_step_kernel");
     }
     if (st) return st;
-    const int nt = (n + 31) / 32;
-    hipLaunchKernelGGL(chol_finish_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, p->stream, A, n, diag);
-    st = hip_status(hipGetLastError(), "chol_finish_kernel");
-    if (st) return st;
+    if (n > CH_NB) {
+        const int nt = (n + 31) / 32;
+        hipLaunchKernelGGL(chol_finish_kernel, dim3(nt * (nt + 1) / 2), dim3(256), 0, p->stream, A, n, diag);
+        st = hip_status(hipGetLastError(), "chol_finish_kernel");
+        if (st) return st;
+    }
     int bad = 0;
     st = hip_status(hipMemcpyAsync(&bad, p->dStatus, sizeof(int), hipMemcpyDeviceToHost, p->stream),
                     "copy status");

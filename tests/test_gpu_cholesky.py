@@ -45,3 +45,23 @@ def test_pivot_is_reported(svc, n, pivot):
         assert "pivot %d " % pivot in str(ei.value)
         # the status does not outlive the call
         plan.cholesky_factor(torch.from_numpy(np.eye(n)).cuda())
+
+
+@pytest.mark.parametrize("n", [1, 3, 6, 16, 31, 32, 33])
+def test_one_block_is_written_in_place(svc, n):
+    """One launch up to n = 32: the factor below the diagonal, zeros above it, and
+    nothing past the matrix."""
+    import torch
+    r = np.random.default_rng(n)
+    X = r.normal(size=(3 * n, n))
+    A = X.T @ X
+    say("cholesky, one block", n)
+    buf = torch.full((n * n + 40,), 7.0, dtype=torch.float64).cuda()
+    with svc.Plan(8, 8, 1, (1.0,), (0,), 0) as plan:
+        M = buf[:n * n].view(n, n)
+        M.copy_(torch.from_numpy(np.where(np.tril(np.ones((n, n))) > 0, A, np.nan)))
+        plan.cholesky_factor(M)
+        L, Lref = to_host(M), np.linalg.cholesky(A)
+    assert np.max(np.abs(L - Lref)) <= 8 * n * np.finfo(np.float64).eps * np.abs(Lref).max()
+    assert np.array_equal(np.triu(L, 1), np.zeros((n, n)))
+    assert bool((buf[n * n:] == 7.0).all())
