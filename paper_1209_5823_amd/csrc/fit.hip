@@ -593,20 +593,29 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 }
 
 // root = sqrt(d) and inv = 1 / sqrt(d) for finite d > 0, by Goldschmidt's
-// iteration from the hardware's estimate (both within an ulp or two); the
-// library's square root and division after one another are 40 dependent
-// instructions, the larger part of a pivot's latency.
+// iteration from the hardware's estimate, which is within 2^-23: two steps take
+// that past 2^-52 (1.5 e^2 each), and the root is corrected by its remainder.
+// inv is within an ulp or two, which quotient() makes up for.  The library's
+// square root and division after one another are 40 dependent instructions,
+// the larger part of a pivot's latency.
 __device__ __forceinline__ void sqrt_both(double d, double& root, double& inv) {
     const double y = __builtin_amdgcn_rsq(d);
     double g = d * y, h = 0.5 * y;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < 2; ++i) {
         const double r = fma(-h, g, 0.5);
         g = fma(g, r, g);
         h = fma(h, r, h);
     }
     root = fma(fma(-g, g, d), h, g);
     inv = h + h;
+}
+
+// v / piv from inv = 1 / piv within an ulp or two: the remainder of v inv,
+// formed exactly, corrects it to the rounded quotient but for rare last bits.
+__device__ __forceinline__ double quotient(double v, double piv, double inv) {
+    const double x = v * inv;
+    return fma(fma(-x, piv, v), inv, x);
 }
 
 __global__ __launch_bounds__(256) void chol_step_kernel(double* __restrict__ A, int n, int k0,
@@ -648,7 +657,7 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* __restrict__ A, 
 #pragma unroll
         for (int c = 0; c < CH_NB; ++c) row[c] = L11[r][c];
         int bad = 0;
-        double my_inv = 1.0;
+        double my_inv = 1.0, my_piv = 1.0;
 #pragma unroll
         for (int j = 0; j < CH_NB; ++j) {
             if (j % 8 == 0 && j >= nb) break;   // uniform: a short block's identity rows need no pivots
@@ -659,14 +668,17 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* __restrict__ A, 
             }
             double piv, q;
             sqrt_both(d, piv, q);
-            if (r == j) my_inv = q;
-            row[j] = r == j ? piv : row[j] * q;
+            if (r == j) {
+                my_inv = q;
+                my_piv = piv;
+            }
+            row[j] = r == j ? piv : quotient(row[j], piv, q);
             // entries above the diagonal become meaningless and are never read
 #pragma unroll
             for (int c = j + 1; c < CH_NB; ++c) row[c] = fma(-row[j], lane_value(row[j], c), row[c]);
         }
         if (tid < 32) {
-            inv[r] = my_inv;
+            inv[r] = quotient(1.0, my_piv, my_inv);
 #pragma unroll
             for (int c = 0; c < CH_NB; ++c) {
                 const double v = c <= r ? row[c] : 0.0;
@@ -726,10 +738,10 @@ __global__ __launch_bounds__(256) void chol_step_kernel(double* __restrict__ A, 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int r = rq + 8 * i, gi = r0 + r, gj = c0 + cc;
-        double s = 0.0;
+        double s = a22[i];
 #pragma unroll
-        for (int t = 0; t < CH_NB; ++t) s = fma(P[0][r][t], Pj[cc][t], s);
-        if (gi < n && gj <= gi) A[(size_t)gi * n + gj] = a22[i] - s;
+        for (int t = 0; t < CH_NB; ++t) s = fma(-P[0][r][t], Pj[cc][t], s);
+        if (gi < n && gj <= gi) A[(size_t)gi * n + gj] = s;
     }
 }
 

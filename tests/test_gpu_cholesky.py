@@ -65,3 +65,33 @@ def test_one_block_is_written_in_place(svc, n):
     assert np.max(np.abs(L - Lref)) <= 8 * n * np.finfo(np.float64).eps * np.abs(Lref).max()
     assert np.array_equal(np.triu(L, 1), np.zeros((n, n)))
     assert bool((buf[n * n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("n", [33, 64, 96, 132])
+def test_backward_error_of_plain_elimination(svc, n):
+    """The factor's residual A - L L^T is no larger than that of column-by-column
+    elimination in float64 (one rounding per operation): blocks, reciprocals and
+    the square root's iteration lose nothing.  Root mean square over matrices of
+    condition 1e8 to 1e11 whose rows are scaled over six decades."""
+    import torch
+    say("cholesky residual", n)
+    r = np.random.default_rng(n)
+    rms = {"plain": 0.0, "gpu": 0.0}
+    with svc.Plan(8, 8, 1, (1.0,), (0,), 0) as plan:
+        for cond in (8, 9, 10, 11):
+            q, _ = np.linalg.qr(r.normal(size=(n, n)))
+            s = 10.0 ** r.uniform(-3, 3, n)
+            A = (q * 10.0 ** np.linspace(0, -cond, n)) @ q.T * s[:, None] * s[None, :]
+            A = (A + A.T) / 2
+            P = A.copy()
+            for j in range(n):
+                P[j, j] = np.sqrt(P[j, j])
+                P[j + 1:, j] /= P[j, j]
+                P[j + 1:, j + 1:] -= np.outer(P[j + 1:, j], P[j + 1:, j])
+            G = to_host(plan.cholesky_factor(torch.from_numpy(A.copy()).cuda()))
+            for name, L in (("plain", np.tril(P)), ("gpu", G)):
+                L = L.astype(np.longdouble)
+                d = np.sqrt(np.diag(A).astype(np.longdouble))
+                rms[name] += float(np.mean(((A - L @ L.T) / d[:, None] / d[None, :]) ** 2))
+    say("  ", rms)
+    assert rms["gpu"] <= rms["plain"]
