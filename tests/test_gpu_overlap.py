@@ -86,14 +86,17 @@ def test_streams_overlap(svc):
             assert np.array_equal(to_host(got), want)
 
 
-def test_more_captures_than_tables(svc, orc):
-    """Past the last table a call takes the dense product, which needs none; the
-    streams that hold one keep it."""
+@pytest.mark.parametrize("deg", [DEG, (4, 2, 0), (7,), (3,)])
+def test_more_captures_than_tables(svc, orc, deg):
+    """Past the last table a call takes the dense product, which needs none (49, 22,
+    36 and 10 bases: each number of its 16-filter blocks); the streams that hold one
+    keep it."""
     import torch
-    R, I, a = _case(1)
-    Rd, Id, ad = to_dev(R), to_dev(I), to_dev(a[0])
-    say("captures past the last table")
-    with _plan(svc) as plan:
+    R, I, sig = *_case(0)[:2], SIG[:len(deg)]
+    a = synth.coefficients(synth.n_basis(deg), synth.n_spatial(DS), 0, seed=1)
+    Rd, Id, ad = to_dev(R), to_dev(I), to_dev(a)
+    say("captures past the last table", deg)
+    with svc.Plan(H, W, HALF, sig, deg, DS, pedestal=1000.0) as plan:
         first, out = to_host(plan.difference(Rd, Id, ad)), torch.empty_like(Rd)
         tables = [_table(capture(lambda: plan.difference(Rd, Id, ad, out=out))) for _ in range(70)]
         had = [t for t in tables if t is not None]
@@ -103,7 +106,7 @@ def test_more_captures_than_tables(svc, orc):
         assert any("contract_f32_kernel" in k.name for k in kernels(dense))
         dense.instantiate()
         dense.replay()
-        want = orc.difference(R, I, HALF, orc.basis(HALF, SIG, DEG), DS, a[0])
+        want = orc.difference(R, I, HALF, orc.basis(HALF, sig, deg), DS, a)
         assert err_stats(to_host(out), want)[0] <= TOL_FP32
         assert np.array_equal(to_host(plan.difference(Rd, Id, ad)), first)
 
