@@ -602,6 +602,9 @@ int launch_adjoint_a_sep_mma(SepArgs a, const uint16_t* frag, int precision, con
 constexpr int SA_NC = 3, SA_NP = 3;       // columns and row pairs per thread
 static_assert(SM_XR == 32 * SA_NC && SM_XR / 2 == 16 * SA_NP && SM_NW == 8, "E entries must spread evenly over the threads");
 constexpr size_t SA_LDS = SM_LDS;         // 77 KB: two workgroups per CU
+// The passes run on G / 2: the hi part of a float32 within 0.4 % of the largest
+// would round to an infinite bf16 (clamping the parts instead took 1.4 % longer).
+constexpr float SA_UNSCALE = 2.f;
 
 template <int DSM>
 __global__ __launch_bounds__(SM_NT, SM_MINW) void adjoint_r_sepmm_kernel(SepArgs a, const uint16_t* __restrict__ frag) {
@@ -652,7 +655,8 @@ __global__ __launch_bounds__(SM_NT, SM_MINW) void adjoint_r_sepmm_kernel(SepArgs
 #pragma unroll
             for (int c = 0; c < SA_NC; ++c) {
                 const int xq = 32 * c + w + 8 * g4, gx = X0 - h + xq;
-                if (!(xq < CA && yq < CA && gx >= 0 && gx < a.W && gy >= 0 && gy < a.H)) gv[c][s][e] = 0.f;
+                const bool in = xq < CA && yq < CA && gx >= 0 && gx < a.W && gy >= 0 && gy < a.H;
+                gv[c][s][e] = in ? 0.5f * gv[c][s][e] : 0.f;   // see SA_UNSCALE
             }
         }
     smm_f4 accR[2];   // dR blocks w and w + 8 of the 4 x 4 output blocks
@@ -782,7 +786,7 @@ __global__ __launch_bounds__(SM_NT, SM_MINW) void adjoint_r_sepmm_kernel(SepArgs
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int y = Y0 + 16 * rb + 4 * g4 + e;
-            if (x < a.W && y < a.H) a.out[(size_t)y * a.W + x] = accR[k][e];
+            if (x < a.W && y < a.H) a.out[(size_t)y * a.W + x] = SA_UNSCALE * accR[k][e];
         }
     }
 }

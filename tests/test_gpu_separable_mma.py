@@ -208,3 +208,25 @@ def test_adjoint_a_mma_edge_cases(svc, orc, name):
     e = np.abs(ga - ga_ref)
     say("  max err %.3e (scale %.3e)" % (e.max(), sa.max()))
     assert np.all(e <= MMA_ADJ_A_REL * sa + 1e-9)
+
+
+@pytest.mark.parametrize("d_s", [1, 3, 4, 6])
+def test_adjoint_R_mma_of_the_largest_float32(svc, orc, d_s):
+    """Gradients up to the largest float32, whose bf16 hi part must not round to
+    infinity: the bf16 parts keep 2^-17 each, so 2e-5 of the magnitude sums."""
+    import torch
+    H, W, h, sig, deg = 70, 90, 4, (1.1, 2.2), (2, 1)
+    B = orc.basis(h, sig, deg)
+    a = 0.1 * np.random.default_rng(d_s).uniform(-1, 1, (len(B), synth.n_spatial(d_s))).astype(np.float32)
+    a[0, 0] = 1.0
+    G = np.zeros((H, W), np.float32)
+    most = np.finfo(np.float32).max
+    G[10, 10], G[40, 63], G[41, 80], G[69, 5] = most, -most, np.float32(most * 0.997), 1e30
+    want = orc.grad_R((H, W), h, B, d_s, a, G)
+    sR = orc.grad_R((H, W), h, np.abs(B), 0, np.abs(a).sum(axis=1, keepdims=True), np.abs(G))
+    say("adjoint in R at the largest float32", d_s)
+    R = torch.zeros((H, W), device="cuda")
+    with svc.Plan(H, W, h, sig, deg, d_s, form="separable", precision="bf16x3") as plan:
+        gR = to_host(plan.backward(R, to_dev(a), to_dev(G), want_ga=False)[0]).astype(np.float64)
+    assert np.all(np.isfinite(gR))
+    assert np.all(np.abs(gR - want) <= 2e-5 * sR)
