@@ -256,12 +256,9 @@ namespace svc {
 
 // Vector instructions per pixel of the direct float64 contraction (direct.hip):
 // k^2 taps with d_s + 1 products each and their folding over a thread's rows.
-// A single product per tap and sample (constant filters) does not hide the
-// reads and conversions of the window (0.4 instructions): 4096 x 4096, 11 x 11
-// 120 us, 15 x 15 195.
 static double direct_count(const svconv_plan* p) {
     const double J = p->d_s + 1, rows = J <= 4 ? 16 : 8;
-    return (double)p->k * p->k * (J + 1.5 * p->M / rows + (p->d_s == 0 ? 0.4 : 0.0));
+    return (double)p->k * p->k * (J + 1.5 * p->M / rows);
 }
 
 // Whether D of a plan in the basis or the separable form, at a precision that
@@ -287,9 +284,12 @@ static double direct_count(const svconv_plan* p) {
 // rounds, 112 / 96.  Both times are modelled on these.  The tiles of more than
 // two rounds overlap, which counts them at 0.93: over 924 calls (1.5 to 16
 // Mpixel, 3 x 3 to 31 x 31, 1 to 64 bases, every order) the direct kernel is then
-// taken once where it is the slower by more than 4 % (three times at 1, which
-// also sends 21 x 21 on 2000 x 3000 to it, 343 us against 331), and the time lost
-// to the better of the two is 0.36 % in the mean (0.30 at 1, 0.53 at 0.9).
+// taken once where it is the slower by more than 4 % (six times at 1, which also
+// sends 21 x 21 on 2000 x 3000 to it, 343 us against 331), and the time lost to
+// the better of the two is 0.34 % in the mean (0.31 at 1, 0.45 at 0.9).  On such
+// frames constant filters, one product per tap and sample, do not quite hide the
+// reads of the window (0.1 per tap): 11 x 11, one base, 4096 x 4096 105 us
+// through the factors and 120 directly, 15 x 15, six bases 178 and 198.
 static bool direct_beats_basis(const svconv_plan* p) {
     const double dense = (p->N <= 8 ? 0.25 / 0.6 : 0.5 / 0.55 * ((p->N + 15) / 16)) * p->k * p->k;
     return direct_count(p) * 4.25 / 64 / 0.72 < dense;
@@ -306,7 +306,8 @@ static bool direct_beats_separable(const svconv_plan* p) {
     const long tiles = (long)((p->W + 63) / 64) * ((p->H + 63) / 64), cus = p->cus;
     const double rounds = (double)((tiles + cus - 1) / cus);
     const double separable = rounds * (rounds > 2 ? 0.93 : 1.0) * (5.0 + 0.042 * fold);
-    const double n = direct_count(p), direct = 10.0 + 0.006 * n + 3.5e-8 * n * p->H * p->W;
+    const double reads = p->d_s == 0 && rounds > 2 ? 0.1 * p->k * p->k : 0.0;
+    const double n = direct_count(p) + reads, direct = 10.0 + 0.006 * n + 3.5e-8 * n * p->H * p->W;
     return direct < separable;
 }
 
