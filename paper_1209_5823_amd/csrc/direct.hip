@@ -23,8 +23,8 @@
 // of the cycles).  7 x 7 delta basis, second order, 4846 x 4868: 315 us
 // (float32 FMAs over six terms, float64 row sums) -> 182 us, error against
 // float64 4.0e-8 -> 2.5e-8 of D; 21 x 21, 49 bases, second order, 2048 x 4096:
-// 741 us (float32 matrix cores) -> 432 us; 31 x 31, third order, 2048 x 2048:
-// 1323 -> 715 us.
+// 741 us (float32 matrix cores) -> 450 us (482 with two sets of taps); 31 x 31,
+// third order, 2048 x 2048: 1323 -> 632 us.
 //
 // Per kernel column du and DR_CH kernel rows (an item), the samples the
 // thread's rows need are read from LDS once and widened.  ROWS = 16 rows per
@@ -312,8 +312,8 @@ static void launch_direct(DirectArgs a, hipStream_t s) {
 template <int J>
 static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
     // above third order the totals of 16 rows no longer fit the registers.
-    // (8 rows at second order: more waves, but 13 % more instructions per pixel,
-    // 435 -> 471 us at 21 x 21, 2048 x 4096)
+    // (8 rows at second order: more waves, but 13 % more instructions per pixel;
+    // 21 x 21, 2048 x 4096, with two sets of taps 435 -> 471 us)
     constexpr int ROWS = J <= 4 ? 16 : 8;
     const int cus = a.cus;
     // Small kernels up to second order (3 x 3 and 5 x 5 at third): little work per sample, so the window
@@ -333,11 +333,11 @@ static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
     }
     // whole tiles per wave while they give every CU three workgroups (what the
     // registers hold); then four waves on the same pixels, and eight where there
-    // is at most one such tile per CU (21 x 21 at 512 x 512: 127 us with one
-    // wave per 4 rows, 37 us with four on 16 rows, 26 us with eight; at 517 x
-    // 771, 429 tiles, 40 us with four, 47 us with eight).  A 3 x 3 or 5 x 5
-    // kernel has no eight items to share.  Tiles of half the rows where even
-    // those give a CU at most one (256 x 256: 23 -> 19 us).
+    // is at most one such tile per CU (21 x 21 at 512 x 512, 256 tiles: 34 us with
+    // four on 16 rows, 24 us with eight; at 700 x 760, 528 tiles, 49 us with four,
+    // 58 us with eight).  A 3 x 3 or 5 x 5 kernel has no eight items to share.
+    // Tiles of half the rows where even those give a CU at most one (256 x 256:
+    // 23 -> 20 us).
     if (direct_tiles(a, 4 * ROWS) >= 3 * cus) return launch_direct<J, ROWS, 4, 1>(a, s);
     if (direct_tiles(a, ROWS) > cus || a.h < 3) return launch_direct<J, ROWS, 4, 4>(a, s);
     if constexpr (ROWS == 16) {

@@ -1,8 +1,10 @@
 // Least-squares fit of the coefficients (Optimal Image Subtraction, Sec. 2):
 // loss and its gradient in D, the float64 normal matrix, an in-place
 // Cholesky factorisation, the two triangular solves and the Gauss-Newton
-// update.  Everything here is float64 except the basis responses, which come
-// from the float32 matrix-core contraction.
+// update.  Everything here is float64 except the planes of basis responses,
+// which are held in float32: those of the dense forms come from the float32
+// matrix-core contraction, those of the separable forms are formed in float64
+// and rounded once, and those of a delta basis without a mask are pixels of R.
 //
 // Normal matrix.  With Phi[p][(n,m)] = P_m(p) T_n(p),
 //   JtJ[(n,m)][(n',m')] = sum_p mask(p) T_n(p) T_n'(p) P_m(p) P_m'(p),
@@ -576,10 +578,10 @@ int launch_normal_matrix(svconv_plan* p, const float* R, const float* I, const u
 // block in every workgroup costs nothing (they run side by side) and saves the
 // launch between panel and update; it is done by one wave with a row per lane
 // in registers, entries of other rows broadcast by v_readlane.
-// Bound: the serial chain of the 32 pivots (a square root, a reciprocal and a
-// rank-1 update each).  n = 294: 430 us (panel kernel with 4 barriers per
-// column 34 us a block, then an update kernel) -> 200 us with the host's launches
-// and status copy; n = 735: 1420 -> 420 us.
+// Bound: the serial chain of the 32 pivots (a square root, a quotient and a
+// rank-1 update each).  n = 294: 443 us (panel kernel with 4 barriers per
+// column 34 us a block, then an update kernel) -> 196 us with the host's launches
+// and status copy; n = 735: 1420 -> 422 us.
 //
 // Workgroups still read the lower triangle of the block column while others
 // finish it, so the results go where nobody reads: L21^T and the strict lower
@@ -805,9 +807,11 @@ int launch_cholesky(svconv_plan* p, double* A, int n) {
 // hr + 16) and stage its triangle and the 32 x 32 piece that meets the block
 // being solved, which wave 0 applies itself: one barrier per block.
 // Bound: the serial chain of the triangles, about 100 cycles per unknown.  n =
-// 294: 80 us (panels after triangles, every thread a row of its own with 64
-// cache lines per load) -> 34 us; n = 735: 228 -> 124 us.  With a64, the Newton update is applied
-// at the end: a64 -= x, a32 = float(a64), norm = ||x||_2.
+// 294: 78 us (panels after triangles, every thread a row of its own with 64
+// cache lines per load) -> 33 us; n = 735: 227 -> 124 us, in a loop over a factor
+// that stays in L2 (306 -> 204 us where each iteration's images displace it).
+// With a64, the Newton update is applied at the end: a64 -= x, a32 =
+// float(a64), norm = ||x||_2.
 constexpr int CS_B = 32, CS_HELPERS = 512, CS_NT = 64 + CS_HELPERS;
 
 __global__ __launch_bounds__(CS_NT) void chol_solve_kernel(const double* __restrict__ L,

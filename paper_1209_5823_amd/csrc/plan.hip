@@ -270,7 +270,7 @@ static double direct_count(const svconv_plan* p) {
 // pixel and 16 filters (0.25 with at most 8 filters, which pack two rows) and
 // keeps the matrix cores busy for 55 to 60 % of the time, a vector instruction
 // 4.25 / 64 cycles at 72 %.  Measured at 2048 x 4096, 21 x 21, 49 bases, second
-// order: 6.37 ms densely, 0.43 ms directly; 1021 x 1533: 1206 and 94 us; error
+// order: 6.37 ms densely, 0.45 ms directly; 1021 x 1533: 1206 and 89 us; error
 // against float64 3.7e-8 and 2.5e-8 of D.  Few filters on many spatial terms (8
 // at third order) stay dense.
 //
@@ -278,10 +278,10 @@ static double direct_count(const svconv_plan* p) {
 // its time is the number of rounds of 256 tiles times one tile's chain; it
 // does less work per pixel, but up to a few hundred tiles the direct kernel is
 // better spread (us, separable and direct, 256 x 256, 700 x 760, 900 x 1000):
-// 21 x 21, 49 bases, second order 58 / 22, 59 / 52, 59 / 68; 15 x 15, 22 bases
-// 30 / 16, 30 / 33, 31 / 43; 31 x 31, third order 96 / 46, 95 / 143, 96 / 179;
-// 31 x 31, first order 76 / 28, 77 / 74, 78 / 90; 21 x 21 at 1024 x 1400, two
-// rounds, 112 / 96.  Both times are modelled on these.  The tiles of more than
+// 21 x 21, 49 bases, second order 58 / 20, 59 / 49, 59 / 62; 15 x 15, 22 bases
+// 30 / 14, 30 / 30, 31 / 39; 31 x 31, third order 96 / 42, 95 / 129, 96 / 162;
+// 31 x 31, first order 76 / 26, 77 / 71, 78 / 89; 21 x 21 at 1024 x 1400, two
+// rounds, 112 / 88.  Both times are modelled on these.  The tiles of more than
 // two rounds overlap, which counts them at 0.93: over 924 calls (1.5 to 16
 // Mpixel, 3 x 3 to 31 x 31, 1 to 64 bases, every order) the direct kernel is then
 // taken once where it is the slower by more than 4 % (six times at 1, which also
@@ -708,9 +708,12 @@ static int run_adjoint_a(svconv_plan* p, const float* R, const float* gD, double
 // and its halo and a column pass, and a row pass per factor; directly, k^2 taps
 // with d_s + 1 products each and their folding.  Both kernels keep the vector
 // units busy for two to three quarters of the time (measured at 4096^2, 31 x
-// 31, 49 bases, third order: 4.74 ms through the factors, 2.9 ms directly; at
-// 517 x 771, 21 x 21, second order: 357 and 24 us), so the counts decide; few
-// bases on a wide kernel (10 at 31 x 31) stay with the factors.
+// 31, 49 bases, third order: 4.74 ms through the factors, 2.4 ms directly), so
+// the counts decide; few bases on a wide kernel (10 at 31 x 31) stay with the
+// factors.  Frames that do not fill the chip with the factors' 64 x 64 tiles gain
+// more (517 x 771, 21 x 21, second order: 357 and 23 us), which the counts do not
+// see: where they leave such a frame to the factors (31 x 31, fourth order, 256 x
+// 256: 512 us, directly 53) it stays there.
 static bool adjoint_r_direct(const svconv_plan* p) {
     const double k = p->k, halo = 1.0 + p->h / 32.0;
     int factors = 0;

@@ -40,13 +40,16 @@
 // pedestal restore s sum_m gamma_m P_m and the subtraction of I in float32
 // (sum_m P_m Z_m - I first, which is exact where both are large).
 //
-// Workgroup: 4 waves; output tile 64 x 64; wave w owns the 16-column strip
-// w and every row of the tile.  LDS holds the staged tile (hi / lo rows
-// [96][88]) and, per wave, the second factor's row responses while the
-// first one's column passes run (written and read by the same lanes, so no
-// barrier).  Workgroups are persistent, two per compute unit (the chip's
-// 2048 tiles fall evenly on 512 workgroups); the only barriers are the ends
-// of staging.
+// Workgroup (SzTile<OB, SP>): output tile 64 x 8 OB in four 16-column strips,
+// each of SP waves.  With SP = 1 a wave owns its strip and every row of the
+// tile; with SP = 4 (small frames) the waves of a strip take every fourth pair
+// of row factors, and their sums are added through LDS at the end.  LDS holds
+// the staged tile (hi / lo rows [SzTile::XR][88]) and, per wave, the second
+// factor's row responses while the first one's column passes run (written and
+// read by the same lanes, so no barrier).  Workgroups are persistent, as many
+// per compute unit as the registers allow (at OB = 8 two, on which the chip's
+// 2048 tiles of 64 x 64 fall evenly; with SP = 4 one); the only barriers are the
+// ends of staging and, with SP > 1, the two around the strips' sums.
 #include "internal.hpp"
 #include "sep_fold.hpp"
 
@@ -411,8 +414,8 @@ __device__ __forceinline__ void sz_colpass(sz_f4 (&Z)[OB], const uint32_t (&Uh)[
     }
 }
 
-// Staging of one tile, row by row: wave w stages rows w, w + 4, ... of the
-// [SZ_XR][SZ_XC] window, lane l < SZ_XC / 2 the columns 2 l, 2 l + 1.  The row
+// Staging of one tile, row by row: wave w of the SzTile::NW stages rows w, w +
+// NW, ... of the [SzTile::XR][SZ_XC] window, lane l < SZ_XC / 2 the columns 2 l, 2 l + 1.  The row
 // is uniform across the wave, so a row's address is scalar work and a lane's
 // column offset (clamped into the image) is formed once per tile; no load is
 // conditional, so all of them are in flight together.  Samples outside the
