@@ -38,9 +38,14 @@ namespace svc {
 // L2.  In one step the halo of r_iso = 64 takes 123 KiB of LDS (four waves per
 // CU) and 15 times the tile, and every scan starts at the far corner: crowded
 // fields (sky noise above 0.6 sigma, frac 0.1) at r_iso = 64 took 911 us at 64
-// x 64 and 3714 at 2048 x 4096, now 45 and 151 (whole calls).
+// x 64 and 3714 at 2048 x 4096, now 45 and 151 (whole calls).  A frac above 1
+// takes the second step alone (1200 x 1600, frac 3, r_iso = 25: 420 us, 600 with both).
 // A wave takes the candidates of its rows one after the other, so on frames of
-// at most one tile per CU 16 waves share a tile.
+// at most two tiles per CU, which two workgroups of 16 waves fill, 16 waves
+// share a tile: the field above at 700 x 900, r_iso = 10 and 24, took 71 and
+// 169 us with four waves, 56 and 56 with 16.  Windows above CENTRE_NEAR scanned
+// whole do so up to four tiles per CU (1200 x 1600, r_iso = 24: 163 and 74); on
+// larger frames the staging is what counts (chip, 20,000 stars: 73 and 80).
 constexpr int CENTRE_TX = 64, CENTRE_TY = 32, CENTRE_WHOLE = 24, CENTRE_NEAR = 16, CENTRE_FAR = 4;
 constexpr int COUNT_SLOTS = 64, COUNT_STRIDE = 32;   // counters on 128-byte lines of their own
 
@@ -126,6 +131,7 @@ __global__ __launch_bounds__(64 * NW) void centre_kernel(const float* __restrict
     const int x = x0 + lane;
     const bool inx = x < W && x >= margin && x <= W - 1 - margin;
     constexpr int ROWS = CENTRE_TY / NW;
+    constexpr bool CLIP = NW != 4 || FAR;
     const float* mine = tile + (wave * ROWS + halo) * pitch + lane + halo;
     float v[ROWS];
 #pragma unroll
@@ -139,10 +145,11 @@ __global__ __launch_bounds__(64 * NW) void centre_kernel(const float* __restrict
         if (__any(above)) {
             const float* here = mine + r * pitch;
             found = __ballot(above && strict_local_max(here, pitch));
-            // isolation: the wave scans the window's rows inside the image, one
-            // candidate at a time (a neighbour of a strict maximum is none)
-            const int up = min(r_near, y), total = (up + min(r_near, H - 1 - y) + 1) * ww;
-            for (unsigned long long todo = r_iso > 1 ? found : 0; todo; todo &= todo - 1) {
+            // isolation: the wave scans the window, on small frames its rows inside the
+            // image, one candidate at a time (a neighbour of a strict maximum is none)
+            // a frac above 1 leaves most of them to the whole window
+            const int up = CLIP ? min(r_near, y) : r_near, total = CLIP ? (up + min(r_near, H - 1 - y) + 1) * ww : ww * ww;
+            for (unsigned long long todo = r_iso > 1 && !(FAR && frac > 1.) ? found : 0; todo; todo &= todo - 1) {
                 const int c = __ffsll(todo) - 1;
                 const float* centre = here - lane + c;
                 const double lim = frac * ((double)centre[0] - sky);
@@ -504,7 +511,8 @@ int svconv_stamp_mask(svconv_plan* p, const float* R, double sky, double thresho
     const int cx = (p->W + CENTRE_TX - 1) / CENTRE_TX, cy = (p->H + CENTRE_TY - 1) / CENTRE_TY;
     const int halo = (r_iso > CENTRE_WHOLE ? CENTRE_NEAR : r_iso) + 1;
     const size_t lds = (size_t)(CENTRE_TX + 2 * halo) * (CENTRE_TY + 2 * halo) * sizeof(float);   // <= 37 KB
-    const bool few = (long)cx * cy <= p->cus, far = r_iso > CENTRE_WHOLE;
+    const bool far = r_iso > CENTRE_WHOLE;
+    const bool few = (long)cx * cy <= (r_iso > CENTRE_NEAR && !far ? 4L : 2L) * p->cus;
     auto kernel = few ? (far ? centre_kernel<16, true> : centre_kernel<16, false>)
                       : (far ? centre_kernel<4, true> : centre_kernel<4, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)cx * cy), dim3(few ? 1024 : 256), lds, p->stream, R, p->H, p->W, sky,

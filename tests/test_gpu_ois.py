@@ -239,11 +239,11 @@ def test_normal_equations_with_background_match_oracle_fit(svc, orc, form, preci
     assert hist[-1][1] <= 1e-6 * hist[0][1]
 
 
-@pytest.mark.parametrize("shape", [(40, 50), (150, 333), (700, 1100)])
+@pytest.mark.parametrize("shape", [(40, 50), (150, 333), (700, 1100), (1060, 1300), (1100, 2000)])
 @pytest.mark.parametrize("r_iso,frac", [(2, 0.1), (16, 0.5), (24, 0.9), (25, 0.9), (25, 3.0), (40, 0.3), (64, 0.9)])
 def test_stamp_mask_crowded(svc, orc, shape, r_iso, frac):
     """Fields where most local maxima are candidates, with windows on both sides of
-    the staged halo; frames of few tiles and of more than one per CU; bit-exact."""
+    the staged halo; frames of up to one, two, four and more tiles per CU; bit-exact."""
     H, W = shape
     r = np.random.default_rng(H + r_iso)
     R = (SKY + r.normal(size=shape) * 30).astype(np.float32)
