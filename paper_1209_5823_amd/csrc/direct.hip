@@ -18,13 +18,13 @@
 // scalar registers at high order (31 x 31, sixth order, 256 x 256: 148 -> 58 us;
 // 31 x 31, third order, 2048 x 2048: 705 -> 616 us).
 //
-// Bound: the float64 FMA rate (161 FMAs and 74 other vector instructions per
-// pixel at 7 x 7, second order; the vector units issue on about three quarters
-// of the cycles).  7 x 7 delta basis, second order, 4846 x 4868: 315 us
-// (float32 FMAs over six terms, float64 row sums) -> 182 us, error against
-// float64 4.0e-8 -> 2.5e-8 of D; 21 x 21, 49 bases, second order, 2048 x 4096:
-// 741 us (float32 matrix cores) -> 450 us (482 with two sets of taps); 31 x 31,
-// third order, 2048 x 2048: 1323 -> 632 us.
+// Bound: the float64 FMA rate (248 vector instructions per pixel at 7 x 7,
+// second order, 165 of them FMAs, on 86 % of the cycles; 21 x 21: 88 %). 7 x 7
+// delta basis, second order, 4846 x 4868: 315 us (float32 FMAs over six terms,
+// float64 row sums) -> 182 us, error against float64 4.0e-8 -> 2.5e-8 of D; 21
+// x 21, 49 bases, second order, 2048 x 4096: 741 us (float32 matrix cores) ->
+// 450 us (482 with two sets of taps); 31 x 31, third order, 2048 x 2048: 1323
+// -> 632 us.
 //
 // Per kernel column du and DR_CH kernel rows (an item), the samples the
 // thread's rows need are read from LDS once and widened.  ROWS = 16 rows per
@@ -54,7 +54,7 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
 // TAPS_TABLE: taps64[du][dv][m]; TAPS_FORMED: the same table in LDS, formed by
 // every workgroup.
 enum { TAPS_TABLE = 0, TAPS_DELTA = 1, TAPS_FORMED = 2 };
-// HC: the half-width where it is known at compile time, else 0.
+
 // Filter entry idx of M k^2 (m, then dv, du): sum_n a[n][m] F_n[dv][du], and its
 // place in a table [du][dv][m].
 __device__ __forceinline__ double regrouped_tap(const double* __restrict__ F64, const float* __restrict__ a, int N,
@@ -68,6 +68,7 @@ __device__ __forceinline__ double regrouped_tap(const double* __restrict__ F64, 
     return s;
 }
 
+// HC: the half-width where it is known at compile time, else 0.
 template <int J, int ROWS, int WAVES, int S, int SRC, int HC>
 __global__ __launch_bounds__(64 * WAVES) void contract_direct_kernel(DirectArgs a) {
     constexpr int DS = J - 1, M = J * (J + 1) / 2;
