@@ -280,13 +280,22 @@ static int direct_tiles(const DirectArgs& a, int th) { return a.tiles_x * ((a.H 
 // 10.3 without; the dense product takes 10.1).  More rounds only where few
 // workgroups repeat them (700 x 760, 7 x 7, 22 bases, second order: 13.8 us with
 // the launch, 16.3 without).
-constexpr int FORMED_J = 3;
+constexpr int FORMED_J = 4;   // up to third order
 
 bool direct_forms_taps(int H, int W, int h, int d_s, int N, int cus) {
     const int M = (d_s + 1) * (d_s + 2) / 2, taps = M * (2 * h + 1) * (2 * h + 1);
     const long tiles = (long)((W + DR_TW - 1) / DR_TW) * ((H + 31) / 32);
     const int rounds = (taps + 255) / 256 * ((N + 7) / 8);
-    return d_s < FORMED_J && tiles <= 2L * cus && rounds <= (tiles <= cus && (N <= 8 || taps <= 75) ? 8 : 3);
+    return d_s <= 2 && tiles <= 2L * cus && rounds <= (tiles <= cus && (N <= 8 || taps <= 75) ? 8 : 3);
+}
+
+// Whether the table fits LDS beside the largest tile.  Forming it there keeps
+// float64 without a table in memory whatever the number of bases (replays, 49
+// bases, 21 x 21, 2048 x 4096: second order 625 us, 510 with a table, the dense
+// product 6.4 ms; third order 955, 640 and 6.5 ms).
+bool direct_can_form_taps(int h, int d_s) {
+    const int M = (d_s + 1) * (d_s + 2) / 2, k = 2 * h + 1, rows = 64 + (k + DR_CH - 1) / DR_CH * DR_CH;
+    return d_s < FORMED_J && (size_t)rows * (DR_TW + 2 * h) * sizeof(float) + (size_t)k * k * M * sizeof(double) <= 160 * 1024;
 }
 
 template <int J, int ROWS, int WAVES, int S, int HC = 0>
@@ -350,7 +359,7 @@ static void launch_direct_rows(const DirectArgs& a, hipStream_t s) {
 int launch_contract_direct(DirectArgs a, hipStream_t s) {
     a.tiles_x = (a.W + DR_TW - 1) / DR_TW;
     if (a.h < 0 || a.h > kMaxHalfWidth || a.H <= 0 || a.W <= 0 || a.cus <= 0 || !!a.taps + !!a.taps64 + !!a.coef != 1 ||
-        (a.coef && (!a.F64 || !direct_forms_taps(a.H, a.W, a.h, a.d_s, a.N, a.cus))))
+        (a.coef && (!a.F64 || !direct_can_form_taps(a.h, a.d_s))))
         return fail(SVCONV_EUNSUPPORTED, "direct regrouped kernel: bad arguments");
     switch (a.d_s) {
         case 0: launch_direct_rows<1>(a, s); break;

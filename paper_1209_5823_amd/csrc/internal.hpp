@@ -133,7 +133,7 @@ struct DirectArgs {
     // exactly one of the three is set:
     const float* taps;          // Dirac delta basis: a [k^2][M]
     const double* taps64;       // regrouped filters [du][dv][M] (regroup_filters64)
-    const float* coef;          // a [N][M]: the kernel forms the filters from F64 [N][k][k] (direct_forms_taps)
+    const float* coef;          // a [N][M]: the kernel forms the filters from F64 [N][k][k] (direct_can_form_taps)
     const double* F64;
     int N;
     double sx, ox, sy, oy;
@@ -156,12 +156,13 @@ static_assert(kVecPivots + kMaxCoefficients <= kVecSepCoef && kVecSepCoef + kMax
               "parts of the vector scratch overlap");
 
 // Whose the plan's table of regrouped filters at an index is: one stream's,
-// outside capture or in one capture of it.
+// outside capture or in one capture of it (the per-thread default stream, one
+// handle for the streams of all threads: with its thread).
 constexpr int kTapSlots = 64;
 struct TapSlot {
     bool taken = false, capturing = false;
     hipStream_t stream = nullptr;
-    unsigned long long capture = 0;
+    unsigned long long capture = 0, thread = 0;
 };
 
 }  // namespace svc
@@ -284,8 +285,9 @@ int launch_contract_sepz(SepZArgs a, int precision, hipStream_t s);
 // direct.hip
 int regroup_filters64(const double* F64, const float* a, int N, int M, int k, double* taps, hipStream_t s);
 int launch_contract_direct(DirectArgs a, hipStream_t s);
-// whether the kernel had better form the filters of N bases itself
+// whether the kernel had better form the filters of N bases itself, and whether it can
 bool direct_forms_taps(int H, int W, int h, int d_s, int N, int cus);
+bool direct_can_form_taps(int h, int d_s);
 
 // Both separable forms go through the one-dimensional factors in the adjoints
 // and the fit.

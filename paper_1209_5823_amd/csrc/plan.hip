@@ -317,12 +317,14 @@ static bool direct_beats_separable(const svconv_plan* p) {
 // direct route keeps that: work on one stream is in order and shares a table, a
 // capture has its own (its replays run beside whatever the streams do later).
 // 64 tables: a stream pool of 32, the default stream, and graphs.  The calls of
-// any further stream or capture take the dense product, as do those on the
-// per-thread default stream, one handle for the streams of all threads.
+// any further stream or capture form the filters in the kernel or, where those
+// do not fit it, take the dense product.
 static double* tap_slot(svconv_plan* p) {
+    static std::atomic<unsigned long long> threads{0};
+    static thread_local const unsigned long long thread = ++threads;   // never used again
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     TapSlot want;
-    if (!p->dTaps || p->stream == hipStreamPerThread) return nullptr;
+    if (!p->dTaps) return nullptr;
     if (hipStreamGetCaptureInfo(p->stream, &status, &want.capture) != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
@@ -331,10 +333,12 @@ static double* tap_slot(svconv_plan* p) {
     want.capturing = status != hipStreamCaptureStatusNone;
     if (!want.capturing) want.capture = 0;
     want.stream = p->stream;
+    if (p->stream == hipStreamPerThread) want.thread = thread;
     int at = -1;
     for (int i = 0; i < kTapSlots && (at < 0 || !p->tap_slots[at].taken); ++i) {
         const TapSlot& t = p->tap_slots[i];
-        const bool mine = t.taken && t.stream == want.stream && t.capturing == want.capturing && t.capture == want.capture;
+        const bool mine = t.taken && t.stream == want.stream && t.thread == want.thread &&
+                          t.capturing == want.capturing && t.capture == want.capture;
         if (mine || (!t.taken && at < 0)) at = i;
     }
     if (at < 0) return nullptr;
@@ -397,13 +401,15 @@ int run_forward(svconv_plan* p, const float* R, const float* I, const float* a, 
     const bool split = p->precision == SVCONV_FP16X3 || p->precision == SVCONV_BF16X3 || p->precision == SVCONV_FP16X2;
     // Gaussian plans: the regrouped filters of the direct route, none where it is not taken
     double* taps = nullptr;
-    const bool formed = p->form == SVCONV_FORM_BASIS && !lowp && p->dTaps &&
-                        direct_forms_taps(p->H, p->W, p->h, p->d_s, p->N, p->cus);
+    bool formed = p->form == SVCONV_FORM_BASIS && !lowp && p->dTaps &&
+                  direct_forms_taps(p->H, p->W, p->h, p->d_s, p->N, p->cus);
     if (p->form == SVCONV_FORM_SEPARABLE ? !split && direct_beats_separable(p)
                                          : !lowp && p->form == SVCONV_FORM_REGROUPED)
         taps = reinterpret_cast<double*>(p->dFt32);
-    else if (p->form == SVCONV_FORM_BASIS && !lowp && !formed)
+    else if (p->form == SVCONV_FORM_BASIS && !lowp && !formed) {
         taps = tap_slot(p);
+        formed = !taps && p->dTaps && direct_can_form_taps(p->h, p->d_s);
+    }
     if (taps || formed || (p->dfb && !lowp)) {
         // regrouped in float64 on the vector units.  The responses of a delta
         // basis are shifted pixels, so its basis form is the same sum anyhow.

@@ -86,29 +86,87 @@ def test_streams_overlap(svc):
             assert np.array_equal(to_host(got), want)
 
 
-@pytest.mark.parametrize("deg", [DEG, (4, 2, 0), (7,), (3,)])
-def test_more_captures_than_tables(svc, orc, deg):
-    """Past the last table a call takes the dense product, which needs none (49, 22,
-    36 and 10 bases: each number of its 16-filter blocks); the streams that hold one
-    keep it."""
+@pytest.mark.parametrize("deg,d_s", [(DEG, 0), (DEG, 2), (DEG, 3), (DEG, 4), ((4, 2, 0), 4), ((7,), 4), ((3,), 4)])
+def test_more_captures_than_tables(svc, orc, deg, d_s):
+    """Past the last table the kernel forms the filters, to the same bits, or above
+    third order a call takes the dense product, which needs none (49, 22, 36 and 10 bases:
+    each number of its 16-filter blocks); the streams that hold one keep it."""
     import torch
     R, I, sig = *_case(0)[:2], SIG[:len(deg)]
-    a = synth.coefficients(synth.n_basis(deg), synth.n_spatial(DS), 0, seed=1)
+    a = synth.coefficients(synth.n_basis(deg), synth.n_spatial(d_s), 0, seed=1)
     Rd, Id, ad = to_dev(R), to_dev(I), to_dev(a)
-    say("captures past the last table", deg)
-    with svc.Plan(H, W, HALF, sig, deg, DS, pedestal=1000.0) as plan:
+    say("captures past the last table", deg, d_s)
+    with svc.Plan(H, W, HALF, sig, deg, d_s, pedestal=1000.0) as plan:
         first, out = to_host(plan.difference(Rd, Id, ad)), torch.empty_like(Rd)
         tables = [_table(capture(lambda: plan.difference(Rd, Id, ad, out=out))) for _ in range(70)]
         had = [t for t in tables if t is not None]
         assert 32 <= len(had) < 70 and len(set(had)) == len(had)
         assert tables[len(had):] == [None] * (70 - len(had))
-        dense = capture(lambda: plan.difference(Rd, Id, ad, out=out))
-        assert any("contract_f32_kernel" in k.name for k in kernels(dense))
-        dense.instantiate()
-        dense.replay()
-        want = orc.difference(R, I, HALF, orc.basis(HALF, sig, deg), DS, a)
+        past = capture(lambda: plan.difference(Rd, Id, ad, out=out))
+        route = "contract_direct_kernel" if d_s <= 3 else "contract_f32_kernel"
+        assert any(route in k.name for k in kernels(past))
+        past.instantiate()
+        past.replay()
+        if d_s <= 3:
+            assert np.array_equal(to_host(out), first)
+        want = orc.difference(R, I, HALF, orc.basis(HALF, sig, deg), d_s, a)
         assert err_stats(to_host(out), want)[0] <= TOL_FP32
         assert np.array_equal(to_host(plan.difference(Rd, Id, ad)), first)
+
+
+@pytest.mark.parametrize("half,d_s,fits", [(22, 2, True), (23, 2, True), (24, 2, False), (18, 3, True), (19, 3, False)])
+def test_filters_formed_in_lds_at_its_limit(svc, half, d_s, fits):
+    """The largest table that fits beside a tile, and the first that does not (which
+    the dense product takes, to its own accuracy)."""
+    import torch
+    R, I = _case(0)[:2]
+    a = synth.coefficients(synth.n_basis(DEG), synth.n_spatial(d_s), 0, seed=1)
+    Rd, Id, ad = to_dev(R), to_dev(I), to_dev(a)
+    say("filters formed in LDS, half-width", half, d_s)
+    with svc.Plan(H, W, half, SIG, DEG, d_s, pedestal=1000.0) as plan:
+        first, out = to_host(plan.difference(Rd, Id, ad)), torch.empty_like(Rd)
+        for _ in range(70):
+            g = capture(lambda: plan.difference(Rd, Id, ad, out=out))
+        assert _table(g) is None
+        assert any("contract_direct_kernel" in k.name for k in kernels(g)) == fits
+        g.instantiate()
+        g.replay()
+        if fits:
+            assert np.array_equal(to_host(out), first)
+        assert err_stats(to_host(out), first)[0] <= TOL_FP32
+
+
+def test_per_thread_streams_overlap(svc):
+    """The per-thread default stream is one handle for every thread's own stream."""
+    import ctypes
+    import threading
+    import torch
+    R, I, a = _case(2)
+    Rd, Id, ad = to_dev(R), to_dev(I), [to_dev(x) for x in a]
+    say("per-thread default streams of a basis-form plan")
+    with _plan(svc) as plan:
+        alone = [to_host(plan.difference(Rd, Id, x)) for x in ad]
+        out = [torch.empty_like(Rd) for _ in ad]
+        turn, bad = threading.Lock(), []
+        torch.cuda.synchronize()
+
+        def work(i):
+            for _ in range(20):
+                with turn:   # one thread at a time calls; what they enqueue overlaps
+                    if plan._lib.svconv_plan_set_stream(plan._p, ctypes.c_void_p(2)):
+                        bad.append(i)
+                    args = [ctypes.c_void_p(t.data_ptr()) for t in (Rd, Id, ad[i], out[i])]
+                    if plan._lib.svconv_difference(plan._p, *args):
+                        bad.append(i)
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+        assert not bad
+        for got, want in zip(out, alone):
+            assert np.array_equal(to_host(got), want)
 
 
 def test_pipelines_give_their_table_back(svc):
